@@ -70,6 +70,9 @@ struct SortArgs {
     int32_t* admit_seq;
 };
 
+// Progress counters of one launch: one per cache line.
+enum { PROG_LINES = 64, PROG_STRIDE = 16, PROG_WORDS = PROG_LINES * PROG_STRIDE };
+
 struct SimArgs {
     const int64_t* offsets;
     const int32_t* a;
@@ -96,13 +99,14 @@ struct SimArgs {
     int32_t M;
     int32_t max_steps;
     int64_t step_delta;       // steps to simulate in this launch
-    int32_t* lst_f;           // [G*list_stride] event path, list profile: planned finishes
-    uint32_t* lst_q;          // [G*list_stride]   and prefix sums of s - k
+    int32_t* lst_f;           // [G*list_stride] list profile: planned finishes
+    uint32_t* lst_q;          // [G*list_stride]   and D(F) + F (event path) or prefix sums of s - k
     int32_t list_stride;      // entries per segment in HBM (bound on concurrent requests)
-    int32_t list_cap;         // entries per segment in LDS in this launch (<= list_stride)
+    int32_t list_cap;         // entries per segment in this launch (in LDS and registers)
+    int32_t list_nb;          // event path: bitmap pairs in registers (0: bitmap in LDS)
     int32_t list_resume;      // 1: only continue the segments that stopped with a full list
     int32_t resident;         // workgroups of this launch resident at once (0: no issue priorities)
-    unsigned long long* prog; // [1] progress counter of this launch, cleared before it
+    unsigned long long* prog; // [PROG_WORDS] progress counters of this launch, cleared before it
 };
 
 struct FinArgs {
@@ -132,17 +136,25 @@ hipError_t launch_build_rec(const SortArgs& A, int nchunks, hipStream_t s);
 enum { SORT_REC_MAX = 8192 };
 hipError_t prepare_sort_rec(int max_n);
 hipError_t launch_sort_rec(const SortArgs& A, int G, int max_n, hipStream_t s);
-hipError_t prepare_sim(bool d_lds, size_t lds_ring, bool list, size_t lds_list);
-// entries of LDS the finish-ordered list of capacity cap takes (F and Q each)
+hipError_t prepare_sim(bool d_lds, size_t lds_ring, bool step_list, size_t lds_step);
+// per-step path: entries of LDS the finish-ordered list of capacity cap takes (F and Q each)
 __host__ __device__ inline int list_slots(int cap) { return cap + 65; }
+// Event path: the register form of the kernel for instances of at most max_n
+// requests, the LDS of a list of capacity cap besides the bitmap, the finished
+// entries that may wait at its front, and its kernels.
+inline int list_bitmap_pairs(int max_n) { return max_n <= 4096 ? 1 : (max_n <= 8192 ? 2 : 0); }
+inline size_t list_lds(int64_t cap) { return (size_t)(64 + (cap > 64 ? cap - 64 : 0)) * 8; }
+enum { LIST_DEAD_MAX = 32 };
+hipError_t prepare_list(int nb, size_t lds_first, size_t lds_full);
+// resident waves per compute unit of its first launch
+hipError_t list_occupancy(int nb, size_t lds_bytes, int* blocks);
 // list: the event path keeps its profile as the finish-ordered list
 hipError_t launch_sim(const SimArgs& P, int G, bool d_lds, bool stepped, bool list,
                       size_t lds_bytes, hipStream_t s);
-// resident waves per compute unit of the event kernel (ring or list profile)
-hipError_t sim_known_occupancy(bool list, bool d_lds, size_t lds_bytes, int* blocks);
 // resident waves per compute unit of the per-step kernel with the list
 hipError_t sim_step_occupancy(size_t lds_bytes, int* blocks);
-// resident waves per compute unit of the first simulation kernel of a path
+// resident waves per compute unit of the first per-step kernel (list: with the
+// list profile), or of the event kernel with the ring
 hipError_t sim_occupancy(bool stepped, bool list, bool d_lds, size_t lds_bytes, int* blocks);
 hipError_t launch_finalize(const FinArgs& F, int G, hipStream_t s);
 // Device address and size of the calling thread's current device's scratch

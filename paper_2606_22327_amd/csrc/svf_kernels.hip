@@ -13,7 +13,7 @@
 //                     (each element finds its output slot by binary search in
 //                     the partner run)
 //   k_build_rec       rank-ordered request records and the index->rank map
-//   k_sim<D_LDS, STEPPED>, k_sim_list, k_sim_list_resume, k_sim_steplist,
+//   k_sim<D_LDS, STEPPED>, k_sim_list<NB, RESUME>, k_sim_steplist,
 //   k_sim_steplist_stop, k_sim_steplist_resume
 //                     the simulation: one wave64 per segment (profile as a ring,
 //                     per-step or event-driven; or as a finish-ordered list);
@@ -38,10 +38,10 @@
 // pass over its own window: max_{j<o^_h} D[t+1+j] + (s_h + j + 1) <= M.
 // Admitting h adds its growth to the same window; a step that becomes past is
 // folded into the peak statistic and cleared.  The other form of the profile
-// is the list of running requests ordered by planned finish, with prefix sums
-// of s - k: between admissions the memory only drops at finishes, so the
-// check visits just the finishes inside the candidate's window and its last
-// step (ListProf, StepList).  The host picks the form per batch: the list
+// is the list of running requests ordered by planned finish: between
+// admissions the memory only drops at finishes, so the check visits just the
+// finishes inside the candidate's window and its last step (ListProf with the
+// loop of svf_event_loop.h, StepList).  The host picks the form per batch: the list
 // where few requests run at once, the ring where many do.
 //
 // Known lengths (the scheduler plans with the true length) make D change only
@@ -60,6 +60,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "svf_event_loop.h"
 #include "svf_kernels.h"
 
 namespace svfk {
@@ -487,7 +488,11 @@ __device__ __forceinline__ int wmin(int v) {
 // waves, which issue far less per cycle than a full CU.  Instead the waves
 // keep one counter per launch: the number of running waves and the sum of
 // their remaining requests (admissions still to make, or requests still to
-// finish), updated every 32 requests and when a wave starts and ends.  A
+// finish), updated every 32 or 64 requests and when a wave starts and ends.
+// The counter is split over PROG_LINES cache lines by workgroup number (and
+// with it over the XCDs, whose L2s then keep their own lines): adds to one
+// address complete one per 13.5 ns, which held the heavy-traffic launch to
+// 17.4 ms; the mean over every 64th wave serves as well.  A
 // wave with more remaining than the mean gets a higher level (four levels,
 // 1/64 of its segment apart): remaining work evens out, and the waves that
 // are running when the last ones start end at about the same time.  The
@@ -506,8 +511,9 @@ struct IssuePrio {
     __device__ __forceinline__ void init(const SimArgs& P, int n_, int done) {
         next = INT32_MAX;
         ctr = nullptr;
+        th = last = 0;
         if (P.resident <= 0 || n_ <= 0 || P.prog == nullptr || done >= n_) return;
-        ctr = P.prog;
+        ctr = P.prog + PROG_STRIDE * (blockIdx.x % PROG_LINES);
         n = n_;
         th = max(n / 64, 1);
         last = done;
@@ -896,193 +902,183 @@ struct RingProf {
     }
 };
 
-// The running requests sorted by planned finish F, latest first (entry 0 has
-// the largest F), with Q_j = sum over the entries 0..j of (s - k), k the step a
-// request was started at, in wrapping 32-bit arithmetic (every quantity formed
-// from it fits in int32).  The memory at step tau is D(tau) = sum over running
-// requests with F >= tau of (s - k + tau).  Between two finish steps it grows with tau, so the check of
-// a candidate (size s_h, planned length oh) started at t needs only the steps
-// tau = F_j <= te = t + oh and tau = te:
-//   D(F_j) + F_j = Q_j + F_j (j + 2)      (the entries 0..j have F >= F_j),
-//   D(te) + te   = Q_{c-1} + te (c + 1)   (c entries have F >= te),
-// each at most M - s_h + t (Appendix E.2, eq:c2).  These are the last entries
-// of the list, read from the end in groups of 64 until an entry with F > te
-// shows up; a short candidate touches one group.  Admission inserts the
-// candidate at c: the entries behind it move up by one and gain s_h - t in
-// Q.  Requests finished by t are the last entries and are dropped at each
-// visited step; D at their finish step goes into the peak.  The host bounds
-// the requests that can run at once; the list in LDS may hold fewer (more
-// waves then fit on a compute unit).  A candidate that fits into a full list
-// gets *t_free = -1 (a real failure always gives a step after t): the segment
-// stops at that step with the candidate as the head, and a later launch with
-// room for the bound continues it.
+// One step down the lanes: lane i gets lane i-1's value (lane 0: undefined).
+__device__ __forceinline__ int lane_up(int v) {
+    return __builtin_amdgcn_update_dpp(v, v, 0x138, 0xf, 0xf, false);  // wave_shr:1
+}
+
+// v with lane l (uniform) replaced by the uniform x.
+__device__ int amdgcn_writelane(int x, int l, int v) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ int setlane(int v, int x, int l) { return amdgcn_writelane(x, l, v); }
+
+// The running requests ordered by planned finish F (Section 3.1, eq:c2).  A
+// request started at k with size s holds c + tau at step tau, c = s - k, so
+// with the entries 0, 1, .. in descending order of F the memory at the finish
+// step of entry j is D(F_j) = sum of c over the entries 0..j + (j + 1) F_j.
+// Between two finishes D grows with tau, so the check of a candidate (size
+// s_h, planned length oh) started at t needs only the finishes F_j < te =
+// t + oh and te itself, each at most M - s_h + t for D(tau) + tau
+// (Appendix E.2).
 //
-// Every lane of a group takes part in every step, so that no lane is masked
-// off (the scalar unit, which would juggle the masks, is the busiest unit of
-// this kernel): lanes past the last entry of a group read a copy of that
-// entry, which leaves maxima unchanged and is taken out of counts, and the
-// shift of an insertion writes each lane's entry to a position of its own (a
-// lane whose entry stays rewrites it in place; the lane of entry c-1 writes
-// the candidate; lanes past the group's end write to a slot of their own
-// behind the capacity, so the arrays have 65 slots more than the list may
-// hold).
+// Each entry keeps F and G = D(F) + F, the very value the check compares, so
+// a check is a masked maximum with no product and no prefix sum to read.  An
+// admission at te changes exactly the entries that finish before te: each
+// gains c_h = s_h - t for itself and F for its new position, G += F + c_h.
+// At te, with entry a (position j) the next one to finish at or after te,
+// D(te) + te = G_a - (F_a - te)(j + 2).  All in wrapping 32-bit arithmetic
+// (every quantity formed from it fits in int32).
+//
+// The 64 entries that finish first are in registers, lane i holding the one
+// with i entries before it in order of finish; the others are a stack in LDS.  Most candidates finish among the first 64, so
+// a check reads no memory, and an admission moves the lanes from its place up
+// by one (a DPP move) and pushes the last lane's entry.
+// Finished entries are the first lanes: they stay there, out of every range,
+// until 32 have gathered and the list moves down.  Places past the
+// list hold (INT32_MAX, INT32_MAX), the entry for which the formula above
+// gives D(te) + te = te.
+//
+// The host bounds the requests that can run at once; the LDS may hold fewer
+// (more waves then fit on a compute unit).  A candidate that fits into a full
+// list gets *t_free = -1 (a real failure always gives a step after t): the
+// segment stops at that step with the candidate as the head, and a later
+// launch with room for the bound continues it.
 struct ListProf {
-    int32_t* F;     // [list_slots(cap)] planned finish, descending
-    uint32_t* Q;    // [list_slots(cap)] prefix sums of s - k
-    int cap;        // capacity
-    int ln;         // entries
-    uint32_t tot;   // Q of the last entry (0 if none)
+    int F, G;
+    int2* stk;      // LDS: stk[j] is entry j; 64 empty entries below stk[0]
+    int cap;        // capacity, registers included
+    int ln;         // entries, the finished ones at the front included
+    int dead;       // finished entries still at the front
+    int tprev;      // the step of the last begin
     int peak_lane;
-    __device__ __forceinline__ void begin(int t) {
+
+    __device__ __forceinline__ void load(const int32_t* f, const uint32_t* g, int n) {
         const int lane = lane_id();
-        while (ln > 0) {
-            const int top = ln, base = max(top - 64, 0);
-            const int jr = min(base + lane, top - 1);
-            const int f = F[jr];
-            const uint32_t q = Q[jr];
-            const bool done = f <= t;
-            const uint64_t dm = ballot(done);
-            if (dm == 0ull) break;
-            // the memory at the finish step of a finished request
-            peak_lane = max(peak_lane, done ? (int)(q + (uint32_t)f * (uint32_t)(jr + 1)) : 0);
-            // the finished ones end the group; copies of the last entry are
-            // among them
-            ln = top - ((int)__popcll(dm) - (64 - (top - base)));
-            if (ln > base) {
-                tot = (uint32_t)__builtin_amdgcn_readlane((int)q, ln - 1 - base);
-                break;
-            }
-            if (ln == 0) {
-                tot = 0u;
-                if (lane == 0) F[0] = INT32_MAX;  // an empty list reads as "finishes last"
-                lds_order();
-            }
-        }
-    }
-    __device__ __forceinline__ bool fit(int t, int s_h, int oh, int M, int maxF, int* t_free) {
-        (void)maxF;
-        const int lane = lane_id();
-        const int te = t + oh;
-        const int X = M - s_h;
-        const int lim = X + t;
-        // groups of 64 entries from the end, down to the one holding an entry
-        // with F > te (its first entry has the largest F) or the first entry
-        int m = INT32_MIN;
-        int top = ln, base, f, jr;
-        uint32_t q;
-        for (;;) {
-            base = max(top - 64, 0);
-            jr = min(base + lane, max(top - 1, 0));
-            f = F[jr];
-            q = Q[jr];
-            m = max(m, f <= te ? (int)(q + (uint32_t)f * (uint32_t)(jr + 2)) : INT32_MIN);
-            if (base == 0) break;
-            if (__builtin_amdgcn_readfirstlane(f) > te) break;
-            top = base;
-        }
-        // c = entries with F >= te (a prefix of the group, copies excluded)
-        const int ge = min((int)__popcll(ballot(f >= te)), top - base);
-        const int c = base + ge;
-        const uint32_t qc1 = ge > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)q, ge - 1) : 0u;
-        const int ve = (int)(qc1 + (uint32_t)te * (uint32_t)(c + 1));
-        if (ballot(max(m, ve) > lim) != 0ull) {
-            // the release step: max over the violating steps of min(tau, D + tau - X),
-            // over the same groups again (base: the lowest one scanned)
-            int rel = min(te, ve - X);
-            if (top == ln) {  // one group, still in the registers
-                const int v = (int)(q + (uint32_t)f * (uint32_t)(jr + 2));
-                rel = max(rel, f <= te ? min(f, v - X) : INT32_MIN);
-            } else {
-                for (int tp = ln;;) {
-                    const int b = max(tp - 64, 0);
-                    const int jj = min(b + lane, tp - 1);
-                    const int ff = F[jj];
-                    const int v = (int)(Q[jj] + (uint32_t)ff * (uint32_t)(jj + 2));
-                    rel = max(rel, ff <= te ? min(ff, v - X) : INT32_MIN);
-                    if (b <= base) break;
-                    tp = b;
-                }
-            }
-            *t_free = wmax(rel);
-            return false;
-        }
-        if (ln >= cap) {
-            *t_free = -1;
-            return false;
-        }
-        // the entries c .. ln-1 move up by one and gain s_h - t, group by
-        // group from the end (no entry is overwritten unread); entry c-1
-        // writes the candidate behind itself
-        const uint32_t ch = (uint32_t)(s_h - t);
-        const uint32_t qn = qc1 + ch;
-        auto shift = [&](int b, int tp, int ff, uint32_t qq) {
-            const int j = b + lane;
-            const bool mv = j >= c - 1;
-            const bool nw = j == c - 1;
-            // lanes past the group's end: a slot of their own behind the capacity
-            const int pos = j < tp ? (mv ? j + 1 : j) : cap + 1 + lane;
-            F[pos] = nw ? te : ff;
-            Q[pos] = nw ? qn : (mv ? qq + ch : qq);
-        };
-        if (top == ln) {
-            // the check read only the last group, which holds entry c-1 (or
-            // is the first group): shift it from the registers
-            shift(base, top, f, q);
-        } else {
-            // groups down to the one holding entry max(c-1, 0)
-            const int groups = max((ln - max(c - 1, 0) + 63) >> 6, 1);
-            for (int g = 0, tp = ln; g < groups; ++g, tp -= 64) {
-                const int b = max(tp - 64, 0);
-                const int jj = min(b + lane, max(tp - 1, 0));
-                shift(b, tp, F[jj], Q[jj]);
-            }
-        }
-        if (c == 0) {  // no entry before the candidate (every lane stores the same values)
-            F[0] = te;
-            Q[0] = qn;
-        }
+        ln = n;
+        const int j = n - 1 - lane;
+        F = j >= 0 ? f[j] : INT32_MAX;
+        G = j >= 0 ? (int)g[j] : INT32_MAX;
+        stk[lane - 64] = make_int2(INT32_MAX, INT32_MAX);
+        for (int x = lane; x < n - 64; x += 64) stk[x] = make_int2(f[x], (int)g[x]);
         lds_order();
-        ++ln;
-        tot += ch;
-        return true;
     }
+    __device__ __forceinline__ void store(int32_t* f, uint32_t* g) const {
+        const int lane = lane_id();
+        const int j = ln - 1 - lane;
+        if (j >= 0) {
+            f[j] = F;
+            g[j] = (uint32_t)G;
+        }
+        for (int x = lane; x < ln - 64; x += 64) {
+            const int2 e = stk[x];
+            f[x] = e.x;
+            g[x] = (uint32_t)e.y;
+        }
+    }
+    // the first k entries (finished, 0 < k <= 64) leave
+    __device__ __forceinline__ void drop(int k) {
+        const int lane = lane_id();
+        const int src = ((lane + k) & 63) << 2;
+        const bool own = lane + k < 64;
+        const int2 x = stk[own ? -1 : max(ln - 1 - lane - k, -1)];
+        const int f = __builtin_amdgcn_ds_bpermute(src, F), g = __builtin_amdgcn_ds_bpermute(src, G);
+        F = own ? f : x.x;
+        G = own ? g : x.y;
+        ln -= k;
+    }
+    // The peak over the steps up to t; no finished entry is left.
     __device__ __forceinline__ int end(int t) {
-        begin(t);
+        for (;;) {
+            const int nd = (int)__popcll(ballot(F <= t));
+            // the memory at the finish step of the newly finished ones
+            const bool nw = (uint32_t)(F - tprev - 1) < (uint32_t)(t - tprev);
+            peak_lane = max(peak_lane, nw ? G - F : 0);
+            if (nd == 0) break;
+            drop(nd);
+        }
+        dead = 0;
+        tprev = t;
         // the memory at step t of the requests still running
-        if (ln > 0) peak_lane = max(peak_lane, (int)(tot + (uint32_t)t * (uint32_t)ln));
+        if (ln > 0) {
+            const int f0 = __builtin_amdgcn_readfirstlane(F), g0 = __builtin_amdgcn_readfirstlane(G);
+            peak_lane = max(peak_lane, g0 - f0 - (f0 - t) * ln);
+        }
         return wmax(peak_lane);
     }
 };
 
+// The waiting set of the event path with the ring: a bitmap over priority
+// ranks, two levels in LDS.  open() brings one word into scalar registers for
+// the admissions of a step, which clear its bits there; close() puts it back.
+struct LdsBits {
+    uint64_t* B;
+    uint64_t* S;
+    int W0, W1;
+    int cw;
+    uint64_t cbits;
+    __device__ __forceinline__ void set(uint64_t m, int rk) {
+        // the other lanes add nothing to words of their own
+        const bool in = (m >> lane_id()) & 1ull;
+        const int w = in ? rk >> 6 : min(lane_id(), W0 - 1);
+        atomicOr((unsigned long long*)&B[w], in ? 1ull << (rk & 63) : 0ull);
+        atomicOr((unsigned long long*)&S[w >> 6], in ? 1ull << (w & 63) : 0ull);
+        lds_order();
+    }
+    __device__ __forceinline__ void open(int r) {
+        cw = r >> 6;
+        const uint64_t v = B[cw];
+        const uint32_t lo = (uint32_t)uni((int)(uint32_t)v);
+        const uint32_t hi = (uint32_t)uni((int)(uint32_t)(v >> 32));
+        cbits = ((uint64_t)hi << 32) | lo;
+    }
+    __device__ __forceinline__ void clear(int r) { cbits &= ~(1ull << (r & 63)); }
+    // every lane stores the same word (no lane mask to set up)
+    __device__ __forceinline__ void close() {
+        B[cw] = cbits;
+        if (cbits == 0ull) S[cw >> 6] &= ~(1ull << (cw & 63));
+        lds_order();
+    }
+    __device__ __forceinline__ int next() {
+        if (cbits == 0ull) {
+            close();
+            const int r = bitmap_first(B, S, W1);
+            if (r < 0) return -1;
+            open(r);
+        }
+        return cw * 64 + __builtin_ctzll(cbits);
+    }
+};
 
-template <class PROF>
-__device__ void run_known(const SimArgs& P, const Seg& sg, uint64_t* B, uint64_t* S, int W1,
-                          PROF& prof, SegState& st, int t_lim) {
+template <class PROF, class BITS>
+__device__ __forceinline__ void run_known(const SimArgs& P, const Seg& sg, BITS& bits, PROF& prof,
+                                          SegState& st, int t_lim) {
     const int lane = lane_id();
     const int M = P.M;
     const int n = sg.n;
     // admissions so far: seq0 + nstg (known lengths: every admitted request
     // is finished at start + o, so no other count is needed)
-    int t = uni(st.t), cursor = uni(st.cursor), seq0 = uni(st.seq);
+    int t = uni(st.t), seq0 = uni(st.seq);
     int max_fin = uni(st.max_fin), head = uni(st.head_rank), t_f = uni(st.t_f);
+    const int t_stop = min(t_lim, P.max_steps + 1);
     int status = STATUS_RUNNING;
 
-    // Arrival window: lane l holds request wb + l (arrival, rank, record).
-    int wb = 0, a_reg = INT32_MAX, rk_reg = 0;
+    // Arrival window: lane l holds request wb + l (arrival, rank, record);
+    // pend: the lanes still to arrive (arrivals are sorted: a suffix).
+    int wb = 0, a_reg = INT32_MAX, rk_reg = INT32_MAX;
+    uint64_t pend = ~0ull;
     int4 aq = make_int4(0, 0, 0, 0);
+    // (no lane-dependent branch in the loop: lanes past the end read the last
+    // request again)
     auto load_arrivals = [&](int base) {
-        wb = uni(base);
-        const int i = base + lane;
-        a_reg = INT32_MAX;
-        rk_reg = 0;
-        if (i < n) {
-            a_reg = sg.a[i];
-            rk_reg = sg.rank[i];
-            if ((unsigned)rk_reg >= (unsigned)n) rk_reg = 0;  // only a broken sort
-            aq = sg.rec[rk_reg];
-        }
+        wb = base;
+        pend = ~0ull;
+        const int i = min(base + lane, n - 1);
+        const int av = sg.a[i];
+        const int rk = (int)min((uint32_t)sg.rank[i], (uint32_t)(n - 1));  // (in range unless the sort broke)
+        aq = sg.rec[rk];
+        a_reg = base + lane < n ? av : INT32_MAX;
+        rk_reg = base + lane < n ? rk : INT32_MAX;
     };
-    load_arrivals(cursor);
+    if (n > 0) load_arrivals(uni(st.cursor));
 
     // the record of one rank: a scalar load (read-only while the simulation runs)
     auto rec_of = [&](int r) -> int4 { return record(sg.rec, r); };
@@ -1095,142 +1091,183 @@ __device__ void run_known(const SimArgs& P, const Seg& sg, uint64_t* B, uint64_t
     int stg_idx = 0, stg_t = 0, nstg = 0;
     IssuePrio prio;
     prio.init(P, n, seq0);
-    auto flush = [&]() {
-        if (lane < nstg) {
-            sg.start[stg_idx] = stg_t;
-            sg.admit_seq[stg_idx] = seq0 + lane;
-        }
-        seq0 += nstg;
-        nstg = 0;
-        prio.update(seq0);
-    };
-
-    // Bitmap word of the current candidate, mirrored in scalar registers for
-    // the admission loop of one step (nothing else writes the bitmap there).
-    int cw = -1;
-    uint64_t cbits = 0ull;
-    auto load_word = [&](int w) {
-        const uint64_t v = B[w];
-        const uint32_t lo = (uint32_t)uni((int)(uint32_t)v);
-        const uint32_t hi = (uint32_t)uni((int)(uint32_t)(v >> 32));
-        cbits = ((uint64_t)hi << 32) | lo;
-        cw = w;
-    };
 
     for (;;) {
         // every request finished by step t-1 (an empty instance is done at t = 0)
-        if (seq0 + nstg == n) {
-            if (n == 0 || max_fin <= t - 1) { status = STATUS_DONE; break; }
+        if (seq0 + nstg == n && (n == 0 || max_fin <= t - 1)) { status = STATUS_DONE; break; }
+        if (t >= t_stop) {
+            if (t > P.max_steps) status = STATUS_EXHAUSTED;
+            break;
         }
-        if (t > P.max_steps) { status = STATUS_EXHAUSTED; break; }
-        if (t >= t_lim) break;
 
         // 1. arrivals up to t: a prefix of the window (arrivals are sorted;
         //    those of earlier steps were ranked below the blocked head, so
-        //    nothing could happen at their steps).  n_below counts those
-        //    ranked above the blocked head (the lowest waiting rank before
-        //    this step; none if nothing was waiting).
+        //    nothing could happen at their steps).  The best of those ranked
+        //    above the blocked head (the lowest waiting rank before this
+        //    step; anything if nothing was waiting) is the first candidate.
         const int old_head = head < 0 ? INT32_MAX : head;
-        int new_min = INT32_MAX, n_below = 0;
-        int4 nq = make_int4(0, 0, 0, 0);
+        int r = old_head;
+        int4 q = hq;
         for (;;) {
-            const bool arr = (wb + lane >= cursor) && (a_reg <= t);
-            const uint64_t m = ballot(arr);
+            const uint64_t m = ballot(a_reg <= t) & pend;
             if (m == 0ull) break;
-            if (arr) bitmap_set_atomic(B, S, rk_reg);
-            n_below += __popcll(ballot(arr && rk_reg < old_head));
-            int mn, src;
-            if ((m & (m - 1ull)) == 0ull) {  // a single arrival
-                src = __builtin_ctzll(m);
-                mn = __builtin_amdgcn_readlane(rk_reg, src);
-            } else {
-                mn = wmin(arr ? rk_reg : INT32_MAX);
-                src = __builtin_ctzll(ballot(arr && rk_reg == mn));
+            pend &= ~m;
+            bits.set(m, rk_reg);
+            uint64_t up = ballot(rk_reg < r) & m;
+            if (up != 0ull) {
+                int src = __builtin_ctzll(up);
+                if ((up & (up - 1ull)) != 0ull) {
+                    const bool in = (up >> lane) & 1ull;
+                    const int mn = wmin(in ? rk_reg : INT32_MAX);
+                    src = __builtin_ctzll(ballot(rk_reg == mn) & up);
+                }
+                r = __builtin_amdgcn_readlane(rk_reg, src);
+                q = readlane4(aq, src);
             }
-            if (mn < new_min) {
-                new_min = mn;
-                nq = readlane4(aq, src);
-            }
-            cursor += __popcll(m);
-            if (cursor < wb + 64) break;
-            load_arrivals(cursor);
+            if (pend != 0ull) break;
+            load_arrivals(wb + 64);
         }
-        lds_order();
 
         // 4. admissions (known lengths: completions change nothing ahead)
-        if (new_min < old_head || (head >= 0 && t >= t_f)) {
-            int r = head;
-            int4 q = hq;
-            if (new_min < old_head) { r = new_min; q = nq; }
-            load_word(r >> 6);  // arrivals may have changed any word
+        if (r < old_head || (head >= 0 && t >= t_f)) {
             prof.begin(t);
+            bits.open(r);
             for (;;) {
                 int tf = 0;
                 if (!prof.fit(t, q.y, q.z, M, max_fin, &tf)) { head = r; hq = q; t_f = tf; break; }
-                if (lane == nstg) {
-                    stg_idx = q.x;
-                    stg_t = t;
+                stg_idx = setlane(stg_idx, q.x, nstg);
+                stg_t = setlane(stg_t, t, nstg);
+                bits.clear(r);
+                max_fin = max(max_fin, t + q.z);
+                if (++nstg == 64) {
+                    sg.start[stg_idx] = stg_t;
+                    sg.admit_seq[stg_idx] = seq0 + lane;
+                    seq0 += 64;
+                    nstg = 0;
+                    prio.update(seq0);
                 }
-                if (++nstg == 64) flush();
-                cbits &= ~(1ull << (r & 63));
-                // every lane stores the same word (no lane mask to set up)
-                B[cw] = cbits;
-                if (cbits == 0ull) S[cw >> 6] &= ~(1ull << (cw & 63));
-                lds_order();
-                max_fin = max(max_fin, t + q.w);
+                r = bits.next();
+                if (r < 0) { head = -1; break; }
                 // Once every arrival ranked above the old head is running, the
-                // old head is next, or nothing is left waiting.
-                // Before t_f it still does not fit: the profile has only grown
-                // since t_f was computed, which can only delay the release.
-                // (Candidates come in rank order, so the first n_below of them
-                // are exactly those arrivals.)
-                // (n_below <= 0 stays below zero)
-                if (--n_below == 0) {
-                    if (old_head == INT32_MAX) { head = -1; break; }
-                    if (t < t_f) break;
-                    // the old head is now the lowest waiting rank: found below
-                }
-                if (cbits != 0ull) {
-                    r = cw * 64 + __builtin_ctzll(cbits);
-                } else {
-                    r = bitmap_first(B, S, W1);
-                    if (r < 0) { head = -1; break; }
-                    load_word(r >> 6);
-                }
+                // old head is next.  Before t_f it still does not fit: the
+                // profile has only grown since t_f was computed, which can
+                // only delay the release.
+                if (r == old_head && t < t_f) break;
                 q = rec_of(r);
             }
+            bits.close();
+            // a full list: the candidate is the head, checked again at t when
+            // the segment resumes
+            if (t_f < 0) break;
         }
-
-        // a full list: the candidate is the head, checked again at t when the
-        // segment resumes
-        if (t_f < 0) break;
 
         // 5. advance to the next step where anything can happen: with a
         //    blocked head, its release or the next arrival ranked above it
         //    (past the window: the window's end)
         int nt;
         if (head >= 0) {
-            const uint64_t up = ballot((wb + lane >= cursor) && rk_reg < head);
+            const uint64_t up = ballot(rk_reg < head) & pend;
             const int next_up = up != 0ull ? __builtin_amdgcn_readlane(a_reg, __builtin_ctzll(up))
                                            : (wb + 64 < n ? uni(sg.a[wb + 64]) : INT32_MAX);
             nt = min(t_f, next_up);
-        } else if (cursor < n) {
-            nt = cursor < wb + 64 ? __builtin_amdgcn_readlane(a_reg, cursor - wb) : uni(sg.a[cursor]);
         } else {
-            nt = max_fin + 1;
+            nt = __builtin_amdgcn_readlane(a_reg, __builtin_ctzll(pend));
+            if (nt == INT32_MAX) nt = max_fin + 1;
         }
-        nt = max(nt, t + 1);
-        nt = min(nt, t_lim);
-        nt = min(nt, P.max_steps + 1);
-        if (nt <= t) nt = t + 1;
-        t = uni(nt);
+        t = max(min(nt, t_stop), t + 1);
     }
-    flush();
+    if (lane < nstg) {
+        sg.start[stg_idx] = stg_t;
+        sg.admit_seq[stg_idx] = seq0 + lane;
+    }
+    seq0 += nstg;
     prio.leave();
     // the peak over the steps up to t
     const int pk = prof.end(t);
-    st.t = t; st.cursor = cursor; st.seq = seq0; st.nfin = seq0; st.max_fin = max_fin;
+    st.t = t;
+    st.cursor = min(wb + (pend != 0ull ? __builtin_ctzll(pend) : 64), n);
+    st.seq = seq0; st.nfin = seq0; st.max_fin = max_fin;
     st.head_rank = head; st.t_f = t_f; st.status = status;
+    st.peak = max(st.peak, (int64_t)pk);
+}
+
+// run_known with the finish-ordered list: the loop is svf_event_loop.h.  The
+// rank bitmap is in registers (word w in lane w & 63 of pair w >> 6) for up to
+// 4096 NB requests, for NB = 0 in LDS at B, its upper level behind its W0 words.
+template <int NB>
+__device__ __forceinline__ void run_list(const SimArgs& P, const Seg& sg, uint64_t* Bg, uint64_t* B,
+                                         int W0, int W1, ListProf& L, SegState& st, int t_lim) {
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    const int lane = lane_id();
+    const int n = sg.n;
+    int t = uni(st.t), seq = uni(st.seq), nstg = 0, stg_idx = 0, stg_t = 0;
+    int max_fin = uni(st.max_fin), head = uni(st.head_rank), t_f = uni(st.t_f);
+    const int t_stop = min(t_lim, P.max_steps + 1);
+    int4 hq = make_int4(0, 0, 0, 0);  // record of the blocked head
+    if (head >= 0) {
+        hq = record(sg.rec, head);
+    } else {
+        head = t_f = INT32_MAX;  // nothing waits
+    }
+    IssuePrio prio;
+    prio.init(P, n, seq);
+
+    int lo0 = 0, hi0 = 0, lo1 = 0, hi1 = 0;
+    if (NB > 0) {
+        const uint64_t v = lane < W0 ? Bg[lane] : 0ull;
+        lo0 = (int)(uint32_t)v;
+        hi0 = (int)(uint32_t)(v >> 32);
+    }
+    if (NB > 1) {
+        const uint64_t v = 64 + lane < W0 ? Bg[64 + lane] : 0ull;
+        lo1 = (int)(uint32_t)v;
+        hi1 = (int)(uint32_t)(v >> 32);
+    }
+    if (NB == 0) {
+        for (int x = lane; x < W0 + W1; x += 64) B[x] = Bg[x];
+        lds_order();
+    }
+    int status = STATUS_RUNNING;
+    if (n == 0) {
+        status = STATUS_DONE;  // at its first step
+    } else {
+        const uint32_t stk = (uint32_t)(uintptr_t)(lds_ptr)L.stk;
+        int wb = uni(st.cursor), ln1 = L.ln + 1;
+        uint64_t pend = ~0ull;
+        if (NB == 1) {
+            asm volatile(EV_LOOP_1 : EV_STATE, [b0l] "+&v"(lo0), [b0h] "+&v"(hi0) : EV_INPUT : EV_CLOBBER);
+        } else if (NB == 2) {
+            asm volatile(EV_LOOP_2
+                         : EV_STATE, [b0l] "+&v"(lo0), [b0h] "+&v"(hi0), [b1l] "+&v"(lo1), [b1h] "+&v"(hi1)
+                         : EV_INPUT : EV_CLOBBER);
+        } else {
+            const uint32_t bb = (uint32_t)(uintptr_t)(lds_ptr)B;
+            asm volatile(EV_LOOP_0 : EV_STATE
+                         : EV_INPUT, [bb] "s"(bb), [sb] "s"(bb + 8 * W0), [w1] "s"(W1) : EV_CLOBBER);
+        }
+        L.ln = ln1 - 1;
+        st.cursor = min(wb + __builtin_ctzll(pend), n);
+        if (lane < nstg) {
+            sg.start[stg_idx] = stg_t;
+            sg.admit_seq[stg_idx] = seq + lane;
+        }
+        seq += nstg;
+        if (seq == n && max_fin <= t - 1) status = STATUS_DONE;
+        else if (t > P.max_steps && t_f >= 0) status = STATUS_EXHAUSTED;
+    }
+    if (NB > 0 && lane < W0) Bg[lane] = ((uint64_t)(uint32_t)hi0 << 32) | (uint32_t)lo0;
+    if (NB > 1 && 64 + lane < W0) Bg[64 + lane] = ((uint64_t)(uint32_t)hi1 << 32) | (uint32_t)lo1;
+    if (NB == 0) {
+        lds_order();
+        for (int x = lane; x < W0 + W1; x += 64) Bg[x] = B[x];
+    }
+    prio.leave();
+    // the peak over the steps up to t
+    const int pk = L.end(t);
+    st.t = t; st.seq = seq; st.nfin = seq; st.max_fin = max_fin;
+    st.head_rank = head == INT32_MAX ? -1 : head;
+    st.t_f = head == INT32_MAX ? 0 : t_f;
+    st.status = status;
     st.peak = max(st.peak, (int64_t)pk);
 }
 
@@ -1877,24 +1914,8 @@ __device__ void stepped_resume_tail(const SimArgs& P, const Seg& sg, uint64_t* B
     st.max_fin = maxF;
 }
 
-// One wave64 per segment; launched once for segments that plan with the
-// true lengths (event-driven) and once for the others (per step), so each
-// kernel carries only its own path.  LIST: the event path keeps its profile
-// as the finish-ordered list (LDS after the bitmap, kept in global memory
-// between launches) instead of the ring.
-template <bool D_LDS, bool STEPPED, bool LIST, bool RESUME = false, bool STOP = false>
-__device__ __forceinline__ void sim_segment(const SimArgs& P) {
-    extern __shared__ uint64_t smem[];
-    const int g = blockIdx.x;
-    if ((P.stepped[g] != 0) != STEPPED) return;
-    const int lane = lane_id();
-    const int pol = g / P.I, inst = g - pol * P.I;
-    const int64_t off = P.offsets[inst];
-    const int n = (int)(P.offsets[inst + 1] - off);
-    SegState st = P.st[g];
-    if (st.status != STATUS_RUNNING) return;
-    if (LIST && P.list_resume && st.resume_lim == 0) return;
-
+// The pointers of segment g = (policy pol, instance inst).
+__device__ __forceinline__ Seg segment(const SimArgs& P, int pol, int64_t off, int n) {
     Seg sg;
     sg.n = n;
     const int64_t base = (int64_t)pol * P.N + off;
@@ -1908,6 +1929,75 @@ __device__ __forceinline__ void sim_segment(const SimArgs& P) {
     sg.act = P.act ? P.act + base : nullptr;
     sg.actkr = P.actkr ? P.actkr + base : nullptr;
     sg.evl = P.evl ? P.evl + base : nullptr;
+    return sg;
+}
+
+// The event path with the finish-ordered list, one wave64 per segment: the
+// bitmap in registers (NB > 0) or at the start of the LDS, then the list's
+// stack.  List and bitmap are kept in global memory between launches.
+template <int NB>
+__device__ __forceinline__ void known_list_segment(const SimArgs& P) {
+    extern __shared__ uint64_t smem[];
+    const int g = blockIdx.x;
+    if (P.stepped[g] != 0) return;
+    const int lane = lane_id();
+    const int pol = g / P.I, inst = g - pol * P.I;
+    const int64_t off = P.offsets[inst];
+    const int n = (int)(P.offsets[inst + 1] - off);
+    SegState st = P.st[g];
+    if (st.status != STATUS_RUNNING) return;
+    if (P.list_resume && st.resume_lim == 0) return;
+    int t_lim = (int)min((int64_t)st.t + P.step_delta, (int64_t)P.max_steps + 2);
+    if (P.list_resume) t_lim = st.resume_lim;
+    if (st.ln > P.list_cap) {
+        // more running than this launch has room for: left to the continuation
+        st.resume_lim = t_lim;
+        if (lane == 0) P.st[g] = st;
+        return;
+    }
+    st.resume_lim = 0;
+    // a stop on a full list left t_f = -1: the head is checked again at t
+    if (st.t_f < 0) st.t_f = st.t;
+
+    const Seg sg = segment(P, pol, off, n);
+    const int W0 = (n + 63) >> 6;
+    const int W1 = (W0 + 63) >> 6;
+    uint64_t* Bg = P.bitmap + (int64_t)pol * P.bw_total + P.bw_off[inst];
+    int32_t* Fg = P.lst_f + (int64_t)g * P.list_stride;
+    uint32_t* Gg = P.lst_q + (int64_t)g * P.list_stride;
+    ListProf L;
+    L.cap = P.list_cap;
+    L.stk = reinterpret_cast<int2*>(smem + (NB == 0 ? P.bw_max : 0)) + 64;
+    L.dead = 0;
+    L.tprev = uni(st.t);
+    L.peak_lane = 0;
+    L.load(Fg, Gg, uni(st.ln));
+    run_list<NB>(P, sg, Bg, smem, W0, W1, L, st, t_lim);
+    L.store(Fg, Gg);
+    st.ln = L.ln;
+    if (st.t_f < 0) st.resume_lim = t_lim;  // stopped on a full list
+    if (lane == 0) P.st[g] = st;
+}
+
+// One wave64 per segment; launched once for segments that plan with the
+// true lengths (event-driven) and once for the others (per step), so each
+// kernel carries only its own path.  LIST: the per-step path keeps its
+// profile as the finish-ordered list (LDS after the bitmap, kept in global
+// memory between launches) instead of the ring.
+template <bool D_LDS, bool STEPPED, bool LIST, bool RESUME = false, bool STOP = false>
+__device__ __forceinline__ void sim_segment(const SimArgs& P) {
+    extern __shared__ uint64_t smem[];
+    const int g = blockIdx.x;
+    if ((P.stepped[g] != 0) != STEPPED) return;
+    const int lane = lane_id();
+    const int pol = g / P.I, inst = g - pol * P.I;
+    const int64_t off = P.offsets[inst];
+    const int n = (int)(P.offsets[inst + 1] - off);
+    SegState st = P.st[g];
+    if (st.status != STATUS_RUNNING) return;
+    if (LIST && P.list_resume && st.resume_lim == 0) return;
+
+    const Seg sg = segment(P, pol, off, n);
 
     // rank bitmap (two levels) staged in LDS for the launch
     const int W0 = (n + 63) >> 6;
@@ -1964,41 +2054,6 @@ __device__ __forceinline__ void sim_segment(const SimArgs& P) {
             st.lq = L.tot;
             if (st.resume_nev >= 0) st.resume_lim = t_lim;  // stopped inside step st.t
         }
-    } else if (LIST) {
-        const int cap = P.list_cap;
-        int32_t* Fg = P.lst_f + (int64_t)g * P.list_stride;
-        uint32_t* Qg = P.lst_q + (int64_t)g * P.list_stride;
-        ListProf L;
-        L.cap = cap;
-        L.F = reinterpret_cast<int32_t*>(smem + P.bw_max);
-        L.Q = reinterpret_cast<uint32_t*>(L.F + list_slots(cap));
-        L.ln = uni(st.ln);
-        L.tot = (uint32_t)uni((int)st.lq);
-        L.peak_lane = 0;
-        if (P.list_resume) t_lim = st.resume_lim;
-        st.resume_lim = 0;
-        if (L.ln > cap) {
-            // more running than this launch has room for: left to the continuation
-            st.resume_lim = t_lim;
-        } else {
-            for (int x = lane; x < L.ln; x += 64) {
-                L.F[x] = Fg[x];
-                L.Q[x] = Qg[x];
-            }
-            if (L.ln == 0 && lane == 0) L.F[0] = INT32_MAX;  // the empty list's sentinel
-            // a stop on a full list left t_f = -1: the head is checked again at t
-            if (st.t_f < 0) st.t_f = st.t;
-            __syncthreads();
-            run_known(P, sg, B, S, W1, L, st, t_lim);
-            __syncthreads();
-            for (int x = lane; x < L.ln; x += 64) {
-                Fg[x] = L.F[x];
-                Qg[x] = L.Q[x];
-            }
-            st.ln = L.ln;
-            st.lq = L.tot;
-            if (st.t_f < 0) st.resume_lim = t_lim;  // stopped on a full list
-        }
     } else {
         const int RS = P.H + 64;  // ring stride: H slots and the spare slot, padded
         int32_t* Dg = P.ring + (int64_t)g * RS;
@@ -2019,7 +2074,14 @@ __device__ __forceinline__ void sim_segment(const SimArgs& P) {
             run_stepped<false>(P, sg, B, S, W1, R, A, st, t_lim);
         } else {
             RingProf<D_LDS> R(D, uni(st.t));
-            run_known(P, sg, B, S, W1, R, st, t_lim);
+            LdsBits bits;
+            bits.B = B;
+            bits.S = S;
+            bits.W0 = W0;
+            bits.W1 = W1;
+            bits.cw = 0;
+            bits.cbits = 0ull;
+            run_known(P, sg, bits, R, st, t_lim);
         }
         __syncthreads();
         if (D_LDS) {
@@ -2035,12 +2097,14 @@ __global__ __launch_bounds__(64) void k_sim(SimArgs P) {
     sim_segment<D_LDS, STEPPED, false>(P);
 }
 
-// The list kernel needs few vector registers; its scalar state is squeezed
-// (spilled to vector lanes) so that eight waves fit on each SIMD, which the
-// short LDS footprint of the list allows.
+// The list kernel needs few registers: eight waves fit on each SIMD, which
+// the short LDS footprint of the list allows.  RESUME: the continuation of
+// segments whose list outgrew the first launch's LDS (a kernel of its own, so
+// that timings keep the two apart).
+template <int NB, bool RESUME>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void k_sim_list(SimArgs P) {
-    sim_segment<false, false, true>(P);
+    known_list_segment<NB>(P);
 }
 
 // The per-step path with the finish-ordered list: with room for the bound,
@@ -2053,13 +2117,6 @@ __global__ __launch_bounds__(64) void k_sim_steplist_stop(SimArgs P) {
 }
 __global__ __launch_bounds__(64) void k_sim_steplist_resume(SimArgs P) {
     sim_segment<false, true, true, true>(P);
-}
-
-// The same for the continuation of segments whose list outgrew the first
-// launch's LDS (a kernel of its own, so that timings keep the two apart).
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8)))
-void k_sim_list_resume(SimArgs P) {
-    sim_segment<false, false, true>(P);
 }
 
 // ------------------------------------------------------------ finalize
@@ -2250,6 +2307,15 @@ hipError_t launch_sort_rec(const SortArgs& A, int G, int max_n, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
+typedef void (*SimKernel)(SimArgs);
+
+// the event path's list kernel: bitmap pairs in registers (0: in LDS)
+static SimKernel list_kernel(int nb, bool resume) {
+    if (nb == 1) return resume ? &k_sim_list<1, true> : &k_sim_list<1, false>;
+    if (nb == 2) return resume ? &k_sim_list<2, true> : &k_sim_list<2, false>;
+    return resume ? &k_sim_list<0, true> : &k_sim_list<0, false>;
+}
+
 hipError_t launch_sim(const SimArgs& P, int G, bool d_lds, bool stepped, bool list,
                       size_t lds_bytes, hipStream_t s) {
     if (G <= 0) return hipSuccess;
@@ -2258,8 +2324,8 @@ hipError_t launch_sim(const SimArgs& P, int G, bool d_lds, bool stepped, bool li
         else if (P.list_cap < P.list_stride) hipLaunchKernelGGL(k_sim_steplist_stop, dim3(G), dim3(64), lds_bytes, s, P);
         else hipLaunchKernelGGL(k_sim_steplist, dim3(G), dim3(64), lds_bytes, s, P);
     } else if (!stepped && list) {
-        if (P.list_resume) hipLaunchKernelGGL(k_sim_list_resume, dim3(G), dim3(64), lds_bytes, s, P);
-        else hipLaunchKernelGGL(k_sim_list, dim3(G), dim3(64), lds_bytes, s, P);
+        hipLaunchKernelGGL(list_kernel(P.list_nb, P.list_resume != 0), dim3(G), dim3(64),
+                           lds_bytes, s, P);
     } else if (d_lds) {
         if (stepped) hipLaunchKernelGGL((k_sim<true, true>), dim3(G), dim3(64), lds_bytes, s, P);
         else hipLaunchKernelGGL((k_sim<true, false>), dim3(G), dim3(64), lds_bytes, s, P);
@@ -2275,7 +2341,7 @@ static hipError_t sim_attr(const void* f, size_t lds_bytes) {
     return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
 }
 
-hipError_t prepare_sim(bool d_lds, size_t lds_ring, bool list, size_t lds_list) {
+hipError_t prepare_sim(bool d_lds, size_t lds_ring, bool step_list, size_t lds_step) {
     hipError_t e;
     if (d_lds) {
         e = sim_attr((const void*)k_sim<true, true>, lds_ring);
@@ -2284,26 +2350,28 @@ hipError_t prepare_sim(bool d_lds, size_t lds_ring, bool list, size_t lds_list) 
         e = sim_attr((const void*)k_sim<false, true>, lds_ring);
         if (e == hipSuccess) e = sim_attr((const void*)k_sim<false, false>, lds_ring);
     }
-    if (e == hipSuccess && list) e = sim_attr((const void*)k_sim_list, lds_list);
-    if (e == hipSuccess && list) e = sim_attr((const void*)k_sim_steplist, lds_list);
-    if (e == hipSuccess && list) e = sim_attr((const void*)k_sim_steplist_resume, lds_list);
-    if (e == hipSuccess && list) e = sim_attr((const void*)k_sim_steplist_stop, lds_list);
-    if (e == hipSuccess && list) e = sim_attr((const void*)k_sim_list_resume, lds_list);
+    if (e == hipSuccess && step_list) e = sim_attr((const void*)k_sim_steplist, lds_step);
+    if (e == hipSuccess && step_list) e = sim_attr((const void*)k_sim_steplist_resume, lds_step);
+    if (e == hipSuccess && step_list) e = sim_attr((const void*)k_sim_steplist_stop, lds_step);
     return e;
 }
 
-hipError_t sim_known_occupancy(bool list, bool d_lds, size_t lds_bytes, int* blocks) {
-    const void* f = list ? (const void*)k_sim_list
-                         : (d_lds ? (const void*)k_sim<true, false>
-                                  : (const void*)k_sim<false, false>);
-    hipError_t e = sim_attr(f, lds_bytes);
-    if (e != hipSuccess) return e;
+hipError_t prepare_list(int nb, size_t lds_first, size_t lds_full) {
+    hipError_t r = sim_attr((const void*)list_kernel(nb, false), lds_first);
+    if (r == hipSuccess) r = sim_attr((const void*)list_kernel(nb, true), lds_full);
+    return r;
+}
+
+hipError_t list_occupancy(int nb, size_t lds_bytes, int* blocks) {
+    const void* f = (const void*)list_kernel(nb, false);
+    hipError_t r = sim_attr(f, lds_bytes);
+    if (r != hipSuccess) return r;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, 64, lds_bytes);
 }
 
 hipError_t sim_occupancy(bool stepped, bool list, bool d_lds, size_t lds_bytes, int* blocks) {
     const void* f;
-    if (list) f = stepped ? (const void*)k_sim_steplist : (const void*)k_sim_list;
+    if (list) f = (const void*)k_sim_steplist;
     else if (stepped) f = d_lds ? (const void*)k_sim<true, true> : (const void*)k_sim<false, true>;
     else f = d_lds ? (const void*)k_sim<true, false> : (const void*)k_sim<false, false>;
     hipError_t e = sim_attr(f, lds_bytes);

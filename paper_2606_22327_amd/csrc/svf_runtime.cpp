@@ -69,7 +69,9 @@ struct svf_batch {
     bool list_known = false;  // event path: profile as the finish-ordered list
     bool ring_used = true;    // some segment keeps its profile in the ring
     int32_t list_stride = 0;  // list entries per segment in HBM (the bound)
-    int32_t list_cap = 0;     // list entries per segment in LDS (first launch)
+    int32_t list_cap = 0;     // event path: list entries per segment (first launch)
+    int32_t list_full = 0;    //   and with room for the bound (continuation)
+    int32_t list_nb = 0;      // event path: bitmap pairs in registers (0: in LDS)
     size_t lds_list = 0;      // LDS of the event kernel with the list
     size_t lds_list_full = 0; //   and with room for the bound (continuation)
     bool list_stepped = false; // per-step path: profile as the finish-ordered list
@@ -112,7 +114,7 @@ struct svf_batch {
     StatsOut* d_stats = nullptr;
     int32_t* d_lst_f = nullptr;
     uint32_t* d_lst_q = nullptr;
-    unsigned long long* d_prog = nullptr;  // [2] progress counters of the simulation launches
+    unsigned long long* d_prog = nullptr;  // [2 * PROG_WORDS] progress counters of the simulation launches
     const uint64_t* sorted_keys = nullptr;  // which key buffer holds the final order
 };
 
@@ -341,38 +343,44 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
     if (env && !strcmp(env, "lds") && ring_bytes + bm_bytes <= 160 * 1024) h->d_lds = true;
     h->lds_bytes = std::max<size_t>(8, bm_bytes + (h->d_lds ? ring_bytes : 0));
     // The event path keeps its profile as the finish-ordered list (8 bytes
-    // per running request) when the ring does not fit in LDS, or when few
-    // requests run at once: the list's checks and insertions touch the
-    // running requests that finish before the candidate, the ring's the
-    // candidate's whole planned length.  Measured: the list is faster at
-    // about 140-280 concurrent requests (4096 x 1000 and 16384 x 5000
-    // workloads), 4x slower at about 930 (64 x 200,000); the estimate is
-    // M / (mean s + mean o / 2) and the crossover is taken at 512.  The list
-    // in LDS gets the largest capacity that still lets as many waves reside
-    // as the list kernel's registers allow; segments that outgrow it stop,
-    // and a second launch with room for the bound on concurrent requests
-    // continues them.
+    // per running request past the 64 in registers) when the ring does not fit
+    // in LDS, or when few requests run at once: the list's checks and
+    // insertions touch the running requests that finish before the candidate,
+    // the ring's the candidate's whole planned length.  Measured, list against
+    // ring: 1.7 against 4.2 ms at about 140 concurrent requests (3 x 4096 x
+    // 1000), 11.1 against 59 ms at about 170 (16384 x 5000), 412 against 162
+    // ms at about 930 (64 x 200,000); the estimate is M / (mean s + mean o /
+    // 2) and the crossover is taken at 512.  The list gets the largest
+    // capacity that still lets as many waves reside as the list kernel's
+    // registers allow; segments that outgrow it stop, and a second launch with
+    // room for the bound on concurrent requests (and for finished entries not
+    // yet removed) continues them.
     const int64_t bound = (h->n_known > 0 || h->any_stepped)
                               ? std::max<int64_t>(1, running_bound(v.s, off, I, d->M)) : 1;
     const size_t full_bytes = bm_bytes + (size_t)svfk::list_slots((int)std::min<int64_t>(bound, 1 << 24)) * 8;
     if (h->n_known > 0) {
         const char* pe = getenv("SVFSIM_PROFILE");
         bool use = false;
-        int64_t cap = bound;
-        if (full_bytes <= 160 * 1024) {
-            auto occ = [&](bool list, bool dl, size_t bytes) {
+        h->list_nb = svfk::list_bitmap_pairs(h->max_n);
+        const size_t lds_bm = h->list_nb == 0 ? bm_bytes : 0;
+        h->list_full = (int32_t)std::min<int64_t>(bound + svfk::LIST_DEAD_MAX, 1 << 24);
+        h->lds_list_full = lds_bm + svfk::list_lds(h->list_full);
+        int64_t cap = h->list_full;
+        const bool fits = h->lds_list_full <= 160 * 1024;
+        if (fits) {
+            auto occ = [&](int64_t c) {
                 int w = 0;
-                return svfk::sim_known_occupancy(list, dl, bytes, &w) == hipSuccess ? w : -1;
+                return svfk::list_occupancy(h->list_nb, lds_bm + svfk::list_lds(c), &w) == hipSuccess ? w : -1;
             };
-            const int w_top = occ(true, false, bm_bytes + (size_t)svfk::list_slots(64) * 8);
-            int64_t lo = std::min<int64_t>(bound, 64), hi = bound;  // occ(lo) >= w_top
+            const int w_top = occ(64);
+            int64_t lo = std::min<int64_t>(cap, 64), hi = cap;  // occ(lo) >= w_top
             while (lo < hi) {
                 const int64_t mid = lo + (hi - lo + 1) / 2;
-                if (occ(true, false, bm_bytes + (size_t)svfk::list_slots((int)mid) * 8) >= w_top) lo = mid;
+                if (occ(mid) >= w_top) lo = mid;
                 else hi = mid - 1;
             }
             cap = lo;
-            const char* pc = getenv("SVFSIM_LIST_LDS_CAP");  // testing: a smaller LDS list
+            const char* pc = getenv("SVFSIM_LIST_LDS_CAP");  // testing: a smaller list
             if (pc && atoll(pc) > 0) cap = std::min<int64_t>(cap, atoll(pc));
             double sum_s = 0.0, sum_o = 0.0;
             for (int64_t x = 0; x < N; ++x) {
@@ -383,12 +391,11 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
             if (w_top > 0) use = !h->d_lds || running <= 512.0;
         }
         if (pe && !strcmp(pe, "ring")) use = false;
-        if (pe && !strcmp(pe, "list")) use = full_bytes <= 160 * 1024;
+        if (pe && !strcmp(pe, "list")) use = fits;
         if (use) {
             h->list_known = true;
             h->list_cap = (int32_t)cap;
-            h->lds_list = bm_bytes + (size_t)svfk::list_slots((int)cap) * 8;
-            h->lds_list_full = full_bytes;
+            h->lds_list = lds_bm + svfk::list_lds(cap);
         }
     }
     // The per-step path keeps its planned profile as the finish-ordered list
@@ -426,17 +433,17 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
     h->ring_used = (h->n_known > 0 && !h->list_known) || (h->any_stepped && !h->list_stepped);
     // Resident workgroups of the first simulation launch of each path; the
     // waves set their issue priorities only when it is known (timing only).
-    // With at most one segment per CU there is nothing to arbitrate.
+    // With at most one segment per SIMD (four per CU) there is nothing to arbitrate.
     {
         int ncu = 0;
         const char* pp = getenv("SVFSIM_ISSUE_PRIO");  // "0": all waves at one priority
         const bool on = !(pp && !strcmp(pp, "0"));
         if (on && hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess &&
-            ncu > 0 && (int64_t)P * I > ncu) {
+            ncu > 0 && (int64_t)P * I > 4 * (int64_t)ncu) {
             int w = 0;
             if (h->n_known > 0 &&
-                svfk::sim_occupancy(false, h->list_known, h->d_lds,
-                                    h->list_known ? h->lds_list : h->lds_bytes, &w) == hipSuccess)
+                (h->list_known ? svfk::list_occupancy(h->list_nb, h->lds_list, &w)
+                               : svfk::sim_occupancy(false, false, h->d_lds, h->lds_bytes, &w)) == hipSuccess)
                 h->res_known = w * ncu;
             w = 0;
             if (h->any_stepped &&
@@ -556,10 +563,11 @@ int do_sim(svf_batch* h, int64_t delta) {
     S.lst_q = h->d_lst_q;
     S.list_stride = h->list_stride;
     S.list_cap = h->list_cap;
+    S.list_nb = h->list_nb;
     S.list_resume = 0;
     S.resident = h->res_known;
     S.prog = h->d_prog;
-    HIPCHK(svfk::launch_fill_u64(reinterpret_cast<uint64_t*>(h->d_prog), 2, 0ull, h->stream));
+    HIPCHK(svfk::launch_fill_u64(reinterpret_cast<uint64_t*>(h->d_prog), 2 * svfk::PROG_WORDS, 0ull, h->stream));
     hipEvent_t e0 = nullptr;
     record(h, 1, &e0);
     // The two paths simulate disjoint segments (each kernel leaves the other
@@ -584,7 +592,7 @@ int do_sim(svf_batch* h, int64_t delta) {
         T.list_cap = h->step_cap;
         T.list_resume = 0;
         T.resident = h->res_stepped;
-        T.prog = h->d_prog + 1;
+        T.prog = h->d_prog + svfk::PROG_WORDS;
         le = svfk::launch_sim(T, G, h->d_lds, true, h->list_stepped,
                               h->list_stepped ? h->lds_step : h->lds_bytes, st_stepped);
         if (le == hipSuccess && h->list_stepped && h->step_cap < h->list_stride) {
@@ -598,9 +606,9 @@ int do_sim(svf_batch* h, int64_t delta) {
     if (le == hipSuccess && h->n_known > 0) {
         le = svfk::launch_sim(S, G, h->d_lds, false, h->list_known,
                               h->list_known ? h->lds_list : h->lds_bytes, st_known);
-        if (le == hipSuccess && h->list_known && h->list_cap < h->list_stride) {
+        if (le == hipSuccess && h->list_known && h->list_cap < h->list_full) {
             // segments whose list outgrew the LDS capacity, up to the same step
-            S.list_cap = h->list_stride;
+            S.list_cap = h->list_full;
             S.list_resume = 1;
             S.resident = 0;
             le = svfk::launch_sim(S, G, false, false, true, h->lds_list_full, st_known);
@@ -772,7 +780,7 @@ int svf_create(const svf_batch_desc* d, void* hip_stream, svf_batch** out) {
         ALLOC(d_evl, PN);
     }
     ALLOC(d_st, G);
-    ALLOC(d_prog, 2);
+    ALLOC(d_prog, 2 * svfk::PROG_WORDS);
     ALLOC(d_fin_out, PN);
     ALLOC(d_stats, G);
 #undef ALLOC
@@ -804,8 +812,9 @@ int svf_create(const svf_batch_desc* d, void* hip_stream, svf_batch** out) {
     if (e == hipSuccess) e = svfk::launch_fill_i32(h->d_pre, PN, 0, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e == hipSuccess) {
-        hipError_t a = svfk::prepare_sim(h->d_lds, h->lds_bytes, h->list_known || h->list_stepped,
-                                         std::max(h->lds_list_full, h->lds_step_full));
+        hipError_t a = svfk::prepare_sim(h->d_lds, h->lds_bytes, h->list_stepped, h->lds_step_full);
+        if (a == hipSuccess && h->list_known)
+            a = svfk::prepare_list(h->list_nb, h->lds_list, h->lds_list_full);
         if (a != hipSuccess) e = a;
     }
     if (e == hipSuccess && h->fused_sort) {
@@ -989,7 +998,7 @@ int svf_run_noalloc(const svf_batch_desc* d, void* hip_stream, int32_t* start, i
         h.d_evl = c.take<int32_t>(PN);
     }
     h.d_st = c.take<SegState>(G);
-    h.d_prog = c.take<unsigned long long>(2);
+    h.d_prog = c.take<unsigned long long>(2 * svfk::PROG_WORDS);
     if (c.used > cap)
         return fail(SVF_EINVAL, "svf_run_noalloc: the batch needs %zu bytes of device scratch, "
                                 "more than the %zu this entry point has", c.used, cap);
@@ -1021,8 +1030,8 @@ int svf_run_noalloc(const svf_batch_desc* d, void* hip_stream, int32_t* start, i
     if (e == hipSuccess) e = hipStreamSynchronize(h.stream);
     if (e != hipSuccess)
         return fail(SVF_EHIP, "svf_run_noalloc: copying the inputs failed: %s", hipGetErrorString(e));
-    HIPCHK(svfk::prepare_sim(h.d_lds, h.lds_bytes, h.list_known || h.list_stepped,
-                             std::max(h.lds_list_full, h.lds_step_full)));
+    HIPCHK(svfk::prepare_sim(h.d_lds, h.lds_bytes, h.list_stepped, h.lds_step_full));
+    if (h.list_known) HIPCHK(svfk::prepare_list(h.list_nb, h.lds_list, h.lds_list_full));
     if (h.max_n > 0) HIPCHK(svfk::prepare_sort_rec(h.max_n));
     RETCHK(do_reset(&h));
     RETCHK(do_sim(&h, int64_t(1) << 40));
