@@ -46,8 +46,8 @@ def kernel_source_digest():
 
     csrc = os.path.join(ROOT, "paper_2606_22327_amd", "csrc")
     data = b"".join(open(os.path.join(csrc, f), "rb").read()
-                    for f in ("svf_kernels.hip", "svf_event_loop.h", "svf_kernels.h",
-                              "svf_runtime.cpp"))
+                    for f in ("svf_kernels.hip", "svf_event_loop.h", "svf_step_loop.h",
+                              "svf_kernels.h", "svf_runtime.cpp"))
     return hashlib.sha256(data + " ".join(B.GPU_FLAGS).encode()).hexdigest()[:16]
 
 

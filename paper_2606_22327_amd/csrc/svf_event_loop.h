@@ -93,21 +93,22 @@
     "s_nop 1\n\t"
 
 // ---- the rank bitmap: up to 4096 ranks in one register pair, up to 8192 in
-// two, else both levels in LDS.  SET: the arrivals eM1; OPEN: word eCw into
-// eCb; CLOSE: eCb back; FIND: an empty word was open: its level above, then
-// the lowest non-empty word into eCw, eCb (to ev_none if there is none)
+// two, else both levels in LDS.  SET: the ranks in the lanes eM1 of v[reg];
+// OPEN: word eCw into eCb; CLOSE: eCb back; EMPTY: the open word has no bit
+// left; SCAN: the lowest non-empty word into eCw, eCb (to ev_none if there is
+// none).  l: a suffix for the labels.
 
-#define EV_SET_LOOP(body)                                                     \
+#define EV_SET_LOOP(reg, l, body)                                             \
     "s_mov_b64 s[eX:eX+1], s[eM1:eM1+1]\n"                                    \
-    ".Lev_bit_%=:\n\t"                                                        \
+    ".Lev_bit" l "_%=:\n\t"                                                   \
     "s_ff1_i32_b64 s[eI], s[eX:eX+1]\n\t"                                     \
-    "v_readlane_b32 s[eU], v[vRk], s[eI]\n\t"                                 \
+    "v_readlane_b32 s[eU], v[" reg "], s[eI]\n\t"                             \
     "s_bitset0_b64 s[eX:eX+1], s[eI]\n\t"                                     \
     "s_lshr_b32 s[eW], s[eU], 6\n\t"                                          \
     "s_mov_b32 m0, s[eW]\n\t"                                                 \
     body                                                                      \
     "s_cmp_lg_u64 s[eX:eX+1], 0\n\t"                                          \
-    "s_cbranch_scc1 .Lev_bit_%=\n\t"
+    "s_cbranch_scc1 .Lev_bit" l "_%=\n\t"
 
 #define EV_SET_PAIR(lo, hi)                                                   \
     "v_readlane_b32 s[eMk], " lo ", s[eW]\n\t"                                \
@@ -124,24 +125,25 @@
     "v_writelane_b32 " lo ", s[eCb], m0\n\t"                                  \
     "v_writelane_b32 " hi ", s[eCb+1], m0\n\t"
 
-#define EV_SET_1 EV_SET_LOOP(EV_SET_PAIR("%[b0l]", "%[b0h]"))
-#define EV_OPEN_1 EV_GET_PAIR("%[b0l]", "%[b0h]")
-#define EV_CLOSE_1 "s_mov_b32 m0, s[eCw]\n\t" EV_PUT_PAIR("%[b0l]", "%[b0h]")
-#define EV_FIND_1                                                             \
-    EV_CLOSE_1                                                                \
+#define EV_SET_1(reg, l) EV_SET_LOOP(reg, l, EV_SET_PAIR("%[b0l]", "%[b0h]"))
+#define EV_OPEN_1(l) EV_GET_PAIR("%[b0l]", "%[b0h]")
+#define EV_CLOSE_1(l) "s_mov_b32 m0, s[eCw]\n\t" EV_PUT_PAIR("%[b0l]", "%[b0h]")
+#define EV_EMPTY_1 EV_CLOSE_1("")
+#define EV_SCAN_1(l)                                                          \
     "v_or_b32 v[vX], %[b0l], %[b0h]\n\t"                                      \
     "v_cmp_ne_u32 vcc, 0, v[vX]\n\t"                                          \
     "s_cbranch_vccz .Lev_none_%=\n\t"                                         \
-    "s_ff1_i32_b64 s[eCw], vcc\n\t" EV_OPEN_1
+    "s_ff1_i32_b64 s[eCw], vcc\n\t" EV_OPEN_1(l)
 
-#define EV_SET_2                                                              \
-    EV_SET_LOOP("s_cmp_lt_u32 s[eW], 64\n\t"                                  \
-                "s_cbranch_scc0 .Lev_bit1_%=\n\t"                             \
+#define EV_SET_2(reg, l)                                                      \
+    EV_SET_LOOP(reg, l,                                                       \
+                "s_cmp_lt_u32 s[eW], 64\n\t"                                  \
+                "s_cbranch_scc0 .Lev_bit1" l "_%=\n\t"                        \
                 EV_SET_PAIR("%[b0l]", "%[b0h]")                               \
-                "s_branch .Lev_bit2_%=\n"                                     \
-                ".Lev_bit1_%=:\n\t"                                           \
+                "s_branch .Lev_bit2" l "_%=\n"                                \
+                ".Lev_bit1" l "_%=:\n\t"                                      \
                 EV_SET_PAIR("%[b1l]", "%[b1h]")                               \
-                ".Lev_bit2_%=:\n\t")
+                ".Lev_bit2" l "_%=:\n\t")
 #define EV_OPEN_2(l)                                                          \
     "s_cmp_lt_u32 s[eCw], 64\n\t"                                             \
     "s_cbranch_scc0 .Lev_get" l "_%=\n\t"                                     \
@@ -159,54 +161,54 @@
     ".Lev_put" l "_%=:\n\t"                                                   \
     EV_PUT_PAIR("%[b1l]", "%[b1h]")                                           \
     ".Lev_pot" l "_%=:\n\t"
-#define EV_FIND_2                                                             \
-    EV_CLOSE_2("f")                                                           \
+#define EV_EMPTY_2 EV_CLOSE_2("f")
+#define EV_SCAN_2(l)                                                          \
     "v_or_b32 v[vX], %[b0l], %[b0h]\n\t"                                      \
     "v_cmp_ne_u32 vcc, 0, v[vX]\n\t"                                          \
-    "s_cbranch_vccz .Lev_find1_%=\n\t"                                        \
+    "s_cbranch_vccz .Lev_find1" l "_%=\n\t"                                   \
     "s_ff1_i32_b64 s[eCw], vcc\n\t"                                           \
     EV_GET_PAIR("%[b0l]", "%[b0h]")                                           \
-    "s_branch .Lev_found_%=\n"                                                \
-    ".Lev_find1_%=:\n\t"                                                      \
+    "s_branch .Lev_found" l "_%=\n"                                           \
+    ".Lev_find1" l "_%=:\n\t"                                                 \
     "v_or_b32 v[vX], %[b1l], %[b1h]\n\t"                                      \
     "v_cmp_ne_u32 vcc, 0, v[vX]\n\t"                                          \
     "s_cbranch_vccz .Lev_none_%=\n\t"                                         \
     "s_ff1_i32_b64 s[eCw], vcc\n\t"                                           \
     "s_add_i32 s[eCw], s[eCw], 64\n\t"                                        \
     EV_GET_PAIR("%[b1l]", "%[b1h]")                                           \
-    ".Lev_found_%=:\n\t"
+    ".Lev_found" l "_%=:\n\t"
 
-// LDS: word w at %[bb] + 8 w, its level above at %[sb] + 8 (w >> 6), %[w1]
-// words of it
-#define EV_SET_0                                                              \
+/* LDS: word w at %[bb] + 8 w, its level above at %[sb] + 8 (w >> 6), %[w1]
+   words of it */
+#define EV_SET_0(reg, l)                                                      \
     "s_mov_b64 exec, s[eM1:eM1+1]\n\t"                                        \
-    "v_lshrrev_b32 v[vAd], 6, v[vRk]\n\t"                                     \
-    "v_lshlrev_b64 v[vX:vX+1], v[vRk], 1\n\t"                                 \
+    "v_lshrrev_b32 v[vAd], 6, v[" reg "]\n\t"                                 \
+    "v_lshlrev_b64 v[vX:vX+1], v[" reg "], 1\n\t"                             \
     "v_lshlrev_b64 v[vZ:vZ+1], v[vAd], 1\n\t"                                 \
     "v_lshlrev_b32 v[vAd], 3, v[vAd]\n\t"                                     \
     "v_add_u32 v[vAd], %[bb], v[vAd]\n\t"                                     \
     "ds_or_b64 v[vAd], v[vX:vX+1]\n\t"                                        \
-    "v_lshrrev_b32 v[vAd], 12, v[vRk]\n\t"                                    \
+    "v_lshrrev_b32 v[vAd], 12, v[" reg "]\n\t"                                \
     "v_lshlrev_b32 v[vAd], 3, v[vAd]\n\t"                                     \
     "v_add_u32 v[vAd], %[sb], v[vAd]\n\t"                                     \
     "ds_or_b64 v[vAd], v[vZ:vZ+1]\n\t"                                        \
     "s_mov_b64 exec, -1\n\t"
-#define EV_OPEN_0                                                             \
+#define EV_OPEN_0(l)                                                          \
     "s_lshl3_add_u32 s[eU], s[eCw], %[bb]\n\t"                                \
     "v_mov_b32 v[vAd], s[eU]\n\t"                                             \
     "ds_read_b64 v[vX:vX+1], v[vAd]\n\t"                                      \
     "s_waitcnt lgkmcnt(0)\n\t"                                                \
     "v_readfirstlane_b32 s[eCb], v[vX]\n\t"                                   \
     "v_readfirstlane_b32 s[eCb+1], v[vY]\n\t"
-// (every lane stores the same word)
-#define EV_CLOSE_0                                                            \
+/* (every lane stores the same word) */
+#define EV_CLOSE_0(l)                                                         \
     "s_lshl3_add_u32 s[eU], s[eCw], %[bb]\n\t"                                \
     "v_mov_b32 v[vAd], s[eU]\n\t"                                             \
     "v_mov_b32 v[vX], s[eCb]\n\t"                                             \
     "v_mov_b32 v[vY], s[eCb+1]\n\t"                                           \
     "ds_write_b64 v[vAd], v[vX:vX+1]\n\t"
-#define EV_FIND_0                                                             \
-    EV_CLOSE_0                                                                \
+#define EV_EMPTY_0                                                            \
+    EV_CLOSE_0("")                                                            \
     "s_lshr_b32 s[eU], s[eCw], 6\n\t"                                         \
     "s_lshl3_add_u32 s[eU], s[eU], %[sb]\n\t"                                 \
     "v_mov_b32 v[vAd], s[eU]\n\t"                                             \
@@ -217,9 +219,10 @@
     "s_bitset0_b64 s[eCb:eCb+1], s[eCw]\n\t"                                  \
     "v_mov_b32 v[vX], s[eCb]\n\t"                                             \
     "v_mov_b32 v[vY], s[eCb+1]\n\t"                                           \
-    "ds_write_b64 v[vAd], v[vX:vX+1]\n\t"                                     \
+    "ds_write_b64 v[vAd], v[vX:vX+1]\n\t"
+#define EV_SCAN_0(l)                                                          \
     "s_mov_b32 s[eW], 0\n"                                                    \
-    ".Lev_find_%=:\n\t"                                                       \
+    ".Lev_find" l "_%=:\n\t"                                                  \
     "s_lshl3_add_u32 s[eU], s[eW], %[sb]\n\t"                                 \
     "v_lshlrev_b32 v[vAd], 3, %[lane]\n\t"                                    \
     "v_add_u32 v[vAd], s[eU], v[vAd]\n\t"                                     \
@@ -229,12 +232,12 @@
     "s_waitcnt lgkmcnt(0)\n\t"                                                \
     "v_cmp_ne_u64 vcc, 0, v[vX:vX+1]\n\t"                                     \
     "s_and_b64 vcc, vcc, s[eMk:eMk+1]\n\t"                                    \
-    "s_cbranch_scc1 .Lev_found_%=\n\t"                                        \
+    "s_cbranch_scc1 .Lev_found" l "_%=\n\t"                                   \
     "s_add_i32 s[eW], s[eW], 64\n\t"                                          \
     "s_cmp_lt_i32 s[eW], %[w1]\n\t"                                           \
-    "s_cbranch_scc1 .Lev_find_%=\n\t"                                         \
+    "s_cbranch_scc1 .Lev_find" l "_%=\n\t"                                    \
     "s_branch .Lev_none_%=\n"                                                 \
-    ".Lev_found_%=:\n\t"                                                      \
+    ".Lev_found" l "_%=:\n\t"                                                 \
     "s_ff1_i32_b64 s[eI], vcc\n\t"                                            \
     "v_readlane_b32 s[eX], v[vX], s[eI]\n\t"                                  \
     "v_readlane_b32 s[eX+1], v[vY], s[eI]\n\t"                                \
@@ -242,7 +245,7 @@
     "s_ff1_i32_b64 s[eCw], s[eX:eX+1]\n\t"                                    \
     "s_lshl_b32 s[eI], s[eI], 6\n\t"                                          \
     "s_add_i32 s[eCw], s[eCw], s[eI]\n\t"                                     \
-    EV_OPEN_0
+    EV_OPEN_0(l)
 
 // the next 64 requests: arrivals and ranks were loaded one window ahead
 #define EV_RELOAD                                                             \
@@ -262,89 +265,11 @@
     "global_load_dword v[vNa], v[vAd], %[arr]\n\t"                            \
     "global_load_dword v[vNr], v[vAd], %[rank]\n\t"
 
-// ---- the loop
-
-#define EV_LOOP(SET, OPEN, CLOSE, CLOSE_FULL, FIND)                           \
-    EV_NAMES                                                                  \
-    "v_mov_b32 v[vM0], m0\n\t"                                                \
-    /* the first window's arrivals and ranks; the progress counter */         \
-    "v_add_u32 v[vAd], %[wb], %[lane]\n\t"                                    \
-    "v_min_i32 v[vAd], %[n1], v[vAd]\n\t"                                     \
-    "v_lshlrev_b32 v[vAd], 2, v[vAd]\n\t"                                     \
-    "global_load_dword v[vNa], v[vAd], %[arr]\n\t"                            \
-    "global_load_dword v[vNr], v[vAd], %[rank]\n\t"                           \
-    "s_cmp_lg_u64 %[ctr], 0\n\t"                                              \
-    "s_cbranch_scc0 .Lev_noctr_%=\n\t"                                        \
-    "v_mov_b32 v[vZ], 0\n\t"                                                  \
-    "global_load_dwordx2 v[vPd:vPd+1], v[vZ], %[ctr]\n"                       \
-    ".Lev_noctr_%=:\n\t"                                                      \
-    "s_sub_i32 %[wb], %[wb], 64\n\t"                                          \
-    EV_RELOAD                                                                 \
-                                                                              \
-    /* visit */                                                               \
-    ".Lev_visit_%=:\n\t"                                                      \
-    "s_add_i32 s[eU], %[seq], %[nstg]\n\t"                                    \
-    "s_cmp_gt_i32 s[eU], %[n1]\n\t"                                           \
-    "s_cbranch_scc1 .Lev_alladm_%=\n"                                         \
-    ".Lev_visit1_%=:\n\t"                                                     \
-    "s_cmp_ge_i32 %[t], %[tstop]\n\t"                                         \
-    "s_cbranch_scc1 .Lev_exit_%=\n\t"                                         \
-    "s_mov_b32 s[eR], %[head]\n"                                              \
-                                                                              \
-    /* arrivals */                                                            \
-    ".Lev_arr_%=:\n\t"                                                        \
-    "v_cmp_ge_i32 vcc, %[t], v[vA]\n\t"                                       \
-    "s_and_b64 s[eM1:eM1+1], vcc, %[pend]\n\t"                                \
-    "s_cbranch_scc0 .Lev_noarr_%=\n\t"                                        \
-    "s_andn2_b64 %[pend], %[pend], s[eM1:eM1+1]\n\t"                          \
-    SET                                                                       \
-    "v_cmp_gt_i32 vcc, s[eR], v[vRk]\n\t"                                     \
-    "s_and_b64 s[eX:eX+1], vcc, s[eM1:eM1+1]\n\t"                             \
-    "s_cbranch_scc0 .Lev_arrdone_%=\n\t"                                      \
-    "s_ff1_i32_b64 s[eI], s[eX:eX+1]\n\t"                                     \
-    "s_bcnt1_i32_b64 s[eU], s[eX:eX+1]\n\t"                                   \
-    "s_cmp_eq_u32 s[eU], 1\n\t"                                               \
-    "s_cbranch_scc1 .Lev_one_%=\n\t"                                          \
-    "v_cndmask_b32 v[vX], %[vmax], v[vRk], s[eX:eX+1]\n\t"                    \
-    EV_REDUCE("v_min_i32_dpp", "vX")                                          \
-    "v_readlane_b32 s[eU], v[vX], 63\n\t"                                     \
-    "s_nop 1\n\t"                                                             \
-    "v_cmp_eq_u32 vcc, s[eU], v[vRk]\n\t"                                     \
-    "s_and_b64 s[eX:eX+1], vcc, s[eX:eX+1]\n\t"                               \
-    "s_ff1_i32_b64 s[eI], s[eX:eX+1]\n"                                       \
-    ".Lev_one_%=:\n\t"                                                        \
-    "s_waitcnt vmcnt(0)\n\t"                                                  \
-    "v_readlane_b32 s[eR], v[vRk], s[eI]\n\t"                                 \
-    "v_readlane_b32 s[eQ], v[vAq], s[eI]\n\t"                                 \
-    "v_readlane_b32 s[eQ+1], v[vAq+1], s[eI]\n\t"                             \
-    "v_readlane_b32 s[eQ+2], v[vAq+2], s[eI]\n"                               \
-    ".Lev_arrdone_%=:\n\t"                                                    \
-    "s_cmp_eq_u64 %[pend], 0\n\t"                                             \
-    "s_cbranch_scc1 .Lev_reload_%=\n"                                         \
-    ".Lev_noarr_%=:\n\t"                                                      \
-    "s_cmp_lt_i32 s[eR], %[head]\n\t"                                         \
-    "s_cbranch_scc1 .Lev_cand_%=\n\t"                                         \
-    "s_cmp_ge_i32 %[t], %[tf]\n\t"                                            \
-    "s_cbranch_scc0 .Lev_adv_%=\n\t"                                          \
-    "s_mov_b32 s[eQ], %[h0]\n\t"                                              \
-    "s_mov_b32 s[eQ+1], %[h1]\n\t"                                            \
-    "s_mov_b32 s[eQ+2], %[h2]\n"                                              \
-                                                                              \
-    /* begin */                                                               \
-    ".Lev_cand_%=:\n\t"                                                       \
-    "v_cmp_ge_i32 vcc, %[t], %[F]\n\t"                                        \
-    "s_bcnt1_i32_b64 s[eU], vcc\n\t"                                          \
-    "s_add_i32 s[eT1], %[t], 1\n\t"                                           \
-    "s_add_i32 s[eMt], %[t], %[M]\n\t"                                        \
-    "s_cmp_lg_u32 s[eU], %[dead]\n\t"                                         \
-    "s_cbranch_scc1 .Lev_begin_%=\n"                                          \
-    ".Lev_begun_%=:\n\t"                                                      \
-    "s_mov_b32 %[tprev], %[t]\n\t"                                            \
-    "s_lshr_b32 s[eCw], s[eR], 6\n\t"                                         \
-    OPEN                                                                      \
-                                                                              \
-    /* fit */                                                                 \
-    ".Lev_fit_%=:\n\t"                                                        \
+// The check of a candidate (size eQ+1, planned length eQ+2) started at t and,
+// when it fits, its place in the list: entries with t < F < te, their largest
+// G (vM) and number (eP); then, past EV_ADMITTED, the insertion.  A full
+// register group first pushes lane 63's entry.
+#define EV_FIT                                                                \
     "v_subrev_u32 v[vX], s[eT1], %[F]\n\t"                                    \
     "s_add_i32 s[eU], s[eQ+2], -1\n\t"                                        \
     "v_cmp_gt_u32 s[eIn:eIn+1], s[eU], v[vX]\n\t"                             \
@@ -388,49 +313,10 @@
     "v_writelane_b32 v[vX], s[eTe], m0\n\t"                                   \
     "v_writelane_b32 v[vY], s[eVe], m0\n\t"                                   \
     "v_cndmask_b32 %[F], %[F], v[vX], s[eMk:eMk+1]\n\t"                       \
-    "v_cndmask_b32 %[G], v[vM], v[vY], s[eMk:eMk+1]\n"                        \
-                                                                              \
-    /* admitted */                                                            \
-    ".Lev_adm_%=:\n\t"                                                        \
-    "s_add_i32 %[ln1], %[ln1], 1\n\t"                                         \
-    "s_mov_b32 m0, %[nstg]\n\t"                                               \
-    "v_writelane_b32 %[sgi], s[eQ], m0\n\t"                                   \
-    "v_writelane_b32 %[sgt], %[t], m0\n\t"                                    \
-    "s_max_i32 %[mf], %[mf], s[eTe]\n\t"                                      \
-    "s_bitset0_b64 s[eCb:eCb+1], s[eR]\n\t"                                   \
-    "s_add_i32 %[nstg], %[nstg], 1\n\t"                                       \
-    "s_cmp_eq_u32 %[nstg], 64\n\t"                                            \
-    "s_cbranch_scc1 .Lev_flush_%=\n"                                          \
-    ".Lev_next_%=:\n\t"                                                       \
-    "s_cmp_eq_u64 s[eCb:eCb+1], 0\n\t"                                        \
-    "s_cbranch_scc1 .Lev_word_%=\n"                                           \
-    ".Lev_pick_%=:\n\t"                                                       \
-    "s_ff1_i32_b64 s[eR], s[eCb:eCb+1]\n\t"                                   \
-    "s_lshl_b32 s[eU], s[eCw], 6\n\t"                                         \
-    "s_add_i32 s[eR], s[eR], s[eU]\n\t"                                       \
-    "s_cmp_eq_u32 s[eR], %[head]\n\t"                                         \
-    "s_cbranch_scc1 .Lev_oldhead_%=\n"                                        \
-    ".Lev_rec_%=:\n\t"                                                        \
-    "s_lshl_b32 s[eU], s[eR], 4\n\t"                                          \
-    "s_load_dwordx4 s[eQ:eQ+3], %[rec], s[eU]\n\t"                            \
-    "s_waitcnt lgkmcnt(0)\n\t"                                                \
-    "s_branch .Lev_fit_%=\n"                                                  \
-    /* the old head: before t_f it still does not fit (the profile has only   \
-       grown since t_f was computed) */                                       \
-    ".Lev_oldhead_%=:\n\t"                                                    \
-    "s_cmp_ge_i32 %[t], %[tf]\n\t"                                            \
-    "s_cbranch_scc1 .Lev_rec_%=\n\t"                                          \
-    "s_branch .Lev_close_%=\n"                                                \
-    ".Lev_word_%=:\n\t"                                                       \
-    FIND                                                                      \
-    "s_branch .Lev_pick_%=\n"                                                 \
-    ".Lev_none_%=:\n\t"                                                       \
-    "s_brev_b32 %[head], -2\n\t"                                              \
-    "s_brev_b32 %[tf], -2\n\t"                                                \
-    "s_branch .Lev_adv_%=\n"                                                  \
-                                                                              \
-    /* fail: t_f = max over the violating steps of min(tau, D + tau - X) */   \
-    ".Lev_fail_%=:\n\t"                                                       \
+    "v_cndmask_b32 %[G], v[vM], v[vY], s[eMk:eMk+1]\n"
+
+// It does not fit: t_f = max over the violating steps of min(tau, D + tau - X).
+#define EV_REL                                                                \
     "s_sub_i32 s[eU], %[M], s[eQ+1]\n\t"                                      \
     "v_subrev_u32 v[vX], s[eU], %[G]\n\t"                                     \
     "v_min_i32 v[vX], v[vX], %[F]\n\t"                                        \
@@ -440,63 +326,11 @@
     "v_readlane_b32 %[tf], v[vX], 63\n\t"                                     \
     "s_sub_i32 s[eV], s[eVe], s[eU]\n\t"                                      \
     "s_min_i32 s[eV], s[eV], s[eTe]\n\t"                                      \
-    "s_max_i32 %[tf], %[tf], s[eV]\n\t"                                       \
-    "s_mov_b32 %[head], s[eR]\n\t"                                            \
-    "s_mov_b32 %[h0], s[eQ]\n\t"                                              \
-    "s_mov_b32 %[h1], s[eQ+1]\n\t"                                            \
-    "s_mov_b32 %[h2], s[eQ+2]\n"                                              \
-    ".Lev_close_%=:\n\t"                                                      \
-    CLOSE                                                                     \
-                                                                              \
-    /* advance */                                                             \
-    ".Lev_adv_%=:\n\t"                                                        \
-    "v_cmp_gt_i32 vcc, %[head], v[vRk]\n\t"                                   \
-    "s_and_b64 s[eX:eX+1], vcc, %[pend]\n\t"                                  \
-    "s_cbranch_scc0 .Lev_advnone_%=\n\t"                                      \
-    "s_ff1_i32_b64 s[eI], s[eX:eX+1]\n\t"                                     \
-    "v_readlane_b32 s[eV], v[vA], s[eI]\n\t"                                  \
-    "s_min_i32 s[eV], s[eV], %[tf]\n"                                         \
-    ".Lev_advto_%=:\n\t"                                                      \
-    "s_add_i32 s[eU], %[t], 1\n\t"                                            \
-    "s_min_i32 s[eV], s[eV], %[tstop]\n\t"                                    \
-    "s_max_i32 %[t], s[eV], s[eU]\n\t"                                        \
-    "s_branch .Lev_visit_%=\n"                                                \
-    /* none in the window: its end, or (no more to come) the head's release   \
-       or the last finish */                                                  \
-    ".Lev_advnone_%=:\n\t"                                                    \
-    "s_add_i32 s[eU], %[wb], 63\n\t"                                          \
-    "s_mov_b32 s[eV], %[tf]\n\t"                                              \
-    "s_cmp_lt_i32 s[eU], %[n1]\n\t"                                           \
-    "s_cbranch_scc0 .Lev_advlast_%=\n\t"                                      \
-    "s_waitcnt vmcnt(0)\n\t"                                                  \
-    "v_readfirstlane_b32 s[eV], v[vNa]\n\t"                                   \
-    "s_min_i32 s[eV], s[eV], %[tf]\n\t"                                       \
-    "s_branch .Lev_advto_%=\n"                                                \
-    ".Lev_advlast_%=:\n\t"                                                    \
-    "s_add_i32 s[eU], %[mf], 1\n\t"                                           \
-    "s_cmp_eq_u32 %[head], 0x7fffffff\n\t"                                    \
-    "s_cselect_b32 s[eV], s[eU], s[eV]\n\t"                                   \
-    "s_branch .Lev_advto_%=\n"                                                \
-                                                                              \
-    ".Lev_reload_%=:\n\t"                                                     \
-    EV_RELOAD                                                                 \
-    "s_branch .Lev_arr_%=\n"                                                  \
-                                                                              \
-    /* begin: the memory at the finish steps of the newly finished entries,   \
-       tprev < F <= t; they stay in front until 32 have gathered */           \
-    ".Lev_begin_%=:\n\t"                                                      \
-    "s_add_i32 s[eV], %[tprev], 1\n\t"                                        \
-    "v_subrev_u32 v[vX], s[eV], %[F]\n\t"                                     \
-    "s_sub_i32 s[eV], %[t], %[tprev]\n\t"                                     \
-    "v_cmp_gt_u32 s[eMk:eMk+1], s[eV], v[vX]\n\t"                             \
-    "v_sub_u32 v[vY], %[G], %[F]\n\t"                                         \
-    "s_mov_b32 %[dead], s[eU]\n\t"                                            \
-    "s_nop 0\n\t"                                                             \
-    "v_cndmask_b32 v[vY], 0, v[vY], s[eMk:eMk+1]\n\t"                         \
-    "v_max_i32 %[peak], %[peak], v[vY]\n\t"                                   \
-    "s_cmp_lt_u32 s[eU], 32\n\t"                                              \
-    "s_cbranch_scc1 .Lev_begun_%=\n\t"                                        \
-    /* drop eU entries: lane i takes entry i + eU, from the stack past lane 63 */ \
+    "s_max_i32 %[tf], %[tf], s[eV]\n\t"
+
+// The first eU entries leave: lane i takes entry i + eU, from the stack past
+// lane 63.
+#define EV_DROP                                                               \
     "v_add_u32 v[vX], s[eU], %[lane]\n\t"                                     \
     "v_lshlrev_b32 v[vY], 2, v[vX]\n\t"                                       \
     "v_and_b32 v[vY], 0xfc, v[vY]\n\t"                                        \
@@ -516,15 +350,11 @@
     "s_mov_b32 %[dead], 0\n\t"                                                \
     "s_waitcnt lgkmcnt(0)\n\t"                                                \
     "v_cndmask_b32 %[F], v[vX], v[vZ], s[eMk:eMk+1]\n\t"                      \
-    "v_cndmask_b32 %[G], v[vY], v[vW], s[eMk:eMk+1]\n\t"                      \
-    "v_cmp_ge_i32 vcc, %[t], %[F]\n\t"                                        \
-    "s_bcnt1_i32_b64 s[eU], vcc\n\t"                                          \
-    "s_cmp_lg_u32 s[eU], 0\n\t"                                               \
-    "s_cbranch_scc1 .Lev_begin_%=\n\t"                                        \
-    "s_branch .Lev_begun_%=\n"                                                \
-                                                                              \
-    /* fit past the registers: groups of the stack from its end, eW one past  \
-       the group's entries */                                                 \
+    "v_cndmask_b32 %[G], v[vY], v[vW], s[eMk:eMk+1]\n\t"
+
+// The check past the registers: groups of the stack from its end, eW one past
+// the group's entries.
+#define EV_DEEP                                                               \
     ".Lev_deep_%=:\n\t"                                                       \
     "s_add_i32 s[eW], %[ln1], -65\n"                                          \
     ".Lev_deepg_%=:\n\t"                                                      \
@@ -605,40 +435,35 @@
     "s_cmp_ge_i32 s[eC1], s[eW]\n\t"                                          \
     "s_cbranch_scc1 .Lev_deepr_%=\n\t"                                        \
     "v_mov_b32 v[vX], v[vM]\n\t"                                              \
-    "s_branch .Lev_rel_%=\n"                                                  \
-                                                                              \
-    /* 64 staged admissions out; the issue priority by the remaining work */  \
-    ".Lev_flush_%=:\n\t"                                                      \
-    "v_lshlrev_b32 v[vAd], 2, %[sgi]\n\t"                                     \
-    "v_add_u32 v[vX], %[seq], %[lane]\n\t"                                    \
-    "s_add_i32 %[seq], %[seq], 64\n\t"                                        \
-    "s_mov_b32 %[nstg], 0\n\t"                                                \
-    "s_cmp_eq_u64 %[ctr], 0\n\t"                                              \
-    "s_cbranch_scc1 .Lev_noprio_%=\n\t"                                       \
+    "s_branch .Lev_rel_%=\n"
+
+// The issue priority by the remaining work, n - done requests; the progress
+// since the last update into the launch's counter.
+#define EV_PRIO(done)                                                         \
     "s_waitcnt vmcnt(0)\n\t"                                                  \
     "v_readfirstlane_b32 s[eU], v[vPd]\n\t"                                   \
     "v_readfirstlane_b32 s[eV], v[vPd+1]\n\t"                                 \
-    "s_sub_i32 s[eFa], %[n1], %[seq]\n\t"                                     \
+    "s_sub_i32 s[eFa], %[n1], " done "\n\t"                                   \
     "s_add_i32 s[eFa], s[eFa], 1\n\t"                                         \
-    "s_lshr_b32 s[eC1], s[eV], 8\n\t"          /* waves in the count */        \
+    "s_lshr_b32 s[eC1], s[eV], 8\n\t"          /* waves in the count */       \
     "s_and_b32 s[eV], s[eV], 0xff\n\t"                                        \
     "s_mul_i32 s[eX], s[eFa], s[eC1]\n\t"                                     \
     "s_mul_hi_u32 s[eX+1], s[eFa], s[eC1]\n\t"                                \
-    "s_sub_u32 s[eX], s[eX], s[eU]\n\t"        /* d: (mine - mean) * waves */  \
+    "s_sub_u32 s[eX], s[eX], s[eU]\n\t"        /* d: (mine - mean) * waves */ \
     "s_subb_u32 s[eX+1], s[eX+1], s[eV]\n\t"                                  \
-    "s_mul_i32 s[eMk], %[th], s[eC1]\n\t"      /* s: the level step * waves */ \
+    "s_mul_i32 s[eMk], %[th], s[eC1]\n\t"      /* s: the level step * waves */\
     "s_mul_hi_u32 s[eMk+1], %[th], s[eC1]\n\t"                                \
     "s_sub_u32 s[eU], s[eMk], s[eX]\n\t"                                      \
     "s_subb_u32 s[eU], s[eMk+1], s[eX+1]\n\t"                                 \
-    "s_cmp_lt_i32 s[eU], 0\n\t"                /* d > s */                     \
+    "s_cmp_lt_i32 s[eU], 0\n\t"                /* d > s */                    \
     "s_cbranch_scc1 .Lev_prio3_%=\n\t"                                        \
     "s_sub_u32 s[eU], 0, s[eX]\n\t"                                           \
     "s_subb_u32 s[eU], 0, s[eX+1]\n\t"                                        \
-    "s_cmp_lt_i32 s[eU], 0\n\t"                /* d > 0 */                     \
+    "s_cmp_lt_i32 s[eU], 0\n\t"                /* d > 0 */                    \
     "s_cbranch_scc1 .Lev_prio2_%=\n\t"                                        \
     "s_add_u32 s[eU], s[eX], s[eMk]\n\t"                                      \
     "s_addc_u32 s[eU], s[eX+1], s[eMk+1]\n\t"                                 \
-    "s_cmp_lt_i32 s[eU], 0\n\t"                /* d < -s */                    \
+    "s_cmp_lt_i32 s[eU], 0\n\t"                /* d < -s */                   \
     "s_cbranch_scc1 .Lev_prio0_%=\n\t"                                        \
     "s_setprio 1\n\t"                                                         \
     "s_branch .Lev_prio_%=\n"                                                 \
@@ -651,15 +476,216 @@
     ".Lev_prio3_%=:\n\t"                                                      \
     "s_setprio 3\n"                                                           \
     ".Lev_prio_%=:\n\t"                                                       \
-    "s_sub_i32 s[eU], %[last], %[seq]\n\t"                                    \
+    "s_sub_i32 s[eU], %[last], " done "\n\t"                                  \
     "s_ashr_i32 s[eV], s[eU], 31\n\t"                                         \
-    "s_mov_b32 %[last], %[seq]\n\t"                                           \
+    "s_mov_b32 %[last], " done "\n\t"                                         \
     "v_mov_b32 v[vZ], s[eU]\n\t"                                              \
     "v_mov_b32 v[vW], s[eV]\n\t"                                              \
     "v_mov_b32 v[vM], 0\n\t"                                                  \
     "s_mov_b64 exec, 1\n\t"                                                   \
-    "global_atomic_add_x2 v[vPd:vPd+1], v[vM], v[vZ:vZ+1], %[ctr] sc0\n\t"   \
-    "s_mov_b64 exec, -1\n"                                                    \
+    "global_atomic_add_x2 v[vPd:vPd+1], v[vM], v[vZ:vZ+1], %[ctr] sc0\n\t"    \
+    "s_mov_b64 exec, -1\n"
+
+// ---- the loop
+
+#define EV_LOOP(SET, OPEN, CLOSE, EMPTY, SCAN)                                \
+    EV_NAMES                                                                  \
+    "v_mov_b32 v[vM0], m0\n\t"                                                \
+    /* the first window's arrivals and ranks; the progress counter */         \
+    "v_add_u32 v[vAd], %[wb], %[lane]\n\t"                                    \
+    "v_min_i32 v[vAd], %[n1], v[vAd]\n\t"                                     \
+    "v_lshlrev_b32 v[vAd], 2, v[vAd]\n\t"                                     \
+    "global_load_dword v[vNa], v[vAd], %[arr]\n\t"                            \
+    "global_load_dword v[vNr], v[vAd], %[rank]\n\t"                           \
+    "s_cmp_lg_u64 %[ctr], 0\n\t"                                              \
+    "s_cbranch_scc0 .Lev_noctr_%=\n\t"                                        \
+    "v_mov_b32 v[vZ], 0\n\t"                                                  \
+    "global_load_dwordx2 v[vPd:vPd+1], v[vZ], %[ctr]\n"                       \
+    ".Lev_noctr_%=:\n\t"                                                      \
+    "s_sub_i32 %[wb], %[wb], 64\n\t"                                          \
+    EV_RELOAD                                                                 \
+                                                                              \
+    /* visit */                                                               \
+    ".Lev_visit_%=:\n\t"                                                      \
+    "s_add_i32 s[eU], %[seq], %[nstg]\n\t"                                    \
+    "s_cmp_gt_i32 s[eU], %[n1]\n\t"                                           \
+    "s_cbranch_scc1 .Lev_alladm_%=\n"                                         \
+    ".Lev_visit1_%=:\n\t"                                                     \
+    "s_cmp_ge_i32 %[t], %[tstop]\n\t"                                         \
+    "s_cbranch_scc1 .Lev_exit_%=\n\t"                                         \
+    "s_mov_b32 s[eR], %[head]\n"                                              \
+                                                                              \
+    /* arrivals */                                                            \
+    ".Lev_arr_%=:\n\t"                                                        \
+    "v_cmp_ge_i32 vcc, %[t], v[vA]\n\t"                                       \
+    "s_and_b64 s[eM1:eM1+1], vcc, %[pend]\n\t"                                \
+    "s_cbranch_scc0 .Lev_noarr_%=\n\t"                                        \
+    "s_andn2_b64 %[pend], %[pend], s[eM1:eM1+1]\n\t"                          \
+    SET("vRk", "")                                                            \
+    "v_cmp_gt_i32 vcc, s[eR], v[vRk]\n\t"                                     \
+    "s_and_b64 s[eX:eX+1], vcc, s[eM1:eM1+1]\n\t"                             \
+    "s_cbranch_scc0 .Lev_arrdone_%=\n\t"                                      \
+    "s_ff1_i32_b64 s[eI], s[eX:eX+1]\n\t"                                     \
+    "s_bcnt1_i32_b64 s[eU], s[eX:eX+1]\n\t"                                   \
+    "s_cmp_eq_u32 s[eU], 1\n\t"                                               \
+    "s_cbranch_scc1 .Lev_one_%=\n\t"                                          \
+    "v_cndmask_b32 v[vX], %[vmax], v[vRk], s[eX:eX+1]\n\t"                    \
+    EV_REDUCE("v_min_i32_dpp", "vX")                                          \
+    "v_readlane_b32 s[eU], v[vX], 63\n\t"                                     \
+    "s_nop 1\n\t"                                                             \
+    "v_cmp_eq_u32 vcc, s[eU], v[vRk]\n\t"                                     \
+    "s_and_b64 s[eX:eX+1], vcc, s[eX:eX+1]\n\t"                               \
+    "s_ff1_i32_b64 s[eI], s[eX:eX+1]\n"                                       \
+    ".Lev_one_%=:\n\t"                                                        \
+    "s_waitcnt vmcnt(0)\n\t"                                                  \
+    "v_readlane_b32 s[eR], v[vRk], s[eI]\n\t"                                 \
+    "v_readlane_b32 s[eQ], v[vAq], s[eI]\n\t"                                 \
+    "v_readlane_b32 s[eQ+1], v[vAq+1], s[eI]\n\t"                             \
+    "v_readlane_b32 s[eQ+2], v[vAq+2], s[eI]\n"                               \
+    ".Lev_arrdone_%=:\n\t"                                                    \
+    "s_cmp_eq_u64 %[pend], 0\n\t"                                             \
+    "s_cbranch_scc1 .Lev_reload_%=\n"                                         \
+    ".Lev_noarr_%=:\n\t"                                                      \
+    "s_cmp_lt_i32 s[eR], %[head]\n\t"                                         \
+    "s_cbranch_scc1 .Lev_cand_%=\n\t"                                         \
+    "s_cmp_ge_i32 %[t], %[tf]\n\t"                                            \
+    "s_cbranch_scc0 .Lev_adv_%=\n\t"                                          \
+    "s_mov_b32 s[eQ], %[h0]\n\t"                                              \
+    "s_mov_b32 s[eQ+1], %[h1]\n\t"                                            \
+    "s_mov_b32 s[eQ+2], %[h2]\n"                                              \
+                                                                              \
+    /* begin */                                                               \
+    ".Lev_cand_%=:\n\t"                                                       \
+    "v_cmp_ge_i32 vcc, %[t], %[F]\n\t"                                        \
+    "s_bcnt1_i32_b64 s[eU], vcc\n\t"                                          \
+    "s_add_i32 s[eT1], %[t], 1\n\t"                                           \
+    "s_add_i32 s[eMt], %[t], %[M]\n\t"                                        \
+    "s_cmp_lg_u32 s[eU], %[dead]\n\t"                                         \
+    "s_cbranch_scc1 .Lev_begin_%=\n"                                          \
+    ".Lev_begun_%=:\n\t"                                                      \
+    "s_mov_b32 %[tprev], %[t]\n\t"                                            \
+    "s_lshr_b32 s[eCw], s[eR], 6\n\t"                                         \
+    OPEN("o")                                                                 \
+                                                                              \
+    /* fit */                                                                 \
+    ".Lev_fit_%=:\n\t"                                                        \
+    EV_FIT                                                                    \
+    /* admitted */                                                            \
+    ".Lev_adm_%=:\n\t"                                                        \
+    "s_add_i32 %[ln1], %[ln1], 1\n\t"                                         \
+    "s_mov_b32 m0, %[nstg]\n\t"                                               \
+    "v_writelane_b32 %[sgi], s[eQ], m0\n\t"                                   \
+    "v_writelane_b32 %[sgt], %[t], m0\n\t"                                    \
+    "s_max_i32 %[mf], %[mf], s[eTe]\n\t"                                      \
+    "s_bitset0_b64 s[eCb:eCb+1], s[eR]\n\t"                                   \
+    "s_add_i32 %[nstg], %[nstg], 1\n\t"                                       \
+    "s_cmp_eq_u32 %[nstg], 64\n\t"                                            \
+    "s_cbranch_scc1 .Lev_flush_%=\n"                                          \
+    ".Lev_next_%=:\n\t"                                                       \
+    "s_cmp_eq_u64 s[eCb:eCb+1], 0\n\t"                                        \
+    "s_cbranch_scc1 .Lev_word_%=\n"                                           \
+    ".Lev_pick_%=:\n\t"                                                       \
+    "s_ff1_i32_b64 s[eR], s[eCb:eCb+1]\n\t"                                   \
+    "s_lshl_b32 s[eU], s[eCw], 6\n\t"                                         \
+    "s_add_i32 s[eR], s[eR], s[eU]\n\t"                                       \
+    "s_cmp_eq_u32 s[eR], %[head]\n\t"                                         \
+    "s_cbranch_scc1 .Lev_oldhead_%=\n"                                        \
+    ".Lev_rec_%=:\n\t"                                                        \
+    "s_lshl_b32 s[eU], s[eR], 4\n\t"                                          \
+    "s_load_dwordx4 s[eQ:eQ+3], %[rec], s[eU]\n\t"                            \
+    "s_waitcnt lgkmcnt(0)\n\t"                                                \
+    "s_branch .Lev_fit_%=\n"                                                  \
+    /* the old head: before t_f it still does not fit (the profile has only   \
+       grown since t_f was computed) */                                       \
+    ".Lev_oldhead_%=:\n\t"                                                    \
+    "s_cmp_ge_i32 %[t], %[tf]\n\t"                                            \
+    "s_cbranch_scc1 .Lev_rec_%=\n\t"                                          \
+    "s_branch .Lev_close_%=\n"                                                \
+    ".Lev_word_%=:\n\t"                                                       \
+    EMPTY                                                                     \
+    SCAN("")                                                                  \
+    "s_branch .Lev_pick_%=\n"                                                 \
+    ".Lev_none_%=:\n\t"                                                       \
+    "s_brev_b32 %[head], -2\n\t"                                              \
+    "s_brev_b32 %[tf], -2\n\t"                                                \
+    "s_branch .Lev_adv_%=\n"                                                  \
+                                                                              \
+    /* fail: t_f = max over the violating steps of min(tau, D + tau - X) */   \
+    ".Lev_fail_%=:\n\t"                                                       \
+    EV_REL                                                                    \
+    "s_mov_b32 %[head], s[eR]\n\t"                                            \
+    "s_mov_b32 %[h0], s[eQ]\n\t"                                              \
+    "s_mov_b32 %[h1], s[eQ+1]\n\t"                                            \
+    "s_mov_b32 %[h2], s[eQ+2]\n"                                              \
+    ".Lev_close_%=:\n\t"                                                      \
+    CLOSE("c")                                                                \
+                                                                              \
+    /* advance */                                                             \
+    ".Lev_adv_%=:\n\t"                                                        \
+    "v_cmp_gt_i32 vcc, %[head], v[vRk]\n\t"                                   \
+    "s_and_b64 s[eX:eX+1], vcc, %[pend]\n\t"                                  \
+    "s_cbranch_scc0 .Lev_advnone_%=\n\t"                                      \
+    "s_ff1_i32_b64 s[eI], s[eX:eX+1]\n\t"                                     \
+    "v_readlane_b32 s[eV], v[vA], s[eI]\n\t"                                  \
+    "s_min_i32 s[eV], s[eV], %[tf]\n"                                         \
+    ".Lev_advto_%=:\n\t"                                                      \
+    "s_add_i32 s[eU], %[t], 1\n\t"                                            \
+    "s_min_i32 s[eV], s[eV], %[tstop]\n\t"                                    \
+    "s_max_i32 %[t], s[eV], s[eU]\n\t"                                        \
+    "s_branch .Lev_visit_%=\n"                                                \
+    /* none in the window: its end, or (no more to come) the head's release   \
+       or the last finish */                                                  \
+    ".Lev_advnone_%=:\n\t"                                                    \
+    "s_add_i32 s[eU], %[wb], 63\n\t"                                          \
+    "s_mov_b32 s[eV], %[tf]\n\t"                                              \
+    "s_cmp_lt_i32 s[eU], %[n1]\n\t"                                           \
+    "s_cbranch_scc0 .Lev_advlast_%=\n\t"                                      \
+    "s_waitcnt vmcnt(0)\n\t"                                                  \
+    "v_readfirstlane_b32 s[eV], v[vNa]\n\t"                                   \
+    "s_min_i32 s[eV], s[eV], %[tf]\n\t"                                       \
+    "s_branch .Lev_advto_%=\n"                                                \
+    ".Lev_advlast_%=:\n\t"                                                    \
+    "s_add_i32 s[eU], %[mf], 1\n\t"                                           \
+    "s_cmp_eq_u32 %[head], 0x7fffffff\n\t"                                    \
+    "s_cselect_b32 s[eV], s[eU], s[eV]\n\t"                                   \
+    "s_branch .Lev_advto_%=\n"                                                \
+                                                                              \
+    ".Lev_reload_%=:\n\t"                                                     \
+    EV_RELOAD                                                                 \
+    "s_branch .Lev_arr_%=\n"                                                  \
+                                                                              \
+    /* begin: the memory at the finish steps of the newly finished entries,   \
+       tprev < F <= t; they stay in front until 32 have gathered */           \
+    ".Lev_begin_%=:\n\t"                                                      \
+    "s_add_i32 s[eV], %[tprev], 1\n\t"                                        \
+    "v_subrev_u32 v[vX], s[eV], %[F]\n\t"                                     \
+    "s_sub_i32 s[eV], %[t], %[tprev]\n\t"                                     \
+    "v_cmp_gt_u32 s[eMk:eMk+1], s[eV], v[vX]\n\t"                             \
+    "v_sub_u32 v[vY], %[G], %[F]\n\t"                                         \
+    "s_mov_b32 %[dead], s[eU]\n\t"                                            \
+    "s_nop 0\n\t"                                                             \
+    "v_cndmask_b32 v[vY], 0, v[vY], s[eMk:eMk+1]\n\t"                         \
+    "v_max_i32 %[peak], %[peak], v[vY]\n\t"                                   \
+    "s_cmp_lt_u32 s[eU], 32\n\t"                                              \
+    "s_cbranch_scc1 .Lev_begun_%=\n\t"                                        \
+    EV_DROP                                                                   \
+    "v_cmp_ge_i32 vcc, %[t], %[F]\n\t"                                        \
+    "s_bcnt1_i32_b64 s[eU], vcc\n\t"                                          \
+    "s_cmp_lg_u32 s[eU], 0\n\t"                                               \
+    "s_cbranch_scc1 .Lev_begin_%=\n\t"                                        \
+    "s_branch .Lev_begun_%=\n"                                                \
+                                                                              \
+    EV_DEEP                                                                   \
+                                                                              \
+    /* 64 staged admissions out; the issue priority by the remaining work */  \
+    ".Lev_flush_%=:\n\t"                                                      \
+    "v_lshlrev_b32 v[vAd], 2, %[sgi]\n\t"                                     \
+    "v_add_u32 v[vX], %[seq], %[lane]\n\t"                                    \
+    "s_add_i32 %[seq], %[seq], 64\n\t"                                        \
+    "s_mov_b32 %[nstg], 0\n\t"                                                \
+    "s_cmp_eq_u64 %[ctr], 0\n\t"                                              \
+    "s_cbranch_scc1 .Lev_noprio_%=\n\t"                                       \
+    EV_PRIO("%[seq]")                                                         \
     ".Lev_noprio_%=:\n\t"                                                     \
     "global_store_dword v[vAd], %[sgt], %[start]\n\t"                         \
     "global_store_dword v[vAd], v[vX], %[adm]\n\t"                            \
@@ -670,7 +696,7 @@
     ".Lev_full_%=:\n\t"                                                       \
     "s_mov_b32 %[head], s[eR]\n\t"                                            \
     "s_mov_b32 %[tf], -1\n\t"                                                 \
-    CLOSE_FULL                                                                \
+    CLOSE("g")                                                                \
     "s_branch .Lev_exit_%=\n"                                                 \
     ".Lev_alladm_%=:\n\t"                                                     \
     "s_cmp_lt_i32 %[mf], %[t]\n\t"                                            \
@@ -680,9 +706,9 @@
     "v_readfirstlane_b32 s[eU], v[vM0]\n\t"                                   \
     "s_mov_b32 m0, s[eU]\n\t"
 
-#define EV_LOOP_1 EV_LOOP(EV_SET_1, EV_OPEN_1, EV_CLOSE_1, EV_CLOSE_1, EV_FIND_1)
-#define EV_LOOP_2 EV_LOOP(EV_SET_2, EV_OPEN_2("o"), EV_CLOSE_2("c"), EV_CLOSE_2("g"), EV_FIND_2)
-#define EV_LOOP_0 EV_LOOP(EV_SET_0, EV_OPEN_0, EV_CLOSE_0, EV_CLOSE_0, EV_FIND_0)
+#define EV_LOOP_1 EV_LOOP(EV_SET_1, EV_OPEN_1, EV_CLOSE_1, EV_EMPTY_1, EV_SCAN_1)
+#define EV_LOOP_2 EV_LOOP(EV_SET_2, EV_OPEN_2, EV_CLOSE_2, EV_EMPTY_2, EV_SCAN_2)
+#define EV_LOOP_0 EV_LOOP(EV_SET_0, EV_OPEN_0, EV_CLOSE_0, EV_EMPTY_0, EV_SCAN_0)
 
 #define EV_STATE                                                              \
     [t] "+&s"(t), [head] "+&s"(head), [tf] "+&s"(t_f), [h0] "+&s"(hq.x),          \

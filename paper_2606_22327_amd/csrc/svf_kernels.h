@@ -23,7 +23,8 @@ struct SegState {
     int32_t head_rank;  // event path: blocked head (-1: none known)
     int32_t t_f;        // event path: the head cannot fit before this step
     int32_t N_O;        // per-step path: requests past their planned length
-    int64_t C_O;        // per-step path: sum of (s - k) over those requests
+    int64_t C_O;        // per-step path: sum of (s - k) over those requests (k_sim_step: over all
+                        //   running ones, modulo 2^32)
     int64_t peak;       // largest memory total over the steps folded so far
     int64_t req_steps;  // per-step path: sum over steps of running requests
     int32_t ln;         // event path with the list profile: running requests
@@ -104,6 +105,7 @@ struct SimArgs {
     int32_t list_stride;      // entries per segment in HBM (bound on concurrent requests)
     int32_t list_cap;         // entries per segment in this launch (in LDS and registers)
     int32_t list_nb;          // event path: bitmap pairs in registers (0: bitmap in LDS)
+    int32_t step_regs;        // per-step path: its running requests in registers (k_sim_step)
     int32_t list_resume;      // 1: only continue the segments that stopped with a full list
     int32_t resident;         // workgroups of this launch resident at once (0: no issue priorities)
     unsigned long long* prog; // [PROG_WORDS] progress counters of this launch, cleared before it
@@ -148,6 +150,17 @@ enum { LIST_DEAD_MAX = 32 };
 hipError_t prepare_list(int nb, size_t lds_first, size_t lds_full);
 // resident waves per compute unit of its first launch
 hipError_t list_occupancy(int nb, size_t lds_bytes, int* blocks);
+// The per-step path with its running requests in registers: places of the
+// first launch and of the continuation (64 each), and what it assumes of a
+// batch: the bound on running requests below its places, indexes and ranks in
+// 16 bits, the factors of a remaining volume in 24 bits, twice a volume in 32.
+enum { STEP_E = 6, STEP_E_FULL = 32 };
+inline bool step_regs_ok(int64_t bound, int64_t max_n, int64_t M, uint64_t max_volume) {
+    return bound < 64 * STEP_E_FULL && max_n <= 65536 && M < (1 << 23) - 1 &&
+           max_volume < (uint64_t(1) << 31);
+}
+hipError_t prepare_step(int nb, size_t lds_first, size_t lds_full);
+hipError_t step_occupancy(int nb, size_t lds_bytes, int* blocks);
 // list: the event path keeps its profile as the finish-ordered list
 hipError_t launch_sim(const SimArgs& P, int G, bool d_lds, bool stepped, bool list,
                       size_t lds_bytes, hipStream_t s);

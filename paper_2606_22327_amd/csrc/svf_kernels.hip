@@ -13,8 +13,8 @@
 //                     (each element finds its output slot by binary search in
 //                     the partner run)
 //   k_build_rec       rank-ordered request records and the index->rank map
-//   k_sim<D_LDS, STEPPED>, k_sim_list<NB, RESUME>, k_sim_steplist,
-//   k_sim_steplist_stop, k_sim_steplist_resume
+//   k_sim<D_LDS, STEPPED>, k_sim_list<NB, RESUME>, k_sim_step<NB, E>,
+//   k_sim_steplist, k_sim_steplist_stop, k_sim_steplist_resume
 //                     the simulation: one wave64 per segment (profile as a ring,
 //                     per-step or event-driven; or as a finish-ordered list);
 //                     the waves order their issue priorities by remaining work
@@ -41,7 +41,7 @@
 // is the list of running requests ordered by planned finish: between
 // admissions the memory only drops at finishes, so the check visits just the
 // finishes inside the candidate's window and its last step (ListProf with the
-// loop of svf_event_loop.h, StepList).  The host picks the form per batch: the list
+// loop of svf_event_loop.h or svf_step_loop.h, StepList).  The host picks the form per batch: the list
 // where few requests run at once, the ring where many do.
 //
 // Known lengths (the scheduler plans with the true length) make D change only
@@ -62,6 +62,7 @@
 
 #include "svf_event_loop.h"
 #include "svf_kernels.h"
+#include "svf_step_loop.h"
 
 namespace svfk {
 
@@ -1191,9 +1192,42 @@ __device__ __forceinline__ void run_known(const SimArgs& P, const Seg& sg, BITS&
     st.peak = max(st.peak, (int64_t)pk);
 }
 
-// run_known with the finish-ordered list: the loop is svf_event_loop.h.  The
-// rank bitmap is in registers (word w in lane w & 63 of pair w >> 6) for up to
-// 4096 NB requests, for NB = 0 in LDS at B, its upper level behind its W0 words.
+// The rank bitmap of the assembly loops: in registers (word w in lane w & 63 of
+// pair w >> 6) for up to 4096 NB requests, for NB = 0 in LDS at B, its upper
+// level behind its W0 words.
+template <int NB>
+__device__ __forceinline__ void bits_in(const uint64_t* Bg, uint64_t* B, int W0, int W1, int& lo0,
+                                        int& hi0, int& lo1, int& hi1) {
+    const int lane = lane_id();
+    if (NB > 0) {
+        const uint64_t v = lane < W0 ? Bg[lane] : 0ull;
+        lo0 = (int)(uint32_t)v;
+        hi0 = (int)(uint32_t)(v >> 32);
+    }
+    if (NB > 1) {
+        const uint64_t v = 64 + lane < W0 ? Bg[64 + lane] : 0ull;
+        lo1 = (int)(uint32_t)v;
+        hi1 = (int)(uint32_t)(v >> 32);
+    }
+    if (NB == 0) {
+        for (int x = lane; x < W0 + W1; x += 64) B[x] = Bg[x];
+        lds_order();
+    }
+}
+
+template <int NB>
+__device__ __forceinline__ void bits_out(uint64_t* Bg, const uint64_t* B, int W0, int W1, int lo0,
+                                         int hi0, int lo1, int hi1) {
+    const int lane = lane_id();
+    if (NB > 0 && lane < W0) Bg[lane] = ((uint64_t)(uint32_t)hi0 << 32) | (uint32_t)lo0;
+    if (NB > 1 && 64 + lane < W0) Bg[64 + lane] = ((uint64_t)(uint32_t)hi1 << 32) | (uint32_t)lo1;
+    if (NB == 0) {
+        lds_order();
+        for (int x = lane; x < W0 + W1; x += 64) Bg[x] = B[x];
+    }
+}
+
+// run_known with the finish-ordered list: the loop is svf_event_loop.h.
 template <int NB>
 __device__ __forceinline__ void run_list(const SimArgs& P, const Seg& sg, uint64_t* Bg, uint64_t* B,
                                          int W0, int W1, ListProf& L, SegState& st, int t_lim) {
@@ -1213,20 +1247,7 @@ __device__ __forceinline__ void run_list(const SimArgs& P, const Seg& sg, uint64
     prio.init(P, n, seq);
 
     int lo0 = 0, hi0 = 0, lo1 = 0, hi1 = 0;
-    if (NB > 0) {
-        const uint64_t v = lane < W0 ? Bg[lane] : 0ull;
-        lo0 = (int)(uint32_t)v;
-        hi0 = (int)(uint32_t)(v >> 32);
-    }
-    if (NB > 1) {
-        const uint64_t v = 64 + lane < W0 ? Bg[64 + lane] : 0ull;
-        lo1 = (int)(uint32_t)v;
-        hi1 = (int)(uint32_t)(v >> 32);
-    }
-    if (NB == 0) {
-        for (int x = lane; x < W0 + W1; x += 64) B[x] = Bg[x];
-        lds_order();
-    }
+    bits_in<NB>(Bg, B, W0, W1, lo0, hi0, lo1, hi1);
     int status = STATUS_RUNNING;
     if (n == 0) {
         status = STATUS_DONE;  // at its first step
@@ -1255,12 +1276,7 @@ __device__ __forceinline__ void run_list(const SimArgs& P, const Seg& sg, uint64
         if (seq == n && max_fin <= t - 1) status = STATUS_DONE;
         else if (t > P.max_steps && t_f >= 0) status = STATUS_EXHAUSTED;
     }
-    if (NB > 0 && lane < W0) Bg[lane] = ((uint64_t)(uint32_t)hi0 << 32) | (uint32_t)lo0;
-    if (NB > 1 && 64 + lane < W0) Bg[64 + lane] = ((uint64_t)(uint32_t)hi1 << 32) | (uint32_t)lo1;
-    if (NB == 0) {
-        lds_order();
-        for (int x = lane; x < W0 + W1; x += 64) Bg[x] = B[x];
-    }
+    bits_out<NB>(Bg, B, W0, W1, lo0, hi0, lo1, hi1);
     prio.leave();
     // the peak over the steps up to t
     const int pk = L.end(t);
@@ -1269,6 +1285,75 @@ __device__ __forceinline__ void run_list(const SimArgs& P, const Seg& sg, uint64
     st.t_f = head == INT32_MAX ? 0 : t_f;
     st.status = status;
     st.peak = max(st.peak, (int64_t)pk);
+}
+
+// The per-step path with its running requests in registers, 64 E places: the
+// loop is svf_step_loop.h.  nev: -1, or the number of requests evicted at step
+// st.t when the segment continues inside the admissions of that step.
+template <int NB, int E>
+__device__ __forceinline__ void run_step_list(const SimArgs& P, const Seg& sg, uint64_t* Bg,
+                                              uint64_t* B, int W0, int W1, ListProf& L,
+                                              SegState& st, int t_lim, int nev) {
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    const int lane = lane_id();
+    const int n = sg.n;
+    int t = uni(st.t), seq = uni(st.seq), nstg = 0, stg_idx = 0, stg_t = 0;
+    int nfin = uni(st.nfin), nA = uni(st.nA), C = uni((int)st.C_O), peak = 0;
+    const int t_stop = min(t_lim, P.max_steps + 1);
+    const int cur = (P.policies[blockIdx.x / P.I] & ADMIT_CURRENT) ? 1 : 0;
+    // nothing is known of the waiting requests; every running one is looked at
+    // at the first step
+    int head = INT32_MAX, t_f = 0, next_ev = t;
+    uint32_t rs_lo = 0u, rs_hi = 0u;
+    IssuePrio prio;
+    prio.init(P, n, nfin);
+    int lo0 = 0, hi0 = 0, lo1 = 0, hi1 = 0;
+    bits_in<NB>(Bg, B, W0, W1, lo0, hi0, lo1, hi1);
+    int status = STATUS_RUNNING;
+    st.resume_nev = -1;
+    if (n == 0) {
+        status = STATUS_DONE;  // at its first step
+    } else {
+        const uint32_t stk = (uint32_t)(uintptr_t)(lds_ptr)L.stk;
+        int wb = uni(st.cursor), ln1 = L.ln + 1;
+        uint64_t pend = ~0ull;
+        L.dead = (int)__popcll(ballot(L.F <= t));
+#define ST_RUN(NB_, E_, ...)                                                                      \
+    asm volatile(ST_LOOP_##NB_(E_) : ST_STATE __VA_ARGS__ : ST_INPUT : ST_CLOBBER_##E_)
+#define ST_RUN_0(E_)                                                                              \
+    asm volatile(ST_LOOP_0(E_) : ST_STATE                                                         \
+                 : ST_INPUT, [bb] "s"(bb), [sb] "s"(bb + 8 * W0), [w1] "s"(W1) : ST_CLOBBER_##E_)
+        if (NB == 1) {
+            if (E == 6) ST_RUN(1, 6, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0));
+            else ST_RUN(1, 32, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0));
+        } else if (NB == 2) {
+            if (E == 6) ST_RUN(2, 6, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0), [b1l] "+&v"(lo1), [b1h] "+&v"(hi1));
+            else ST_RUN(2, 32, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0), [b1l] "+&v"(lo1), [b1h] "+&v"(hi1));
+        } else {
+            const uint32_t bb = (uint32_t)(uintptr_t)(lds_ptr)B;
+            if (E == 6) ST_RUN_0(6);
+            else ST_RUN_0(32);
+        }
+#undef ST_RUN
+#undef ST_RUN_0
+        L.ln = ln1 - 1;
+        // (the global list has room for the running requests only)
+        for (int nd; (nd = (int)__popcll(ballot(L.F <= t))) > 0;) L.drop(nd);
+        st.cursor = min(wb + __builtin_ctzll(pend), n);
+        if (lane < nstg) {
+            sg.start[stg_idx] = stg_t;
+            sg.admit_seq[stg_idx] = seq + lane;
+        }
+        seq += nstg;
+        if (t_f < 0) st.resume_nev = nev;
+        else if (nfin == n) status = STATUS_DONE;
+        else if (t > P.max_steps) status = STATUS_EXHAUSTED;
+    }
+    bits_out<NB>(Bg, B, W0, W1, lo0, hi0, lo1, hi1);
+    prio.leave();
+    st.t = t; st.seq = seq; st.nfin = nfin; st.nA = nA; st.C_O = C; st.status = status;
+    st.peak = max(st.peak, (int64_t)peak);
+    st.req_steps += (int64_t)(((uint64_t)rs_hi << 32) | rs_lo);
 }
 
 // ---- planned lengths differ from the truth: one step at a time
@@ -1932,14 +2017,16 @@ __device__ __forceinline__ Seg segment(const SimArgs& P, int pol, int64_t off, i
     return sg;
 }
 
-// The event path with the finish-ordered list, one wave64 per segment: the
-// bitmap in registers (NB > 0) or at the start of the LDS, then the list's
-// stack.  List and bitmap are kept in global memory between launches.
-template <int NB>
-__device__ __forceinline__ void known_list_segment(const SimArgs& P) {
+// The paths whose loop is in assembly, one wave64 per segment: the bitmap in
+// registers (NB > 0) or at the start of the LDS, then the list's stack.  List,
+// bitmap and running requests are kept in global memory between launches.
+// E: groups of places for the running requests of the per-step path (0: the
+// event path).
+template <int NB, int E>
+__device__ __forceinline__ void list_segment(const SimArgs& P) {
     extern __shared__ uint64_t smem[];
     const int g = blockIdx.x;
-    if (P.stepped[g] != 0) return;
+    if ((P.stepped[g] != 0) != (E > 0)) return;
     const int lane = lane_id();
     const int pol = g / P.I, inst = g - pol * P.I;
     const int64_t off = P.offsets[inst];
@@ -1949,14 +2036,15 @@ __device__ __forceinline__ void known_list_segment(const SimArgs& P) {
     if (P.list_resume && st.resume_lim == 0) return;
     int t_lim = (int)min((int64_t)st.t + P.step_delta, (int64_t)P.max_steps + 2);
     if (P.list_resume) t_lim = st.resume_lim;
-    if (st.ln > P.list_cap) {
+    if (st.ln > P.list_cap || (E > 0 && st.nA > 64 * E)) {
         // more running than this launch has room for: left to the continuation
         st.resume_lim = t_lim;
         if (lane == 0) P.st[g] = st;
         return;
     }
     st.resume_lim = 0;
-    // a stop on a full list left t_f = -1: the head is checked again at t
+    // a stop of the event path on a full list left t_f = -1: the head is
+    // checked again at t
     if (st.t_f < 0) st.t_f = st.t;
 
     const Seg sg = segment(P, pol, off, n);
@@ -1972,10 +2060,15 @@ __device__ __forceinline__ void known_list_segment(const SimArgs& P) {
     L.tprev = uni(st.t);
     L.peak_lane = 0;
     L.load(Fg, Gg, uni(st.ln));
-    run_list<NB>(P, sg, Bg, smem, W0, W1, L, st, t_lim);
+    if (E == 0) {
+        run_list<NB>(P, sg, Bg, smem, W0, W1, L, st, t_lim);
+        if (st.t_f < 0) st.resume_lim = t_lim;  // stopped on a full list
+    } else {
+        run_step_list<NB, E>(P, sg, Bg, smem, W0, W1, L, st, t_lim, uni(st.resume_nev));
+        if (st.resume_nev >= 0) st.resume_lim = t_lim;  // stopped inside step st.t
+    }
     L.store(Fg, Gg);
     st.ln = L.ln;
-    if (st.t_f < 0) st.resume_lim = t_lim;  // stopped on a full list
     if (lane == 0) P.st[g] = st;
 }
 
@@ -2104,11 +2197,18 @@ __global__ __launch_bounds__(64) void k_sim(SimArgs P) {
 template <int NB, bool RESUME>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void k_sim_list(SimArgs P) {
-    known_list_segment<NB>(P);
+    list_segment<NB, 0>(P);
 }
 
-// The per-step path with the finish-ordered list: with room for the bound,
-// with less (segments may stop inside a step), and the continuation.
+// The per-step path with the running requests in registers, 64 E places.
+template <int NB, int E>
+__global__ __launch_bounds__(64) void k_sim_step(SimArgs P) {
+    list_segment<NB, E>(P);
+}
+
+// The per-step path with the finish-ordered list and the running requests in
+// global memory (batches past the limits of k_sim_step): with room for the
+// bound, with less (segments may stop inside a step), and the continuation.
 __global__ __launch_bounds__(64) void k_sim_steplist(SimArgs P) {
     sim_segment<false, true, true>(P);
 }
@@ -2316,10 +2416,19 @@ static SimKernel list_kernel(int nb, bool resume) {
     return resume ? &k_sim_list<0, true> : &k_sim_list<0, false>;
 }
 
+// the per-step path's kernel with the running requests in registers
+static SimKernel step_kernel(int nb, bool resume) {
+    if (nb == 1) return resume ? &k_sim_step<1, STEP_E_FULL> : &k_sim_step<1, STEP_E>;
+    if (nb == 2) return resume ? &k_sim_step<2, STEP_E_FULL> : &k_sim_step<2, STEP_E>;
+    return resume ? &k_sim_step<0, STEP_E_FULL> : &k_sim_step<0, STEP_E>;
+}
+
 hipError_t launch_sim(const SimArgs& P, int G, bool d_lds, bool stepped, bool list,
                       size_t lds_bytes, hipStream_t s) {
     if (G <= 0) return hipSuccess;
-    if (stepped && list) {
+    if (stepped && list && P.step_regs) {
+        hipLaunchKernelGGL(step_kernel(P.list_nb, P.list_resume != 0), dim3(G), dim3(64), lds_bytes, s, P);
+    } else if (stepped && list) {
         if (P.list_resume) hipLaunchKernelGGL(k_sim_steplist_resume, dim3(G), dim3(64), lds_bytes, s, P);
         else if (P.list_cap < P.list_stride) hipLaunchKernelGGL(k_sim_steplist_stop, dim3(G), dim3(64), lds_bytes, s, P);
         else hipLaunchKernelGGL(k_sim_steplist, dim3(G), dim3(64), lds_bytes, s, P);
@@ -2360,6 +2469,19 @@ hipError_t prepare_list(int nb, size_t lds_first, size_t lds_full) {
     hipError_t r = sim_attr((const void*)list_kernel(nb, false), lds_first);
     if (r == hipSuccess) r = sim_attr((const void*)list_kernel(nb, true), lds_full);
     return r;
+}
+
+hipError_t prepare_step(int nb, size_t lds_first, size_t lds_full) {
+    hipError_t r = sim_attr((const void*)step_kernel(nb, false), lds_first);
+    if (r == hipSuccess) r = sim_attr((const void*)step_kernel(nb, true), lds_full);
+    return r;
+}
+
+hipError_t step_occupancy(int nb, size_t lds_bytes, int* blocks) {
+    const void* f = (const void*)step_kernel(nb, false);
+    hipError_t r = sim_attr(f, lds_bytes);
+    if (r != hipSuccess) return r;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, 64, lds_bytes);
 }
 
 hipError_t list_occupancy(int nb, size_t lds_bytes, int* blocks) {

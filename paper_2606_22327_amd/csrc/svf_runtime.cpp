@@ -75,6 +75,8 @@ struct svf_batch {
     size_t lds_list = 0;      // LDS of the event kernel with the list
     size_t lds_list_full = 0; //   and with room for the bound (continuation)
     bool list_stepped = false; // per-step path: profile as the finish-ordered list
+    bool step_regs = false;    //   and its running requests in registers
+    int32_t step_full = 0;     // its entries with room for the bound (continuation)
     int32_t step_cap = 0;      // its entries in LDS (first launch)
     size_t lds_step = 0;       // LDS of the per-step kernel with the list
     size_t lds_step_full = 0;  //   and with room for the bound (continuation)
@@ -176,15 +178,18 @@ struct HostView {
 // planned (and true) total of that step stays <= M once a step's admissions
 // are done, so at most the k smallest values of s + 1 fit.  Values at or
 // above kCap count as kCap (a lower bound on each), which keeps k an upper
-// bound.
-int64_t running_bound(const int32_t* s, const int64_t* off, int32_t I, int64_t M) {
+// bound.  The largest s goes to max_s.
+int64_t running_bound(const int32_t* s, const int64_t* off, int32_t I, int64_t M, int32_t* max_s) {
     constexpr int kCap = 4096;
     int64_t h[kCap + 1];
     int64_t best = 0;
+    int32_t top = 1;
     for (int32_t i = 0; i < I; ++i) {
         std::fill(h, h + kCap + 1, 0);
-        for (int64_t j = off[i]; j < off[i + 1]; ++j)
+        for (int64_t j = off[i]; j < off[i + 1]; ++j) {
             h[std::min<int64_t>((int64_t)s[j] + 1, kCap)] += 1;
+            top = std::max(top, s[j]);
+        }
         int64_t sum = 0, k = 0;
         for (int v = 1; v <= kCap; ++v) {
             if (!h[v]) continue;
@@ -195,6 +200,7 @@ int64_t running_bound(const int32_t* s, const int64_t* off, int32_t I, int64_t M
         }
         best = std::max(best, k);
     }
+    *max_s = top;
     return best;
 }
 
@@ -355,14 +361,15 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
     // registers allow; segments that outgrow it stop, and a second launch with
     // room for the bound on concurrent requests (and for finished entries not
     // yet removed) continues them.
+    int32_t max_s = 1;
     const int64_t bound = (h->n_known > 0 || h->any_stepped)
-                              ? std::max<int64_t>(1, running_bound(v.s, off, I, d->M)) : 1;
+                              ? std::max<int64_t>(1, running_bound(v.s, off, I, d->M, &max_s)) : 1;
     const size_t full_bytes = bm_bytes + (size_t)svfk::list_slots((int)std::min<int64_t>(bound, 1 << 24)) * 8;
+    h->list_nb = svfk::list_bitmap_pairs(h->max_n);
+    const size_t lds_bm = h->list_nb == 0 ? bm_bytes : 0;  // of the kernels that may keep the bitmap in registers
     if (h->n_known > 0) {
         const char* pe = getenv("SVFSIM_PROFILE");
         bool use = false;
-        h->list_nb = svfk::list_bitmap_pairs(h->max_n);
-        const size_t lds_bm = h->list_nb == 0 ? bm_bytes : 0;
         h->list_full = (int32_t)std::min<int64_t>(bound + svfk::LIST_DEAD_MAX, 1 << 24);
         h->lds_list_full = lds_bm + svfk::list_lds(h->list_full);
         int64_t cap = h->list_full;
@@ -409,24 +416,34 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
         if (ps && !strcmp(ps, "ring")) use = false;
         if (ps && !strcmp(ps, "list")) use = full_bytes <= 160 * 1024;
         if (use) {
-            auto occ = [&](size_t bytes) {
-                int w = 0;
-                return svfk::sim_step_occupancy(bytes, &w) == hipSuccess ? w : -1;
+            // its running requests in registers, within that kernel's limits
+            const uint64_t L = (uint64_t)max_plan;  // (no volume is larger than this one)
+            h->step_regs = svfk::step_regs_ok(bound, h->max_n, d->M,
+                                              (uint64_t)max_s * L + ((L * L + L) >> 1));
+            h->step_full = (int32_t)(bound + (h->step_regs ? svfk::LIST_DEAD_MAX : 0));
+            auto bytes = [&](int64_t c) {
+                return h->step_regs ? lds_bm + svfk::list_lds(c)
+                                    : bm_bytes + (size_t)svfk::list_slots((int)c) * 8;
             };
-            const int w_top = occ(bm_bytes + (size_t)svfk::list_slots(64) * 8);
-            int64_t lo = std::min<int64_t>(bound, 64), hi = bound;
+            auto occ = [&](int64_t c) {
+                int w = 0;
+                return (h->step_regs ? svfk::step_occupancy(h->list_nb, bytes(c), &w)
+                                     : svfk::sim_step_occupancy(bytes(c), &w)) == hipSuccess ? w : -1;
+            };
+            const int w_top = occ(64);
+            int64_t lo = std::min<int64_t>(h->step_full, 64), hi = h->step_full;
             while (w_top > 0 && lo < hi) {
                 const int64_t mid = lo + (hi - lo + 1) / 2;
-                if (occ(bm_bytes + (size_t)svfk::list_slots((int)mid) * 8) >= w_top) lo = mid;
+                if (occ(mid) >= w_top) lo = mid;
                 else hi = mid - 1;
             }
-            int64_t cap = w_top > 0 ? lo : bound;
-            const char* pc = getenv("SVFSIM_STEP_LDS_CAP");  // testing: a smaller LDS list
+            int64_t cap = w_top > 0 ? lo : h->step_full;
+            const char* pc = getenv("SVFSIM_STEP_LDS_CAP");  // testing: a smaller list
             if (pc && atoll(pc) > 0) cap = std::min<int64_t>(cap, atoll(pc));
             h->list_stepped = true;
             h->step_cap = (int32_t)cap;
-            h->lds_step = bm_bytes + (size_t)svfk::list_slots((int)cap) * 8;
-            h->lds_step_full = full_bytes;
+            h->lds_step = bytes(cap);
+            h->lds_step_full = bytes(h->step_full);
         }
     }
     if (h->list_known || h->list_stepped) h->list_stride = (int32_t)bound;
@@ -447,8 +464,10 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
                 h->res_known = w * ncu;
             w = 0;
             if (h->any_stepped &&
-                svfk::sim_occupancy(true, h->list_stepped, h->d_lds,
-                                    h->list_stepped ? h->lds_step : h->lds_bytes, &w) == hipSuccess)
+                (h->step_regs ? svfk::step_occupancy(h->list_nb, h->lds_step, &w)
+                              : svfk::sim_occupancy(true, h->list_stepped, h->d_lds,
+                                                    h->list_stepped ? h->lds_step : h->lds_bytes,
+                                                    &w)) == hipSuccess)
                 h->res_stepped = w * ncu;
         }
         (void)hipGetLastError();
@@ -564,6 +583,7 @@ int do_sim(svf_batch* h, int64_t delta) {
     S.list_stride = h->list_stride;
     S.list_cap = h->list_cap;
     S.list_nb = h->list_nb;
+    S.step_regs = h->step_regs;
     S.list_resume = 0;
     S.resident = h->res_known;
     S.prog = h->d_prog;
@@ -595,9 +615,11 @@ int do_sim(svf_batch* h, int64_t delta) {
         T.prog = h->d_prog + svfk::PROG_WORDS;
         le = svfk::launch_sim(T, G, h->d_lds, true, h->list_stepped,
                               h->list_stepped ? h->lds_step : h->lds_bytes, st_stepped);
-        if (le == hipSuccess && h->list_stepped && h->step_cap < h->list_stride) {
-            // segments whose list outgrew the LDS capacity, up to the same step
-            T.list_cap = h->list_stride;
+        if (le == hipSuccess && h->list_stepped &&
+            (h->step_cap < h->step_full || (h->step_regs && h->list_stride > 64 * svfk::STEP_E))) {
+            // segments whose list outgrew the LDS capacity (or whose running
+            // requests the registers), up to the same step
+            T.list_cap = h->step_full;
             T.list_resume = 1;
             T.resident = 0;
             le = svfk::launch_sim(T, G, false, true, true, h->lds_step_full, st_stepped);
@@ -812,7 +834,10 @@ int svf_create(const svf_batch_desc* d, void* hip_stream, svf_batch** out) {
     if (e == hipSuccess) e = svfk::launch_fill_i32(h->d_pre, PN, 0, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e == hipSuccess) {
-        hipError_t a = svfk::prepare_sim(h->d_lds, h->lds_bytes, h->list_stepped, h->lds_step_full);
+        hipError_t a = svfk::prepare_sim(h->d_lds, h->lds_bytes, h->list_stepped && !h->step_regs,
+                                         h->lds_step_full);
+        if (a == hipSuccess && h->step_regs)
+            a = svfk::prepare_step(h->list_nb, h->lds_step, h->lds_step_full);
         if (a == hipSuccess && h->list_known)
             a = svfk::prepare_list(h->list_nb, h->lds_list, h->lds_list_full);
         if (a != hipSuccess) e = a;
@@ -1030,7 +1055,8 @@ int svf_run_noalloc(const svf_batch_desc* d, void* hip_stream, int32_t* start, i
     if (e == hipSuccess) e = hipStreamSynchronize(h.stream);
     if (e != hipSuccess)
         return fail(SVF_EHIP, "svf_run_noalloc: copying the inputs failed: %s", hipGetErrorString(e));
-    HIPCHK(svfk::prepare_sim(h.d_lds, h.lds_bytes, h.list_stepped, h.lds_step_full));
+    HIPCHK(svfk::prepare_sim(h.d_lds, h.lds_bytes, h.list_stepped && !h.step_regs, h.lds_step_full));
+    if (h.step_regs) HIPCHK(svfk::prepare_step(h.list_nb, h.lds_step, h.lds_step_full));
     if (h.list_known) HIPCHK(svfk::prepare_list(h.list_nb, h.lds_list, h.lds_list_full));
     if (h.max_n > 0) HIPCHK(svfk::prepare_sort_rec(h.max_n));
     RETCHK(do_reset(&h));
