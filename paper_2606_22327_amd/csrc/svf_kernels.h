@@ -45,6 +45,9 @@ struct StatsOut {
     int64_t t_end;
 };
 
+// Progress counters of one launch: one per cache line.
+enum { PROG_LINES = 64, PROG_STRIDE = 16, PROG_WORDS = PROG_LINES * PROG_STRIDE };
+
 struct SortArgs {
     const int64_t* offsets;   // [I+1]
     const int32_t* a;         // [N]
@@ -69,10 +72,22 @@ struct SortArgs {
     int32_t* fin;
     int32_t* preempt;
     int32_t* admit_seq;
+    int32_t clear_all;        // 1: finishes and preemptions of event-path segments too
+    SegState* st;             // [G] and the rest of a run's first state, written by the fused sort
+    uint64_t* bitmap;         // [P*bw_total]
+    const int64_t* bw_off;    // [I+1]
+    int64_t bw_total;
+    int32_t* ring;            // [G*(H+64)] or null
+    int32_t H;
+    unsigned long long* prog; // [2*PROG_WORDS]
 };
 
-// Progress counters of one launch: one per cache line.
-enum { PROG_LINES = 64, PROG_STRIDE = 16, PROG_WORDS = PROG_LINES * PROG_STRIDE };
+// One launch copies arrays of n words (32 bits).
+struct CopyArgs {
+    const int32_t* src[4];
+    int32_t* dst[4];
+    int64_t n;
+};
 
 struct SimArgs {
     const int64_t* offsets;
@@ -108,7 +123,8 @@ struct SimArgs {
     int32_t step_regs;        // per-step path: its running requests in registers (k_sim_step)
     int32_t list_resume;      // 1: only continue the segments that stopped with a full list
     int32_t resident;         // workgroups of this launch resident at once (0: no issue priorities)
-    unsigned long long* prog; // [PROG_WORDS] progress counters of this launch, cleared before it
+    unsigned long long* prog; // [PROG_WORDS] progress counters of this launch, zero before it (and after
+                              //   it: every wave takes back what it added)
 };
 
 struct FinArgs {
@@ -129,6 +145,7 @@ struct FinArgs {
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_init_ring(int32_t* ring, int64_t n, int32_t H, hipStream_t s);
+hipError_t launch_copy4(const CopyArgs& C, int arrays, hipStream_t s);
 hipError_t launch_init_state(SegState* st, int32_t G, hipStream_t s);
 hipError_t launch_chunk_sort(const SortArgs& A, int nchunks, hipStream_t s);
 hipError_t launch_merge_pass(const SortArgs& A, int nchunks, int w, hipStream_t s);

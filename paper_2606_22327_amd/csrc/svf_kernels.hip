@@ -2,7 +2,7 @@
 //
 // One "segment" is one instance under one policy; segments are independent.
 // Kernels, in launch order:
-//   k_fill_*          clear state, bitmaps, rings and outputs (no memset nodes)
+//   k_fill_*, k_init_* clear state, bitmaps, rings and outputs (no memset nodes)
 //   k_sort_rec<NT,E>  instances of at most 8192 requests: priority keys (Eq. 1 /
 //                     Eq. 2), stable radix sort in LDS, rank-ordered records,
 //                     index->rank map and cleared outputs, one workgroup per
@@ -135,24 +135,29 @@ __global__ void k_fill_u64(uint64_t* __restrict__ p, int64_t n, uint64_t v) {
 
 // A fresh ring represents the window [1, H] with D = 0: G[slot] = tau.  Each
 // segment's ring has stride H + 64 (slot H is the spare slot).
+__device__ __forceinline__ int32_t first_slot(int32_t s, int32_t H) {
+    return s == 0 ? H : (s < H ? s : 0);
+}
+
 __global__ void k_init_ring(int32_t* __restrict__ ring, int64_t n, int32_t H) {
     const int64_t RS = (int64_t)H + 64;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t s = (int32_t)(i % RS);
-        ring[i] = s == 0 ? H : (s < H ? s : 0);
-    }
+         i += (int64_t)gridDim.x * blockDim.x)
+        ring[i] = first_slot((int32_t)(i % RS), H);
 }
 
-__global__ void k_init_state(SegState* __restrict__ st, int32_t G) {
-    int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= G) return;
+__device__ __forceinline__ SegState first_state() {
     SegState z;
     z.t = 0; z.cursor = 0; z.seq = 0; z.status = STATUS_RUNNING;
     z.nA = 0; z.nfin = 0; z.max_fin = 0; z.head_rank = -1;
     z.t_f = 0; z.N_O = 0; z.C_O = 0; z.peak = 0; z.req_steps = 0; z.ln = 0; z.lq = 0;
     z.resume_lim = 0; z.resume_nev = -1;
-    st[g] = z;
+    return z;
+}
+
+__global__ void k_init_state(SegState* __restrict__ st, int32_t G) {
+    int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g < G) st[g] = first_state();
 }
 
 // ------------------------------------------------------------ keys and sort
@@ -267,7 +272,11 @@ __global__ __launch_bounds__(256) void k_build_rec(SortArgs A) {
 // LDS counter per digit and thread, two to a 32-bit word for the atomic add),
 // an exclusive scan over the counters in digit-major order turns them into
 // start positions, and the elements are scattered through LDS and read back
-// in thread order.  The element array is padded by one entry per 32 so that
+// in thread order.  The workgroup also writes everything else a run starts
+// from: the segment's state, its empty bitmap and ring, the cleared progress
+// counters (a reset is one launch: five small ones cost 15 us of the 25 that
+// resetting 256 instances of 50 requests took).
+// The element array is padded by one entry per 32 so that
 // the thread-strided reads spread over the banks.  Global memory is read and
 // written in batches of 8 elements per thread, so that a thread has 8
 // requests in flight.
@@ -291,6 +300,19 @@ __global__ __launch_bounds__(NT) void k_sort_rec(SortArgs A) {
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
     const int64_t base = (int64_t)pol * A.N + off;
+
+    if (tid == 0) A.st[g] = first_state();
+    {
+        uint64_t* bits = A.bitmap + (int64_t)pol * A.bw_total + A.bw_off[inst];
+        const int words = (int)(A.bw_off[inst + 1] - A.bw_off[inst]);
+        for (int x = tid; x < words; x += NT) bits[x] = 0ull;
+    }
+    if (A.ring != nullptr) {
+        int32_t* ring = A.ring + (int64_t)g * (A.H + 64);
+        for (int x = tid; x < A.H + 64; x += NT) ring[x] = first_slot(x, A.H);
+    }
+    if (g == 0)
+        for (int x = tid; x < 2 * PROG_WORDS; x += NT) A.prog[x] = 0ull;
 
     // keys, read coalesced (element j = (e0 + u) NT + t) and handed over through LDS
     for (int e0 = 0; e0 * NT < n; e0 += B8) {
@@ -402,7 +424,7 @@ __global__ __launch_bounds__(NT) void k_sort_rec(SortArgs A) {
             if (r < n) {
                 A.start[base + r] = -1;
                 A.admit_seq[base + r] = -1;
-                if (stepped) {  // the event path never writes these (cleared at creation)
+                if (stepped || A.clear_all) {  // the event path never writes these (cleared at creation)
                     A.fin[base + r] = -1;
                     A.preempt[base + r] = 0;
                 }
@@ -2303,6 +2325,27 @@ __global__ __launch_bounds__(FIN_NT) void k_finalize(FinArgs F) {
     }
 }
 
+// ------------------------------------------------------------ copy
+
+// Up to four arrays of n words to their destinations in one launch (svf_read
+// into device memory: four copies of 16 MB took 48 us and their gaps).  Words
+// move 16 bytes at a time where source and destination allow it.
+__global__ __launch_bounds__(256) void k_copy4(CopyArgs C) {
+    const int32_t* __restrict__ src = C.src[blockIdx.y];
+    int32_t* __restrict__ dst = C.dst[blockIdx.y];
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    const int64_t x0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    int64_t done = 0;
+    if (((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0) {
+        const int64_t q = C.n >> 2;
+        const int4* s4 = reinterpret_cast<const int4*>(src);
+        int4* d4 = reinterpret_cast<int4*>(dst);
+        for (int64_t x = x0; x < q; x += step) d4[x] = s4[x];
+        done = q << 2;
+    }
+    for (int64_t x = done + x0; x < C.n; x += step) dst[x] = src[x];
+}
+
 // ------------------------------------------------------------ launchers
 
 static inline int grid_for(int64_t n, int bs) {
@@ -2320,6 +2363,13 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
 hipError_t launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(n, 256)), dim3(256), 0, s, p, n, v);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy4(const CopyArgs& C, int arrays, hipStream_t s) {
+    if (arrays <= 0 || C.n <= 0) return hipSuccess;
+    const int64_t blocks = (C.n + 4 * 256 - 1) / (4 * 256);
+    hipLaunchKernelGGL(k_copy4, dim3((unsigned)(blocks > 4096 ? 4096 : blocks), arrays), dim3(256), 0, s, C);
     return hipGetLastError();
 }
 

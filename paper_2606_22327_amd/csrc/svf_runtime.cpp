@@ -66,6 +66,7 @@ struct svf_batch {
     std::vector<int64_t> offsets;
     int32_t H = 1, CH = 64, nchunks = 0, bw_max = 0, max_n = 0;
     bool fused_sort = false;  // every instance fits one workgroup of k_sort_rec
+    bool clear_all = false;   // the reset clears finishes and preemptions of every segment
     bool list_known = false;  // event path: profile as the finish-ordered list
     bool ring_used = true;    // some segment keeps its profile in the ring
     int32_t list_stride = 0;  // list entries per segment in HBM (the bound)
@@ -498,37 +499,44 @@ int do_reset(svf_batch* h) {
     const int64_t PN = (int64_t)h->P * h->N;
     hipEvent_t e0 = nullptr;
     record(h, 0, &e0);
+    svfk::SortArgs A{};
+    A.offsets = h->d_off;
+    A.a = h->d_a; A.s = h->d_s; A.o = h->d_o; A.plan = h->d_plan; A.bit = h->d_bit;
+    A.policies = h->d_pol;
+    A.chunk_seg = h->d_chunk_seg;
+    A.chunk_lo = h->d_chunk_lo;
+    A.rec = h->d_rec;
+    A.rank = h->d_rank;
+    A.I = h->I; A.P = h->P; A.N = h->N; A.O0 = h->O0; A.O1 = h->O1; A.CH = h->CH;
+    for (int p = 0; p < 8; ++p) A.kbits[p] = h->kbits[p];
+    A.start = h->d_start; A.fin = h->d_fin; A.preempt = h->d_pre; A.admit_seq = h->d_seq;
+    A.stepped = h->d_stepped;
+    A.clear_all = h->clear_all;
+    A.st = h->d_st;
+    A.bitmap = h->d_bitmap;
+    A.bw_off = h->d_bw_off;
+    A.bw_total = h->bw_total;
+    A.ring = h->ring_used ? h->d_ring : nullptr;
+    A.H = h->H;
+    A.prog = h->d_prog;
+    if (h->fused_sort) {
+        // keys, sort, records, ranks, cleared outputs and the first state in one kernel
+        HIPCHK(svfk::launch_sort_rec(A, G, h->max_n, h->stream));
+        record_end(h, 0, e0);
+        h->was_reset = true;
+        h->dirty = true;
+        return SVF_OK;
+    }
     HIPCHK(svfk::launch_init_state(h->d_st, G, h->stream));
     HIPCHK(svfk::launch_fill_u64(h->d_bitmap, (int64_t)h->P * h->bw_total, 0ull, h->stream));
+    HIPCHK(svfk::launch_fill_u64(reinterpret_cast<uint64_t*>(h->d_prog), 2 * svfk::PROG_WORDS, 0ull, h->stream));
     if (h->ring_used)
         HIPCHK(svfk::launch_init_ring(h->d_ring, (int64_t)G * (h->H + 64), h->H, h->stream));
-    if (!h->fused_sort) {
-        HIPCHK(svfk::launch_fill_i32(h->d_start, PN, -1, h->stream));
-        HIPCHK(svfk::launch_fill_i32(h->d_fin, PN, -1, h->stream));
-        HIPCHK(svfk::launch_fill_i32(h->d_pre, PN, 0, h->stream));
-        HIPCHK(svfk::launch_fill_i32(h->d_seq, PN, -1, h->stream));
-    }
+    HIPCHK(svfk::launch_fill_i32(h->d_start, PN, -1, h->stream));
+    HIPCHK(svfk::launch_fill_i32(h->d_fin, PN, -1, h->stream));
+    HIPCHK(svfk::launch_fill_i32(h->d_pre, PN, 0, h->stream));
+    HIPCHK(svfk::launch_fill_i32(h->d_seq, PN, -1, h->stream));
     if (PN > 0) {
-        svfk::SortArgs A{};
-        A.offsets = h->d_off;
-        A.a = h->d_a; A.s = h->d_s; A.o = h->d_o; A.plan = h->d_plan; A.bit = h->d_bit;
-        A.policies = h->d_pol;
-        A.chunk_seg = h->d_chunk_seg;
-        A.chunk_lo = h->d_chunk_lo;
-        A.rec = h->d_rec;
-        A.rank = h->d_rank;
-        A.I = h->I; A.P = h->P; A.N = h->N; A.O0 = h->O0; A.O1 = h->O1; A.CH = h->CH;
-        for (int p = 0; p < 8; ++p) A.kbits[p] = h->kbits[p];
-        A.start = h->d_start; A.fin = h->d_fin; A.preempt = h->d_pre; A.admit_seq = h->d_seq;
-        A.stepped = h->d_stepped;
-        if (h->fused_sort) {
-            // keys, sort, records, ranks and cleared outputs in one kernel
-            HIPCHK(svfk::launch_sort_rec(A, G, h->max_n, h->stream));
-            record_end(h, 0, e0);
-            h->was_reset = true;
-            h->dirty = true;
-            return SVF_OK;
-        }
         A.keys_in = nullptr;
         A.keys_out = h->d_keys0;
         HIPCHK(svfk::launch_chunk_sort(A, h->nchunks, h->stream));
@@ -587,7 +595,6 @@ int do_sim(svf_batch* h, int64_t delta) {
     S.list_resume = 0;
     S.resident = h->res_known;
     S.prog = h->d_prog;
-    HIPCHK(svfk::launch_fill_u64(reinterpret_cast<uint64_t*>(h->d_prog), 2 * svfk::PROG_WORDS, 0ull, h->stream));
     hipEvent_t e0 = nullptr;
     record(h, 1, &e0);
     // The two paths simulate disjoint segments (each kernel leaves the other
@@ -669,6 +676,18 @@ int do_finalize(svf_batch* h) {
     record_end(h, 2, e0);
     h->dirty = false;
     return SVF_OK;
+}
+
+// A kernel on ``device`` may store words at p: memory of that device (another
+// device's, or host memory, is left to the runtime's copy), word-aligned.
+bool kernel_writable(const void* p, int device) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == device &&
+           (reinterpret_cast<uintptr_t>(p) & 3) == 0;
 }
 
 // Sequential placement of buffers in a fixed device region (256-byte
@@ -891,14 +910,32 @@ int svf_read(svf_batch* h, int32_t slot, int32_t* start, int32_t* finish, int32_
     RETCHK(do_finalize(h));
     const int64_t base = (int64_t)slot * h->N;
     const size_t bytes = 4 * (size_t)h->N;
-    const hipMemcpyKind k = outputs_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+    const hipMemcpyKind k = hipMemcpyDeviceToHost;
+    if (outputs_on_device) {
+        svfk::CopyArgs C{};
+        C.n = h->N;
+        int arrays = 0;
+        const int32_t* src[4] = {h->d_start, h->d_fin_out, h->d_pre, h->d_seq};
+        int32_t* const dst[4] = {start, finish, preempt, admit_seq};
+        for (int x = 0; x < 4; ++x) {
+            if (!dst[x]) continue;
+            if (kernel_writable(dst[x], h->device)) {
+                C.src[arrays] = src[x] + base;
+                C.dst[arrays++] = dst[x];
+            } else if (bytes) {
+                HIPCHK(hipMemcpyAsync(dst[x], src[x] + base, bytes, hipMemcpyDeviceToDevice, h->stream));
+            }
+        }
+        HIPCHK(svfk::launch_copy4(C, arrays, h->stream));
+        return ok();
+    }
     if (bytes) {
         if (start) HIPCHK(hipMemcpyAsync(start, h->d_start + base, bytes, k, h->stream));
         if (finish) HIPCHK(hipMemcpyAsync(finish, h->d_fin_out + base, bytes, k, h->stream));
         if (preempt) HIPCHK(hipMemcpyAsync(preempt, h->d_pre + base, bytes, k, h->stream));
         if (admit_seq) HIPCHK(hipMemcpyAsync(admit_seq, h->d_seq + base, bytes, k, h->stream));
     }
-    if (!outputs_on_device) HIPCHK(hipStreamSynchronize(h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
     return ok();
 }
 
@@ -1049,16 +1086,14 @@ int svf_run_noalloc(const svf_batch_desc* d, void* hip_stream, int32_t* start, i
     CPY(h.d_stepped, g_na_stepped, G);
     CPY(h.d_bw_off, g_na_bw_off, 8 * (I + 1));
 #undef CPY
-    // finishes and preemption counts start cleared, as at svf_create
-    if (e == hipSuccess) e = svfk::launch_fill_i32(h.d_fin, PN, -1, h.stream);
-    if (e == hipSuccess) e = svfk::launch_fill_i32(h.d_pre, PN, 0, h.stream);
+    h.clear_all = true;  // finishes and preemption counts start cleared, as at svf_create
     if (e == hipSuccess) e = hipStreamSynchronize(h.stream);
     if (e != hipSuccess)
         return fail(SVF_EHIP, "svf_run_noalloc: copying the inputs failed: %s", hipGetErrorString(e));
     HIPCHK(svfk::prepare_sim(h.d_lds, h.lds_bytes, h.list_stepped && !h.step_regs, h.lds_step_full));
     if (h.step_regs) HIPCHK(svfk::prepare_step(h.list_nb, h.lds_step, h.lds_step_full));
     if (h.list_known) HIPCHK(svfk::prepare_list(h.list_nb, h.lds_list, h.lds_list_full));
-    if (h.max_n > 0) HIPCHK(svfk::prepare_sort_rec(h.max_n));
+    HIPCHK(svfk::prepare_sort_rec(h.max_n));
     RETCHK(do_reset(&h));
     RETCHK(do_sim(&h, int64_t(1) << 40));
     RETCHK(do_finalize(&h));
