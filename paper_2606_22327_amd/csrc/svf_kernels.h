@@ -122,7 +122,7 @@ struct SimArgs {
     int32_t list_nb;          // event path: bitmap pairs in registers (0: bitmap in LDS)
     int32_t step_regs;        // per-step path: its running requests in registers (k_sim_step)
     int32_t list_resume;      // 1: only continue the segments that stopped with a full list
-    int32_t resident;         // workgroups of this launch resident at once (0: no issue priorities)
+    int32_t prio;             // 1: the waves set their issue priorities
     unsigned long long* prog; // [PROG_WORDS] progress counters of this launch, zero before it (and after
                               //   it: every wave takes back what it added)
 };
@@ -183,9 +183,6 @@ hipError_t launch_sim(const SimArgs& P, int G, bool d_lds, bool stepped, bool li
                       size_t lds_bytes, hipStream_t s);
 // resident waves per compute unit of the per-step kernel with the list
 hipError_t sim_step_occupancy(size_t lds_bytes, int* blocks);
-// resident waves per compute unit of the first per-step kernel (list: with the
-// list profile), or of the event kernel with the ring
-hipError_t sim_occupancy(bool stepped, bool list, bool d_lds, size_t lds_bytes, int* blocks);
 hipError_t launch_finalize(const FinArgs& F, int G, hipStream_t s);
 // Device address and size of the calling thread's current device's scratch
 // array of the no-allocation entry point (svf_noalloc.hip).

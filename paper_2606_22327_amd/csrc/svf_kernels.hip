@@ -535,7 +535,7 @@ struct IssuePrio {
         next = INT32_MAX;
         ctr = nullptr;
         th = last = 0;
-        if (P.resident <= 0 || n_ <= 0 || P.prog == nullptr || done >= n_) return;
+        if (!P.prio || n_ <= 0 || P.prog == nullptr || done >= n_) return;
         ctr = P.prog + PROG_STRIDE * (blockIdx.x % PROG_LINES);
         n = n_;
         th = max(n / 64, 1);
@@ -2538,16 +2538,6 @@ hipError_t list_occupancy(int nb, size_t lds_bytes, int* blocks) {
     const void* f = (const void*)list_kernel(nb, false);
     hipError_t r = sim_attr(f, lds_bytes);
     if (r != hipSuccess) return r;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, 64, lds_bytes);
-}
-
-hipError_t sim_occupancy(bool stepped, bool list, bool d_lds, size_t lds_bytes, int* blocks) {
-    const void* f;
-    if (list) f = (const void*)k_sim_steplist;
-    else if (stepped) f = d_lds ? (const void*)k_sim<true, true> : (const void*)k_sim<false, true>;
-    else f = d_lds ? (const void*)k_sim<true, false> : (const void*)k_sim<false, false>;
-    hipError_t e = sim_attr(f, lds_bytes);
-    if (e != hipSuccess) return e;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, 64, lds_bytes);
 }
 

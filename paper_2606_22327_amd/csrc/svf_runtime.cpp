@@ -3,11 +3,16 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
+#include <new>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "svf_kernels.h"
@@ -63,10 +68,8 @@ struct svf_batch {
     int64_t N = 0;
     int32_t M = 0, O0 = 0, O1 = 0, max_steps = 0;
     std::vector<int32_t> policies;
-    std::vector<int64_t> offsets;
     int32_t H = 1, CH = 64, nchunks = 0, bw_max = 0, max_n = 0;
     bool fused_sort = false;  // every instance fits one workgroup of k_sort_rec
-    bool clear_all = false;   // the reset clears finishes and preemptions of every segment
     bool list_known = false;  // event path: profile as the finish-ordered list
     bool ring_used = true;    // some segment keeps its profile in the ring
     int32_t list_stride = 0;  // list entries per segment in HBM (the bound)
@@ -81,8 +84,7 @@ struct svf_batch {
     int32_t step_cap = 0;      // its entries in LDS (first launch)
     size_t lds_step = 0;       // LDS of the per-step kernel with the list
     size_t lds_step_full = 0;  //   and with room for the bound (continuation)
-    int32_t res_known = 0;     // workgroups resident at once: first event launch
-    int32_t res_stepped = 0;   //   and first per-step launch (0: no issue priorities)
+    bool prio = false;         // the first launch of each path sets issue priorities
     int32_t kbits[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t bw_total = 0;
     bool d_lds = true;
@@ -95,7 +97,10 @@ struct svf_batch {
     double acc_ms[3] = {0, 0, 0};
     int64_t sim_launches = 0;
 
-    // device buffers
+    // device buffers, all in one allocation
+    void* arena = nullptr;
+    char* pinned = nullptr;   // host staging of large reads (READ_SLOTS * READ_SLOT bytes)
+    int32_t* d_pack = nullptr; // [4*N] outputs of one slot side by side (small batches)
     int64_t* d_off = nullptr;
     int32_t *d_a = nullptr, *d_s = nullptr, *d_o = nullptr, *d_plan = nullptr;
     int8_t* d_bit = nullptr;
@@ -118,32 +123,15 @@ struct svf_batch {
     int32_t* d_lst_f = nullptr;
     uint32_t* d_lst_q = nullptr;
     unsigned long long* d_prog = nullptr;  // [2 * PROG_WORDS] progress counters of the simulation launches
-    const uint64_t* sorted_keys = nullptr;  // which key buffer holds the final order
 };
 
 namespace {
 
-template <typename T>
-int dalloc(T** p, int64_t count) {
-    *p = nullptr;
-    if (count <= 0) return SVF_OK;
-    hipError_t e = hipMalloc((void**)p, sizeof(T) * (size_t)count);
-    if (e != hipSuccess) {
-        *p = nullptr;
-        return fail(SVF_ENOMEM, "hipMalloc of %lld bytes failed: %s",
-                    (long long)(sizeof(T) * count), hipGetErrorString(e));
-    }
-    return SVF_OK;
-}
-
 void free_all(svf_batch* h) {
-    void* ptrs[] = {h->d_off, h->d_a, h->d_s, h->d_o, h->d_plan, h->d_bit, h->d_pol,
-                    h->d_chunk_seg, h->d_chunk_lo, h->d_keys0, h->d_keys1, h->d_rec,
-                    h->d_rank, h->d_stepped, h->d_bw_off, h->d_bitmap, h->d_ring,
-                    h->d_start, h->d_fin, h->d_pre, h->d_seq, h->d_act, h->d_actkr, h->d_evl,
-                    h->d_st, h->d_fin_out, h->d_stats, h->d_lst_f, h->d_lst_q, h->d_prog};
-    for (void* p : ptrs)
-        if (p) (void)hipFree(p);
+    if (h->arena) (void)hipFree(h->arena);
+    if (h->pinned) (void)hipHostFree(h->pinned);
+    h->arena = nullptr;
+    h->pinned = nullptr;
     for (auto& t : h->timed) {
         (void)hipEventDestroy(t.a);
         (void)hipEventDestroy(t.b);
@@ -174,41 +162,240 @@ struct HostView {
     const int8_t* bit;
 };
 
-// Largest number of requests of one instance that can run at the same time.
-// A running request holds at least s + 1 tokens at the next step, and the
-// planned (and true) total of that step stays <= M once a step's admissions
-// are done, so at most the k smallest values of s + 1 fit.  Values at or
-// above kCap count as kCap (a lower bound on each), which keeps k an upper
-// bound.  The largest s goes to max_s.
-int64_t running_bound(const int32_t* s, const int64_t* off, int32_t I, int64_t M, int32_t* max_s) {
-    constexpr int kCap = 4096;
-    int64_t h[kCap + 1];
-    int64_t best = 0;
-    int32_t top = 1;
-    for (int32_t i = 0; i < I; ++i) {
-        std::fill(h, h + kCap + 1, 0);
-        for (int64_t j = off[i]; j < off[i + 1]; ++j) {
-            h[std::min<int64_t>((int64_t)s[j] + 1, kCap)] += 1;
-            top = std::max(top, s[j]);
-        }
-        int64_t sum = 0, k = 0;
-        for (int v = 1; v <= kCap; ++v) {
-            if (!h[v]) continue;
-            const int64_t take = std::min<int64_t>(h[v], (M - sum) / v);
-            k += take;
-            sum += take * v;
-            if (take < h[v]) break;
-        }
-        best = std::max(best, k);
-    }
-    *max_s = top;
-    return best;
+// Host threads for work on n items (1: in the calling thread only).
+int threads_for(int64_t n) {
+    if (n < (int64_t(1) << 20)) return 1;
+    return (int)std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
 }
 
-// Everything that can be checked without a GPU.  Writes each segment's path
-// (1: per-step) to stepped[P*I] and each policy's largest key to max_key[P].
+// f(0) .. f(count - 1), each on a thread of its own while threads can be had.
+template <typename F>
+void on_threads(int count, F f) {
+    std::vector<std::thread> pool;
+    int k = 1;
+    try {
+        pool.reserve((size_t)std::max(count, 1));
+        for (; k < count; ++k) pool.emplace_back(f, k);
+    } catch (const std::exception&) {
+        // no further thread: the rest runs here
+    }
+    f(0);
+    for (; k < count; ++k) f(k);
+    for (std::thread& t : pool) t.join();
+}
+
+// What the launch plan needs to know of the requests.
+struct Facts {
+    int64_t max_plan = 1;     // longest planned length
+    int64_t max_profile = 0;  // largest planned memory total at one future step
+    uint64_t max_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // each policy's largest key
+    int64_t bound = 0;        // most requests of one instance that can run at once
+    int64_t sum_s = 0, sum_o = 0;
+    int32_t max_s = 1;
+    int32_t bad = INT32_MAX;  // first instance with an error
+};
+
+// Facts of one instance's requests under one source of planned lengths.
+struct Lengths {
+    bool differ = false;  // some planned length is not the true one
+    int32_t longest = 0;
+    int64_t sum = 0;
+    uint64_t volume = 0;
+};
+
+// One instance in straight passes the compiler turns into vector code; true if
+// anything is wrong with it.  volumes: whether the volumes are needed as keys.
+__attribute__((always_inline)) inline bool scan_core(
+    const int32_t* a, const int32_t* s, const int32_t* o, const int32_t* plan, const int8_t* bit,
+    int64_t n, const int32_t O[2], uint32_t M, bool use_plan, bool use_bit, bool volumes, Facts& F,
+    Lengths L[2]) {
+    uint32_t bad = 0;
+    for (int64_t j = 0; j < n; ++j) bad |= (uint32_t)a[j] >> 30;
+    for (int64_t j = 1; j < n; ++j) bad |= (uint32_t)(a[j] < a[j - 1]);
+    int64_t sum_s = 0, sum_o = 0;
+    int32_t max_s = 1;
+    for (int64_t j = 0; j < n; ++j) {
+        bad |= (uint32_t)(s[j] < 1) | (uint32_t)(o[j] < 1);
+        sum_s += s[j];
+        sum_o += o[j];
+        max_s = std::max(max_s, s[j]);
+    }
+    F.sum_s += sum_s;
+    F.sum_o += sum_o;
+    F.max_s = std::max(F.max_s, max_s);
+    if (plan)
+        for (int64_t j = 0; j < n; ++j) bad |= (uint32_t)(plan[j] < 1);
+    if (bit)
+        for (int64_t j = 0; j < n; ++j) bad |= (uint32_t)bit[j] & ~1u;
+    auto lengths = [&](auto of, Lengths& out) {
+        uint32_t differ = 0;
+        int32_t longest = 0;
+        int64_t sum = 0;
+        for (int64_t j = 0; j < n; ++j) {
+            const int32_t l = of(j);
+            differ |= (uint32_t)(l ^ o[j]);
+            longest = std::max(longest, l);
+            sum += l;
+            // (values below 1 are errors already: no wrap among the others)
+            bad |= (uint32_t)((uint32_t)s[j] + (uint32_t)std::max(o[j], l) > M);
+        }
+        if (volumes) {
+            uint64_t most = 0;
+            for (int64_t j = 0; j < n; ++j) {
+                const uint64_t l = (uint32_t)of(j);
+                most = std::max(most, (uint64_t)(uint32_t)s[j] * l + ((l * l + l) >> 1));
+            }
+            out.volume = most;
+        }
+        out.differ = differ != 0;
+        out.longest = longest;
+        out.sum = sum;
+    };
+    if (use_plan) {
+        if (plan) lengths([&](int64_t j) { return plan[j]; }, L[0]);
+        else lengths([&](int64_t j) { return o[j]; }, L[0]);
+    }
+    if (use_bit && bit) lengths([&](int64_t j) { return bit[j] ? O[1] : O[0]; }, L[1]);
+    return bad != 0;
+}
+
+typedef bool (*ScanFn)(const int32_t*, const int32_t*, const int32_t*, const int32_t*, const int8_t*,
+                       int64_t, const int32_t*, uint32_t, bool, bool, bool, Facts&, Lengths*);
+bool scan_any(const int32_t* a, const int32_t* s, const int32_t* o, const int32_t* plan,
+              const int8_t* bit, int64_t n, const int32_t* O, uint32_t M, bool up, bool ub, bool vol,
+              Facts& F, Lengths* L) {
+    return scan_core(a, s, o, plan, bit, n, O, M, up, ub, vol, F, L);
+}
+__attribute__((target("avx2"))) bool scan_avx2(const int32_t* a, const int32_t* s, const int32_t* o,
+                                               const int32_t* plan, const int8_t* bit, int64_t n,
+                                               const int32_t* O, uint32_t M, bool up, bool ub,
+                                               bool vol, Facts& F, Lengths* L) {
+    return scan_core(a, s, o, plan, bit, n, O, M, up, ub, vol, F, L);
+}
+
+// Largest number of requests of one instance that can run at the same time, if
+// it is above ``best``.  A running request holds at least s + 1 tokens at the
+// next step, and the planned (and true) total of that step stays <= M once a
+// step's admissions are done, so at most the k smallest values of s + 1 fit.
+// Values at or above kCap count as kCap (a lower bound on each), which keeps k
+// an upper bound.  h: counts per value, all zero before and after.
+constexpr int kCap = 4096;
+int64_t running_bound(const int32_t* s, int64_t n, int64_t sum_s, int64_t M, int64_t best, int32_t* h) {
+    if (n <= best) return best;
+    if (sum_s + n <= M) return n;
+    auto value = [&](int64_t j) { return (int)std::min<int64_t>((int64_t)s[j] + 1, kCap); };
+    for (int64_t j = 0; j < n; ++j) h[value(j)] += 1;
+    int64_t sum = 0, k = 0;
+    for (int v = 1; v <= kCap; ++v) {
+        if (!h[v]) continue;
+        const int64_t take = std::min<int64_t>(h[v], (M - sum) / v);
+        k += take;
+        sum += take * v;
+        if (take < h[v]) break;
+    }
+    if (n < kCap / 4) for (int64_t j = 0; j < n; ++j) h[value(j)] = 0;
+    else std::fill(h, h + kCap + 1, 0);
+    return std::max(best, k);
+}
+
+// The instances [lo, hi): their facts into F (up to the first with an error),
+// each segment's path (1: per-step) to stepped[P*I].
+void scan(const svf_batch_desc* d, const HostView& v, const int64_t* off, int32_t lo, int32_t hi,
+          uint8_t* stepped, Facts& F) {
+    const int32_t I = d->num_instances, P = d->num_policies;
+    bool use_plan = false, use_bit = false, volumes = false;
+    for (int p = 0; p < P; ++p) {
+        const int pol = d->policies[p] & 0xFF;
+        (pol == SVF_POLICY_SVF1BIT ? use_bit : use_plan) = true;
+        volumes |= pol == SVF_POLICY_SVF || pol == SVF_POLICY_SVF1BIT;
+    }
+    const int32_t O[2] = {d->O0, d->O1};
+    const ScanFn fn = __builtin_cpu_supports("avx2") ? &scan_avx2 : &scan_any;
+    int32_t h[kCap + 1];
+    std::fill(h, h + kCap + 1, 0);
+    F.max_profile = d->M;
+    for (int32_t i = lo; i < hi; ++i) {
+        const int64_t x = off[i], n = off[i + 1] - x;
+        if (n == 0) {
+            for (int p = 0; p < P; ++p) stepped[(size_t)p * I + i] = 0;
+            continue;
+        }
+        Lengths L[2];
+        const int64_t before = F.sum_s;
+        bool bad = fn(v.a + x, v.s + x, v.o + x, v.plan ? v.plan + x : nullptr,
+                      v.bit ? v.bit + x : nullptr, n, O, (uint32_t)d->M, use_plan, use_bit, volumes, F, L);
+        const int64_t sum_s = F.sum_s - before;
+        for (int p = 0; p < P; ++p) {
+            const int pol = d->policies[p] & 0xFF;
+            const bool current_rule = (d->policies[p] & SVF_ADMIT_CURRENT) != 0;
+            const Lengths& l = L[pol == SVF_POLICY_SVF1BIT];
+            uint64_t key;
+            if (pol == SVF_POLICY_FCFS) key = (uint64_t)(uint32_t)v.a[x + n - 1];
+            else if (pol == SVF_POLICY_SJF) key = (uint64_t)(uint32_t)l.longest;
+            else key = l.volume;
+            bad |= key >= (uint64_t(1) << 32);
+            F.max_key[p] = std::max(F.max_key[p], key);
+            // eviction is only possible when plans differ from the truth
+            // or when admission looks at the next step only
+            stepped[(size_t)p * I + i] = l.differ || current_rule;
+            F.max_plan = std::max<int64_t>(F.max_plan, l.longest);
+            // The forward-looking check keeps a step's planned total <= M;
+            // with next-step admission only, the requests of an instance
+            // bound it together: sum of s + o^.
+            if (current_rule) F.max_profile = std::max(F.max_profile, sum_s + l.sum);
+        }
+        if (bad) {
+            F.bad = i;
+            return;
+        }
+        F.bound = running_bound(v.s + x, n, sum_s, d->M, F.bound, h);
+    }
+}
+
+// The first error among the requests of instance i, as a message.
+int first_error(const svf_batch_desc* d, const HostView& v, const int64_t* off, int32_t i) {
+    const int32_t P = d->num_policies;
+    const int64_t lo = off[i], hi = off[i + 1];
+    for (int64_t j = lo; j < hi; ++j) {
+        const int32_t a = v.a[j], s = v.s[j], o = v.o[j];
+        if (a < 0 || a >= kLimit30)
+            return fail(SVF_EINVAL, "instance %d request %lld: arrival %d out of [0, 2^30)", i,
+                        (long long)(j - lo), a);
+        if (j > lo && a < v.a[j - 1])
+            return fail(SVF_EINVAL, "instance %d: arrivals not in order at request %lld", i,
+                        (long long)(j - lo));
+        if (s < 1) return fail(SVF_EINVAL, "instance %d request %lld: prompt %d < 1", i, (long long)(j - lo), s);
+        if (o < 1) return fail(SVF_EINVAL, "instance %d request %lld: output %d < 1", i, (long long)(j - lo), o);
+        if (v.plan && v.plan[j] < 1)
+            return fail(SVF_EINVAL, "instance %d request %lld: plan_len %d < 1", i, (long long)(j - lo), v.plan[j]);
+        if (v.bit && v.bit[j] != 0 && v.bit[j] != 1)
+            return fail(SVF_EINVAL, "instance %d request %lld: long_bit %d not 0/1", i, (long long)(j - lo), v.bit[j]);
+        for (int p = 0; p < P; ++p) {
+            const int pol = d->policies[p] & 0xFF;
+            int64_t oh;
+            if (pol == SVF_POLICY_SVF1BIT) oh = v.bit[j] ? d->O1 : d->O0;
+            else oh = v.plan ? v.plan[j] : o;
+            if ((int64_t)s + std::max<int64_t>(o, oh) > d->M)
+                return fail(SVF_EINFEASIBLE,
+                            "instance %d request %lld: s + max(o, planned) = %lld exceeds M = %lld",
+                            i, (long long)(j - lo), (long long)s + std::max<int64_t>(o, oh),
+                            (long long)d->M);
+            uint64_t key;
+            if (pol == SVF_POLICY_FCFS) key = (uint64_t)a;
+            else if (pol == SVF_POLICY_SJF) key = (uint64_t)oh;
+            else key = (uint64_t)s * (uint64_t)oh + (((uint64_t)oh * oh + oh) >> 1);
+            if (key >= (uint64_t(1) << 32))
+                return fail(SVF_EINVAL, "instance %d request %lld: priority key %llu >= 2^32", i,
+                            (long long)(j - lo), (unsigned long long)key);
+        }
+    }
+    return fail(SVF_EINVAL, "instance %d: malformed requests", i);
+}
+
+// Everything that can be checked without a GPU, and the facts for the launch
+// plan, on ``threads`` host threads (1: none is started, nothing is allocated).
 int validate(const svf_batch_desc* d, const HostView& v, const int64_t* off, int64_t N,
-             uint8_t* stepped, int64_t* max_plan, int64_t* max_profile, uint64_t* max_key) {
+             uint8_t* stepped, int threads, Facts* facts) {
     const int32_t I = d->num_instances, P = d->num_policies;
     bool has1bit = false;
     for (int p = 0; p < P; ++p) has1bit |= (d->policies[p] & 0xFF) == SVF_POLICY_SVF1BIT;
@@ -216,60 +403,33 @@ int validate(const svf_batch_desc* d, const HostView& v, const int64_t* off, int
         return fail(SVF_EINVAL, "arrival, prompt and output must not be NULL");
     if (has1bit && N > 0 && !v.bit) return fail(SVF_EINVAL, "SVF1BIT needs long_bit");
     if (has1bit && (d->O0 < 1 || d->O1 < 1)) return fail(SVF_EINVAL, "SVF1BIT needs O0, O1 >= 1");
-    *max_plan = 1;
-    // Largest planned memory total at one future step.  The forward-looking
-    // check keeps it <= M; with next-step admission only, the requests of an
-    // instance bound it together: sum of s + o^.
-    *max_profile = d->M;
-    std::fill(stepped, stepped + (size_t)P * I, 0);
-    std::fill(max_key, max_key + P, 0);
-    int64_t cur_total[8];
-    for (int32_t i = 0; i < I; ++i) {
-        const int64_t lo = off[i], hi = off[i + 1];
-        std::fill(cur_total, cur_total + P, 0);
-        for (int64_t j = lo; j < hi; ++j) {
-            const int32_t a = v.a[j], s = v.s[j], o = v.o[j];
-            if (a < 0 || a >= kLimit30)
-                return fail(SVF_EINVAL, "instance %d request %lld: arrival %d out of [0, 2^30)", i,
-                            (long long)(j - lo), a);
-            if (j > lo && a < v.a[j - 1])
-                return fail(SVF_EINVAL, "instance %d: arrivals not in order at request %lld", i,
-                            (long long)(j - lo));
-            if (s < 1) return fail(SVF_EINVAL, "instance %d request %lld: prompt %d < 1", i, (long long)(j - lo), s);
-            if (o < 1) return fail(SVF_EINVAL, "instance %d request %lld: output %d < 1", i, (long long)(j - lo), o);
-            if (v.plan && v.plan[j] < 1)
-                return fail(SVF_EINVAL, "instance %d request %lld: plan_len %d < 1", i, (long long)(j - lo), v.plan[j]);
-            if (v.bit && v.bit[j] != 0 && v.bit[j] != 1)
-                return fail(SVF_EINVAL, "instance %d request %lld: long_bit %d not 0/1", i, (long long)(j - lo), v.bit[j]);
-            for (int p = 0; p < P; ++p) {
-                const int pol = d->policies[p] & 0xFF;
-                const bool current_rule = (d->policies[p] & SVF_ADMIT_CURRENT) != 0;
-                int64_t oh;
-                if (pol == SVF_POLICY_SVF1BIT) oh = v.bit[j] ? d->O1 : d->O0;
-                else oh = v.plan ? v.plan[j] : o;
-                if ((int64_t)s + std::max<int64_t>(o, oh) > d->M)
-                    return fail(SVF_EINFEASIBLE,
-                                "instance %d request %lld: s + max(o, planned) = %lld exceeds M = %lld",
-                                i, (long long)(j - lo), (long long)s + std::max<int64_t>(o, oh),
-                                (long long)d->M);
-                uint64_t key;
-                if (pol == SVF_POLICY_FCFS) key = (uint64_t)a;
-                else if (pol == SVF_POLICY_SJF) key = (uint64_t)oh;
-                else key = (uint64_t)s * (uint64_t)oh + (((uint64_t)oh * oh + oh) >> 1);
-                if (key >= (uint64_t(1) << 32))
-                    return fail(SVF_EINVAL, "instance %d request %lld: priority key %llu >= 2^32", i,
-                                (long long)(j - lo), (unsigned long long)key);
-                max_key[p] = std::max(max_key[p], key);
-                // eviction is only possible when plans differ from the truth
-                // or when admission looks at the next step only
-                if (oh != o || current_rule) stepped[(size_t)p * I + i] = 1;
-                *max_plan = std::max(*max_plan, oh);
-                if (current_rule) cur_total[p] += s + oh;
-            }
-        }
-        for (int p = 0; p < P; ++p) *max_profile = std::max(*max_profile, cur_total[p]);
+    Facts part[8];
+    threads = std::max(1, std::min({threads, 8, (int)std::max(I, 1)}));
+    auto work = [&](int k) {
+        // the instances whose first request is in the k-th share of all requests
+        auto cut = [&](int x) {
+            if (x == 0) return (int32_t)0;
+            if (x == threads) return I;
+            return (int32_t)(std::lower_bound(off, off + I, N * x / threads) - off);
+        };
+        scan(d, v, off, cut(k), cut(k + 1), stepped, part[k]);
+    };
+    if (threads == 1) work(0);
+    else on_threads(threads, work);
+    Facts& F = *facts;
+    F = part[0];
+    for (int k = 1; k < threads; ++k) {
+        const Facts& x = part[k];
+        F.max_plan = std::max(F.max_plan, x.max_plan);
+        F.max_profile = std::max(F.max_profile, x.max_profile);
+        for (int p = 0; p < 8; ++p) F.max_key[p] = std::max(F.max_key[p], x.max_key[p]);
+        F.bound = std::max(F.bound, x.bound);
+        F.sum_s += x.sum_s;
+        F.sum_o += x.sum_o;
+        F.max_s = std::max(F.max_s, x.max_s);
+        F.bad = std::min(F.bad, x.bad);
     }
-    return SVF_OK;
+    return F.bad == INT32_MAX ? SVF_OK : first_error(d, v, off, F.bad);
 }
 
 int check_desc_shape(const svf_batch_desc* d, int64_t* N) {
@@ -302,25 +462,49 @@ int check_desc_shape(const svf_batch_desc* d, int64_t* N) {
     return SVF_OK;
 }
 
+// Largest LDS of a workgroup at which the kernel keeps the waves that its
+// registers allow (those it reaches with ``least`` bytes).  For the kernels
+// that keep the bitmap in registers (nb > 0) that is a constant of the kernel,
+// found once.  0 without a GPU.
+template <typename Occ>
+size_t full_occupancy_lds(int kind, int nb, size_t least, Occ occ) {
+    static std::atomic<size_t> known[2][3];
+    const bool keep = kind < 2 && nb > 0;
+    if (keep) {
+        const size_t b = known[kind][nb].load(std::memory_order_relaxed);
+        if (b) return b;
+    }
+    const int top = occ(least);
+    if (top <= 0) return 0;
+    size_t lo = least, hi = std::max<size_t>(least, 160 * 1024);
+    while (hi - lo > 64) {
+        const size_t mid = (lo + (hi - lo) / 2) & ~size_t(7);
+        if (occ(mid) >= top) lo = mid;
+        else hi = mid;
+    }
+    if (keep) known[kind][nb].store(lo, std::memory_order_relaxed);
+    return lo;
+}
+
 // The launch plan of a validated batch: sizes, sort shape, profile kind
 // (ring or finish-ordered list) and its LDS capacity per path, issue
 // priorities.  Fills the host fields of ``h`` (not its buffers) and the
 // bitmap word offsets bw_off[I+1].
-int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const int64_t* off,
-               const uint8_t* stepped, int64_t max_plan, int64_t max_profile,
-               const uint64_t* max_key, int64_t* bw_off) {
+int plan_batch(svf_batch* h, const svf_batch_desc* d, const int64_t* off,
+               const uint8_t* stepped, const Facts& F, int64_t* bw_off) {
     const int32_t I = d->num_instances, P = d->num_policies;
     const int64_t N = off[I];
     h->I = I; h->P = P; h->N = N;
     h->M = (int32_t)d->M;
     h->O0 = d->O0; h->O1 = d->O1;
     h->max_steps = (int32_t)d->max_steps;
+    const int64_t max_plan = F.max_plan, max_profile = F.max_profile;
     h->H = (int32_t)next_pow2(std::max<int64_t>(max_plan, 1));
     for (int32_t i = 0; i < I; ++i) h->max_n = std::max<int32_t>(h->max_n, (int32_t)(off[i + 1] - off[i]));
     h->CH = (int32_t)std::min<int64_t>(8192, std::max<int64_t>(64, next_pow2(h->max_n)));
     h->fused_sort = h->max_n <= svfk::SORT_REC_MAX;
     for (int32_t p = 0; p < P; ++p)
-        h->kbits[p] = max_key[p] ? 64 - __builtin_clzll(max_key[p]) : 0;
+        h->kbits[p] = F.max_key[p] ? 64 - __builtin_clzll(F.max_key[p]) : 0;
     for (int64_t g = 0; g < (int64_t)P * I; ++g) {
         h->any_stepped |= stepped[g] != 0;
         (stepped[g] ? h->n_stepped : h->n_known) += 1;
@@ -362,9 +546,7 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
     // registers allow; segments that outgrow it stop, and a second launch with
     // room for the bound on concurrent requests (and for finished entries not
     // yet removed) continues them.
-    int32_t max_s = 1;
-    const int64_t bound = (h->n_known > 0 || h->any_stepped)
-                              ? std::max<int64_t>(1, running_bound(v.s, off, I, d->M, &max_s)) : 1;
+    const int64_t bound = std::max<int64_t>(1, F.bound);
     const size_t full_bytes = bm_bytes + (size_t)svfk::list_slots((int)std::min<int64_t>(bound, 1 << 24)) * 8;
     h->list_nb = svfk::list_bitmap_pairs(h->max_n);
     const size_t lds_bm = h->list_nb == 0 ? bm_bytes : 0;  // of the kernels that may keep the bitmap in registers
@@ -376,27 +558,17 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
         int64_t cap = h->list_full;
         const bool fits = h->lds_list_full <= 160 * 1024;
         if (fits) {
-            auto occ = [&](int64_t c) {
+            auto occ = [&](size_t bytes) {
                 int w = 0;
-                return svfk::list_occupancy(h->list_nb, lds_bm + svfk::list_lds(c), &w) == hipSuccess ? w : -1;
+                return svfk::list_occupancy(h->list_nb, bytes, &w) == hipSuccess ? w : -1;
             };
-            const int w_top = occ(64);
-            int64_t lo = std::min<int64_t>(cap, 64), hi = cap;  // occ(lo) >= w_top
-            while (lo < hi) {
-                const int64_t mid = lo + (hi - lo + 1) / 2;
-                if (occ(mid) >= w_top) lo = mid;
-                else hi = mid - 1;
-            }
-            cap = lo;
+            const size_t most = full_occupancy_lds(0, h->list_nb, lds_bm + svfk::list_lds(64), occ);
+            cap = std::min<int64_t>(cap, std::max<int64_t>(64, (int64_t)((most - std::min(most, lds_bm)) / 8)));
             const char* pc = getenv("SVFSIM_LIST_LDS_CAP");  // testing: a smaller list
             if (pc && atoll(pc) > 0) cap = std::min<int64_t>(cap, atoll(pc));
-            double sum_s = 0.0, sum_o = 0.0;
-            for (int64_t x = 0; x < N; ++x) {
-                sum_s += v.s[x];
-                sum_o += v.o[x];
-            }
-            const double running = N > 0 ? (double)d->M / ((sum_s + 0.5 * sum_o) / (double)N) : 0.0;
-            if (w_top > 0) use = !h->d_lds || running <= 512.0;
+            const double running =
+                N > 0 ? (double)d->M / (((double)F.sum_s + 0.5 * (double)F.sum_o) / (double)N) : 0.0;
+            if (most > 0) use = !h->d_lds || running <= 512.0;
         }
         if (pe && !strcmp(pe, "ring")) use = false;
         if (pe && !strcmp(pe, "list")) use = fits;
@@ -420,25 +592,24 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
             // its running requests in registers, within that kernel's limits
             const uint64_t L = (uint64_t)max_plan;  // (no volume is larger than this one)
             h->step_regs = svfk::step_regs_ok(bound, h->max_n, d->M,
-                                              (uint64_t)max_s * L + ((L * L + L) >> 1));
+                                              (uint64_t)F.max_s * L + ((L * L + L) >> 1));
             h->step_full = (int32_t)(bound + (h->step_regs ? svfk::LIST_DEAD_MAX : 0));
             auto bytes = [&](int64_t c) {
                 return h->step_regs ? lds_bm + svfk::list_lds(c)
                                     : bm_bytes + (size_t)svfk::list_slots((int)c) * 8;
             };
-            auto occ = [&](int64_t c) {
+            auto occ = [&](size_t b) {
                 int w = 0;
-                return (h->step_regs ? svfk::step_occupancy(h->list_nb, bytes(c), &w)
-                                     : svfk::sim_step_occupancy(bytes(c), &w)) == hipSuccess ? w : -1;
+                return (h->step_regs ? svfk::step_occupancy(h->list_nb, b, &w)
+                                     : svfk::sim_step_occupancy(b, &w)) == hipSuccess ? w : -1;
             };
-            const int w_top = occ(64);
-            int64_t lo = std::min<int64_t>(h->step_full, 64), hi = h->step_full;
-            while (w_top > 0 && lo < hi) {
-                const int64_t mid = lo + (hi - lo + 1) / 2;
-                if (occ(mid) >= w_top) lo = mid;
-                else hi = mid - 1;
+            const size_t most = full_occupancy_lds(h->step_regs ? 1 : 2, h->step_regs ? h->list_nb : 0,
+                                                   bytes(64), occ);
+            int64_t cap = h->step_full;
+            if (most > 0) {
+                const size_t front = h->step_regs ? lds_bm : bm_bytes + (size_t)svfk::list_slots(0) * 8;
+                cap = std::min<int64_t>(cap, std::max<int64_t>(64, (int64_t)((most - std::min(most, front)) / 8)));
             }
-            int64_t cap = w_top > 0 ? lo : h->step_full;
             const char* pc = getenv("SVFSIM_STEP_LDS_CAP");  // testing: a smaller list
             if (pc && atoll(pc) > 0) cap = std::min<int64_t>(cap, atoll(pc));
             h->list_stepped = true;
@@ -449,28 +620,15 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const HostView& v, const i
     }
     if (h->list_known || h->list_stepped) h->list_stride = (int32_t)bound;
     h->ring_used = (h->n_known > 0 && !h->list_known) || (h->any_stepped && !h->list_stepped);
-    // Resident workgroups of the first simulation launch of each path; the
-    // waves set their issue priorities only when it is known (timing only).
+    // The waves of the first simulation launch of each path set their issue
+    // priorities (timing only).
     // With at most one segment per SIMD (four per CU) there is nothing to arbitrate.
     {
         int ncu = 0;
         const char* pp = getenv("SVFSIM_ISSUE_PRIO");  // "0": all waves at one priority
         const bool on = !(pp && !strcmp(pp, "0"));
-        if (on && hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess &&
-            ncu > 0 && (int64_t)P * I > 4 * (int64_t)ncu) {
-            int w = 0;
-            if (h->n_known > 0 &&
-                (h->list_known ? svfk::list_occupancy(h->list_nb, h->lds_list, &w)
-                               : svfk::sim_occupancy(false, false, h->d_lds, h->lds_bytes, &w)) == hipSuccess)
-                h->res_known = w * ncu;
-            w = 0;
-            if (h->any_stepped &&
-                (h->step_regs ? svfk::step_occupancy(h->list_nb, h->lds_step, &w)
-                              : svfk::sim_occupancy(true, h->list_stepped, h->d_lds,
-                                                    h->list_stepped ? h->lds_step : h->lds_bytes,
-                                                    &w)) == hipSuccess)
-                h->res_stepped = w * ncu;
-        }
+        h->prio = on && hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess &&
+                  ncu > 0 && (int64_t)P * I > 4 * (int64_t)ncu;
         (void)hipGetLastError();
     }
     if (h->lds_bytes > 160 * 1024)
@@ -511,7 +669,9 @@ int do_reset(svf_batch* h) {
     for (int p = 0; p < 8; ++p) A.kbits[p] = h->kbits[p];
     A.start = h->d_start; A.fin = h->d_fin; A.preempt = h->d_pre; A.admit_seq = h->d_seq;
     A.stepped = h->d_stepped;
-    A.clear_all = h->clear_all;
+    // finishes and preemption counts of event-path segments are never written:
+    // cleared once
+    A.clear_all = !h->was_reset;
     A.st = h->d_st;
     A.bitmap = h->d_bitmap;
     A.bw_off = h->d_bw_off;
@@ -593,7 +753,7 @@ int do_sim(svf_batch* h, int64_t delta) {
     S.list_nb = h->list_nb;
     S.step_regs = h->step_regs;
     S.list_resume = 0;
-    S.resident = h->res_known;
+    S.prio = h->prio;
     S.prog = h->d_prog;
     hipEvent_t e0 = nullptr;
     record(h, 1, &e0);
@@ -618,7 +778,6 @@ int do_sim(svf_batch* h, int64_t delta) {
         svfk::SimArgs T = S;
         T.list_cap = h->step_cap;
         T.list_resume = 0;
-        T.resident = h->res_stepped;
         T.prog = h->d_prog + svfk::PROG_WORDS;
         le = svfk::launch_sim(T, G, h->d_lds, true, h->list_stepped,
                               h->list_stepped ? h->lds_step : h->lds_bytes, st_stepped);
@@ -628,7 +787,7 @@ int do_sim(svf_batch* h, int64_t delta) {
             // requests the registers), up to the same step
             T.list_cap = h->step_full;
             T.list_resume = 1;
-            T.resident = 0;
+            T.prio = 0;
             le = svfk::launch_sim(T, G, false, true, true, h->lds_step_full, st_stepped);
         }
     }
@@ -639,7 +798,7 @@ int do_sim(svf_batch* h, int64_t delta) {
             // segments whose list outgrew the LDS capacity, up to the same step
             S.list_cap = h->list_full;
             S.list_resume = 1;
-            S.resident = 0;
+            S.prio = 0;
             le = svfk::launch_sim(S, G, false, false, true, h->lds_list_full, st_known);
         }
     }
@@ -693,7 +852,7 @@ bool kernel_writable(const void* p, int device) {
 // Sequential placement of buffers in a fixed device region (256-byte
 // aligned); ``used`` may exceed the region, and is checked before any use.
 struct Carve {
-    char* base;
+    uintptr_t base;  // 0: only the size is wanted
     size_t used;
     template <typename T>
     T* take(int64_t count) {
@@ -706,10 +865,214 @@ struct Carve {
 };
 
 // Host tables of svf_run_noalloc (per-segment path flags, bitmap word
-// offsets), static so that the call allocates nothing; guarded by g_na_mu.
+// offsets, small inputs on their way up), static so that the call allocates nothing; guarded by g_na_mu.
 std::mutex g_na_mu;
 uint8_t g_na_stepped[(size_t)SVF_NOALLOC_MAX_INSTANCES * 8];
 int64_t g_na_bw_off[SVF_NOALLOC_MAX_INSTANCES + 1];
+char g_na_stage[256 << 10];
+
+struct Destroy {
+    void operator()(svf_batch* h) const {
+        free_all(h);
+        delete h;
+    }
+};
+
+// Reads of at least READ_LARGE bytes go through pinned staging, READ_SLOTS
+// slots of READ_SLOT bytes, a host thread per slot: the copies out of the GPU
+// run at the link's rate beside the stores into the caller's pages (which are
+// often touched there for the first time).  Measured, 82 MB into fresh pages:
+// 8.7 ms by four pageable copies.
+constexpr int READ_SLOTS = 8;
+constexpr size_t READ_SLOT = size_t(2) << 20, READ_LARGE = size_t(8) << 20;
+// Batches whose outputs of one slot take at most this are read in one copy.
+constexpr size_t READ_SMALL = size_t(256) << 10;
+// Host inputs and tables up to this size go up in one copy.
+constexpr size_t STAGE_MAX = size_t(1) << 20;
+
+int create(const svf_batch_desc* d, void* hip_stream, svf_batch** out) {
+    int64_t N = 0;
+    RETCHK(check_desc_shape(d, &N));
+    const int32_t I = d->num_instances, P = d->num_policies;
+    const int64_t* off = d->req_offsets;
+    const int64_t G = (int64_t)P * I;
+    const int64_t PN = (int64_t)P * N;
+
+    // host view of the per-request arrays (device inputs are fetched first)
+    std::unique_ptr<int32_t[]> ha, hs, ho, hp;
+    std::unique_ptr<int8_t[]> hb;
+    HostView v{d->arrival, d->prompt, d->output, d->plan_len, d->long_bit};
+    if (d->inputs_on_device && N > 0) {
+        if (!d->arrival || !d->prompt || !d->output)
+            return fail(SVF_EINVAL, "arrival, prompt and output must not be NULL");
+        auto fetch = [&](auto& buf, const auto* src) {
+            typedef typename std::remove_const<typename std::remove_reference<decltype(*src)>::type>::type T;
+            buf.reset(new T[(size_t)N]);
+            return hipMemcpy(buf.get(), src, sizeof(T) * (size_t)N, hipMemcpyDeviceToHost);
+        };
+        HIPCHK(fetch(ha, d->arrival));
+        HIPCHK(fetch(hs, d->prompt));
+        HIPCHK(fetch(ho, d->output));
+        if (d->plan_len) HIPCHK(fetch(hp, d->plan_len));
+        if (d->long_bit) HIPCHK(fetch(hb, d->long_bit));
+        v = HostView{ha.get(), hs.get(), ho.get(), hp.get(), hb.get()};
+    }
+    std::vector<uint8_t> stepped((size_t)G);
+    std::vector<int64_t> bw_off((size_t)I + 1, 0);
+    Facts facts;
+    RETCHK(validate(d, v, off, N, stepped.data(), threads_for(N), &facts));
+
+    std::unique_ptr<svf_batch, Destroy> own(new svf_batch());
+    svf_batch* h = own.get();
+    h->stream = (hipStream_t)hip_stream;
+    (void)hipGetDevice(&h->device);
+    RETCHK(plan_batch(h, d, off, stepped.data(), facts, bw_off.data()));
+    // chunk table (segment, first position) of the sort for large instances
+    std::vector<int32_t> cseg, clo;
+    if (!h->fused_sort)
+        for (int32_t p = 0; p < P; ++p)
+            for (int32_t i = 0; i < I; ++i)
+                for (int64_t lo = 0; lo < off[i + 1] - off[i]; lo += h->CH) {
+                    cseg.push_back(p * I + i);
+                    clo.push_back((int32_t)lo);
+                }
+    h->nchunks = (int32_t)cseg.size();
+
+    // one allocation, the host's tables and the inputs first
+    size_t tables = 0, inputs = 0;
+    auto place = [&](Carve c) {
+        h->d_off = c.take<int64_t>(I + 1);
+        h->d_pol = c.take<int32_t>(P);
+        h->d_stepped = c.take<uint8_t>(G);
+        h->d_bw_off = c.take<int64_t>(I + 1);
+        h->d_chunk_seg = c.take<int32_t>(h->nchunks);
+        h->d_chunk_lo = c.take<int32_t>(h->nchunks);
+        tables = c.used;
+        h->d_a = c.take<int32_t>(N);
+        h->d_s = c.take<int32_t>(N);
+        h->d_o = c.take<int32_t>(N);
+        if (d->plan_len) h->d_plan = c.take<int32_t>(N);
+        if (d->long_bit) h->d_bit = c.take<int8_t>(N);
+        inputs = c.used;
+        if (!h->fused_sort) {
+            h->d_keys0 = c.take<uint64_t>(PN);
+            h->d_keys1 = c.take<uint64_t>(PN);
+        }
+        h->d_rec = c.take<int4>(PN);
+        h->d_rank = c.take<int32_t>(PN);
+        h->d_bitmap = c.take<uint64_t>((int64_t)P * h->bw_total);
+        if (h->ring_used) h->d_ring = c.take<int32_t>(G * (h->H + 64));
+        if (h->list_known || h->list_stepped) {
+            h->d_lst_f = c.take<int32_t>(G * (int64_t)h->list_stride);
+            h->d_lst_q = c.take<uint32_t>(G * (int64_t)h->list_stride);
+        }
+        h->d_start = c.take<int32_t>(PN);
+        h->d_fin = c.take<int32_t>(PN);
+        h->d_pre = c.take<int32_t>(PN);
+        h->d_seq = c.take<int32_t>(PN);
+        if (h->any_stepped) {
+            h->d_act = c.take<int4>(PN);
+            if (!h->step_regs) h->d_actkr = c.take<int2>(PN);
+            h->d_evl = c.take<int32_t>(PN);
+        }
+        h->d_st = c.take<SegState>(G);
+        h->d_prog = c.take<unsigned long long>(2 * svfk::PROG_WORDS);
+        h->d_fin_out = c.take<int32_t>(PN);
+        h->d_stats = c.take<StatsOut>(G);
+        if (16 * (size_t)N <= READ_SMALL) h->d_pack = c.take<int32_t>(4 * N);
+        return c.used;
+    };
+    const size_t total = place(Carve{0, 0});
+    if (hipError_t e = hipMalloc(&h->arena, total); e != hipSuccess) {
+        h->arena = nullptr;
+        return fail(SVF_ENOMEM, "hipMalloc of %lld bytes failed: %s", (long long)total, hipGetErrorString(e));
+    }
+    const uintptr_t base = reinterpret_cast<uintptr_t>(h->arena);
+    place(Carve{base, 0});
+    h->policies.assign(d->policies, d->policies + P);
+
+    // the host's tables in one copy, small host inputs with them
+    const bool together = !d->inputs_on_device && inputs <= STAGE_MAX;
+    const size_t front = together ? inputs : tables;
+    std::unique_ptr<char[]> stage(new char[front]);
+    auto put = [&](const void* dev, const void* src, size_t bytes) {
+        if (dev && bytes) memcpy(stage.get() + (reinterpret_cast<uintptr_t>(dev) - base), src, bytes);
+    };
+    put(h->d_off, off, 8 * ((size_t)I + 1));
+    put(h->d_pol, h->policies.data(), 4 * (size_t)P);
+    put(h->d_stepped, stepped.data(), (size_t)G);
+    put(h->d_bw_off, bw_off.data(), 8 * ((size_t)I + 1));
+    put(h->d_chunk_seg, cseg.data(), 4 * cseg.size());
+    put(h->d_chunk_lo, clo.data(), 4 * clo.size());
+    hipError_t e = hipSuccess;
+    if (together) {
+        put(h->d_a, d->arrival, 4 * (size_t)N);
+        put(h->d_s, d->prompt, 4 * (size_t)N);
+        put(h->d_o, d->output, 4 * (size_t)N);
+        put(h->d_plan, d->plan_len, 4 * (size_t)N);
+        put(h->d_bit, d->long_bit, (size_t)N);
+    }
+    e = hipMemcpyAsync(h->arena, stage.get(), front, hipMemcpyHostToDevice, h->stream);
+    if (!together) {
+        const hipMemcpyKind kind = d->inputs_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+        auto copy = [&](void* dev, const void* src, size_t bytes) {
+            if (e == hipSuccess && dev && bytes) e = hipMemcpyAsync(dev, src, bytes, kind, h->stream);
+        };
+        copy(h->d_a, d->arrival, 4 * (size_t)N);
+        copy(h->d_s, d->prompt, 4 * (size_t)N);
+        copy(h->d_o, d->output, 4 * (size_t)N);
+        if (d->plan_len) copy(h->d_plan, d->plan_len, 4 * (size_t)N);
+        if (d->long_bit) copy(h->d_bit, d->long_bit, (size_t)N);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e == hipSuccess)
+        e = svfk::prepare_sim(h->d_lds, h->lds_bytes, h->list_stepped && !h->step_regs, h->lds_step_full);
+    if (e == hipSuccess && h->step_regs) e = svfk::prepare_step(h->list_nb, h->lds_step, h->lds_step_full);
+    if (e == hipSuccess && h->list_known) e = svfk::prepare_list(h->list_nb, h->lds_list, h->lds_list_full);
+    if (e == hipSuccess && h->fused_sort) e = svfk::prepare_sort_rec(h->max_n);
+    // both paths in one batch: a second stream for the per-step launches
+    // (SVFSIM_CONCURRENT=0 keeps them on one stream)
+    const char* pc = getenv("SVFSIM_CONCURRENT");
+    if (e == hipSuccess && h->n_known > 0 && h->n_stepped > 0 && !(pc && !strcmp(pc, "0"))) {
+        e = hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&h->join_ev, hipEventDisableTiming);
+    }
+    if (e != hipSuccess) return fail(SVF_EHIP, "copying the inputs failed: %s", hipGetErrorString(e));
+    *out = own.release();
+    return ok();
+}
+
+// A large read: src[k] to dst[k], ``bytes`` each (dst[k] null: skipped), in
+// slots over host threads.  The stream's earlier work is waited for.
+int read_large(svf_batch* h, const int32_t* const src[4], int32_t* const dst[4], size_t bytes) {
+    const int64_t per = (int64_t)((bytes + READ_SLOT - 1) / READ_SLOT);
+    std::atomic<int64_t> next{0};
+    std::atomic<int> err{0};
+    const int threads = std::max(1, std::min(READ_SLOTS, threads_for(int64_t(1) << 20)));
+    on_threads(threads, [&](int k) {
+        char* slot = h->pinned + (size_t)k * READ_SLOT;
+        hipEvent_t ev = nullptr;
+        hipError_t e = hipSetDevice(h->device);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        while (e == hipSuccess) {
+            const int64_t c = next.fetch_add(1);
+            if (c >= 4 * per) break;
+            const int x = (int)(c / per);
+            if (!dst[x]) continue;
+            const size_t at = (size_t)(c % per) * READ_SLOT, n = std::min(READ_SLOT, bytes - at);
+            const char* from = reinterpret_cast<const char*>(src[x]) + at;
+            e = hipMemcpyAsync(slot, from, n, hipMemcpyDeviceToHost, h->stream);
+            if (e == hipSuccess) e = hipEventRecord(ev, h->stream);
+            if (e == hipSuccess) e = hipEventSynchronize(ev);
+            if (e == hipSuccess) memcpy(reinterpret_cast<char*>(dst[x]) + at, slot, n);
+        }
+        if (ev) (void)hipEventDestroy(ev);
+        if (e != hipSuccess) err = (int)e;
+    });
+    if (err) return fail(SVF_EHIP, "reading the outputs failed: %s", hipGetErrorString((hipError_t)err.load()));
+    return SVF_OK;
+}
 
 }  // namespace
 
@@ -723,163 +1086,11 @@ int svf_create(const svf_batch_desc* d, void* hip_stream, svf_batch** out) {
     g_err[0] = 0;
     if (!out) return fail(SVF_EINVAL, "out is NULL");
     *out = nullptr;
-    int64_t N = 0;
-    RETCHK(check_desc_shape(d, &N));
-    const int32_t I = d->num_instances, P = d->num_policies;
-    const std::vector<int64_t> off(d->req_offsets, d->req_offsets + I + 1);
-
-    // host view of the per-request arrays (device inputs are fetched first)
-    std::vector<int32_t> ha, hs, ho, hp;
-    std::vector<int8_t> hb;
-    HostView v{d->arrival, d->prompt, d->output, d->plan_len, d->long_bit};
-    if (d->inputs_on_device && N > 0) {
-        if (!d->arrival || !d->prompt || !d->output)
-            return fail(SVF_EINVAL, "arrival, prompt and output must not be NULL");
-        ha.resize(N); hs.resize(N); ho.resize(N);
-        HIPCHK(hipMemcpy(ha.data(), d->arrival, 4 * N, hipMemcpyDeviceToHost));
-        HIPCHK(hipMemcpy(hs.data(), d->prompt, 4 * N, hipMemcpyDeviceToHost));
-        HIPCHK(hipMemcpy(ho.data(), d->output, 4 * N, hipMemcpyDeviceToHost));
-        v.a = ha.data(); v.s = hs.data(); v.o = ho.data();
-        if (d->plan_len) {
-            hp.resize(N);
-            HIPCHK(hipMemcpy(hp.data(), d->plan_len, 4 * N, hipMemcpyDeviceToHost));
-            v.plan = hp.data();
-        }
-        if (d->long_bit) {
-            hb.resize(N);
-            HIPCHK(hipMemcpy(hb.data(), d->long_bit, N, hipMemcpyDeviceToHost));
-            v.bit = hb.data();
-        }
+    try {
+        return create(d, hip_stream, out);
+    } catch (const std::exception&) {
+        return fail(SVF_ENOMEM, "host allocation failed");
     }
-    std::vector<uint8_t> stepped((size_t)P * I);
-    int64_t max_plan = 1, max_profile = 0;
-    uint64_t max_key[8];
-    RETCHK(validate(d, v, off.data(), N, stepped.data(), &max_plan, &max_profile, max_key));
-
-    svf_batch* h = new (std::nothrow) svf_batch();
-    if (!h) return fail(SVF_ENOMEM, "host allocation failed");
-    h->stream = (hipStream_t)hip_stream;
-    (void)hipGetDevice(&h->device);
-    h->policies.assign(d->policies, d->policies + P);
-    h->offsets = off;
-    std::vector<int64_t> bw_off(I + 1, 0);
-    {
-        const int rc = plan_batch(h, d, v, off.data(), stepped.data(), max_plan, max_profile,
-                                  max_key, bw_off.data());
-        if (rc != SVF_OK) {
-            delete h;
-            return rc;
-        }
-    }
-    // chunk table (segment, first position) of the sort for large instances
-    std::vector<int32_t> cseg, clo;
-    for (int32_t p = 0; p < P; ++p)
-        for (int32_t i = 0; i < I; ++i) {
-            const int64_t n = off[i + 1] - off[i];
-            for (int64_t lo = 0; lo < n; lo += h->CH) {
-                cseg.push_back(p * I + i);
-                clo.push_back((int32_t)lo);
-            }
-        }
-    h->nchunks = (int32_t)cseg.size();
-
-    const int64_t G = (int64_t)P * I;
-    const int64_t PN = (int64_t)P * N;
-    int rc = SVF_OK;
-#define ALLOC(ptr, cnt) \
-    if (rc == SVF_OK) rc = dalloc(&h->ptr, (cnt));
-    ALLOC(d_off, I + 1);
-    ALLOC(d_a, N);
-    ALLOC(d_s, N);
-    ALLOC(d_o, N);
-    if (d->plan_len) ALLOC(d_plan, N);
-    if (d->long_bit) ALLOC(d_bit, N);
-    ALLOC(d_pol, P);
-    ALLOC(d_chunk_seg, h->nchunks);
-    ALLOC(d_chunk_lo, h->nchunks);
-    if (!h->fused_sort) {
-        ALLOC(d_keys0, PN);
-        ALLOC(d_keys1, PN);
-    }
-    ALLOC(d_rec, PN);
-    ALLOC(d_rank, PN);
-    ALLOC(d_stepped, G);
-    ALLOC(d_bw_off, I + 1);
-    ALLOC(d_bitmap, (int64_t)P * h->bw_total);
-    if (h->ring_used) ALLOC(d_ring, G * (h->H + 64));
-    if (h->list_known || h->list_stepped) {
-        ALLOC(d_lst_f, G * (int64_t)h->list_stride);
-        ALLOC(d_lst_q, G * (int64_t)h->list_stride);
-    }
-    ALLOC(d_start, PN);
-    ALLOC(d_fin, PN);
-    ALLOC(d_pre, PN);
-    ALLOC(d_seq, PN);
-    if (h->any_stepped) {
-        ALLOC(d_act, PN);
-        ALLOC(d_actkr, PN);
-        ALLOC(d_evl, PN);
-    }
-    ALLOC(d_st, G);
-    ALLOC(d_prog, 2 * svfk::PROG_WORDS);
-    ALLOC(d_fin_out, PN);
-    ALLOC(d_stats, G);
-#undef ALLOC
-    if (rc != SVF_OK) {
-        free_all(h);
-        delete h;
-        return rc;
-    }
-    const hipMemcpyKind kind = d->inputs_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    hipError_t e = hipSuccess;
-#define CPY(dst, src, bytes, k) \
-    if (e == hipSuccess && (bytes) > 0) e = hipMemcpyAsync((dst), (src), (bytes), (k), h->stream);
-    CPY(h->d_off, off.data(), 8 * (I + 1), hipMemcpyHostToDevice);
-    CPY(h->d_a, d->arrival, 4 * N, kind);
-    CPY(h->d_s, d->prompt, 4 * N, kind);
-    CPY(h->d_o, d->output, 4 * N, kind);
-    if (d->plan_len) CPY(h->d_plan, d->plan_len, 4 * N, kind);
-    if (d->long_bit) CPY(h->d_bit, d->long_bit, N, kind);
-    CPY(h->d_pol, h->policies.data(), 4 * P, hipMemcpyHostToDevice);
-    CPY(h->d_chunk_seg, cseg.data(), 4 * (int64_t)cseg.size(), hipMemcpyHostToDevice);
-    CPY(h->d_chunk_lo, clo.data(), 4 * (int64_t)clo.size(), hipMemcpyHostToDevice);
-    CPY(h->d_stepped, stepped.data(), G, hipMemcpyHostToDevice);
-    CPY(h->d_bw_off, bw_off.data(), 8 * (I + 1), hipMemcpyHostToDevice);
-#undef CPY
-    // Finishes and preemption counts are written only by the per-step path;
-    // event-path segments keep these initial values (the reset's sort clears
-    // them for per-step segments only).
-    if (e == hipSuccess) e = svfk::launch_fill_i32(h->d_fin, PN, -1, h->stream);
-    if (e == hipSuccess) e = svfk::launch_fill_i32(h->d_pre, PN, 0, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    if (e == hipSuccess) {
-        hipError_t a = svfk::prepare_sim(h->d_lds, h->lds_bytes, h->list_stepped && !h->step_regs,
-                                         h->lds_step_full);
-        if (a == hipSuccess && h->step_regs)
-            a = svfk::prepare_step(h->list_nb, h->lds_step, h->lds_step_full);
-        if (a == hipSuccess && h->list_known)
-            a = svfk::prepare_list(h->list_nb, h->lds_list, h->lds_list_full);
-        if (a != hipSuccess) e = a;
-    }
-    if (e == hipSuccess && h->fused_sort) {
-        hipError_t a = svfk::prepare_sort_rec(h->max_n);
-        if (a != hipSuccess) e = a;
-    }
-    // both paths in one batch: a second stream for the per-step launches
-    // (SVFSIM_CONCURRENT=0 keeps them on one stream)
-    const char* pc = getenv("SVFSIM_CONCURRENT");
-    if (e == hipSuccess && h->n_known > 0 && h->n_stepped > 0 && !(pc && !strcmp(pc, "0"))) {
-        e = hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&h->join_ev, hipEventDisableTiming);
-    }
-    if (e != hipSuccess) {
-        free_all(h);
-        delete h;
-        return fail(SVF_EHIP, "copying the inputs failed: %s", hipGetErrorString(e));
-    }
-    *out = h;
-    return ok();
 }
 
 int svf_reset(svf_batch* h) {
@@ -915,7 +1126,7 @@ int svf_read(svf_batch* h, int32_t slot, int32_t* start, int32_t* finish, int32_
         svfk::CopyArgs C{};
         C.n = h->N;
         int arrays = 0;
-        const int32_t* src[4] = {h->d_start, h->d_fin_out, h->d_pre, h->d_seq};
+        const int32_t* const src[4] = {h->d_start, h->d_fin_out, h->d_pre, h->d_seq};
         int32_t* const dst[4] = {start, finish, preempt, admit_seq};
         for (int x = 0; x < 4; ++x) {
             if (!dst[x]) continue;
@@ -929,12 +1140,45 @@ int svf_read(svf_batch* h, int32_t slot, int32_t* start, int32_t* finish, int32_
         HIPCHK(svfk::launch_copy4(C, arrays, h->stream));
         return ok();
     }
-    if (bytes) {
-        if (start) HIPCHK(hipMemcpyAsync(start, h->d_start + base, bytes, k, h->stream));
-        if (finish) HIPCHK(hipMemcpyAsync(finish, h->d_fin_out + base, bytes, k, h->stream));
-        if (preempt) HIPCHK(hipMemcpyAsync(preempt, h->d_pre + base, bytes, k, h->stream));
-        if (admit_seq) HIPCHK(hipMemcpyAsync(admit_seq, h->d_seq + base, bytes, k, h->stream));
+    const int32_t* const src[4] = {h->d_start + base, h->d_fin_out + base, h->d_pre + base, h->d_seq + base};
+    int32_t* const dst[4] = {start, finish, preempt, admit_seq};
+    if (bytes && h->d_pack) {
+        // side by side on the device, then one copy
+        svfk::CopyArgs C{};
+        C.n = h->N;
+        int arrays = 0;
+        for (int x = 0; x < 4; ++x)
+            if (dst[x]) {
+                C.src[arrays] = src[x];
+                C.dst[arrays] = h->d_pack + (int64_t)arrays * h->N;
+                ++arrays;
+            }
+        std::unique_ptr<char[]> host(new (std::nothrow) char[bytes * 4]);
+        if (!host) return fail(SVF_ENOMEM, "host allocation failed");
+        if (arrays > 0) {
+            HIPCHK(svfk::launch_copy4(C, arrays, h->stream));
+            HIPCHK(hipMemcpyAsync(host.get(), h->d_pack, bytes * arrays, k, h->stream));
+            HIPCHK(hipStreamSynchronize(h->stream));
+        }
+        arrays = 0;
+        for (int x = 0; x < 4; ++x)
+            if (dst[x]) memcpy(dst[x], host.get() + bytes * arrays++, bytes);
+        return ok();
     }
+    if (4 * bytes >= READ_LARGE && !h->pinned &&
+        hipHostMalloc((void**)&h->pinned, READ_SLOTS * READ_SLOT, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        h->pinned = nullptr;
+    }
+    if (4 * bytes >= READ_LARGE && h->pinned) {
+        try {
+            return read_large(h, src, dst, bytes);
+        } catch (const std::exception&) {
+            return fail(SVF_ENOMEM, "host allocation failed");
+        }
+    }
+    for (int x = 0; x < 4; ++x)
+        if (bytes && dst[x]) HIPCHK(hipMemcpyAsync(dst[x], src[x], bytes, k, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     return ok();
 }
@@ -1024,29 +1268,29 @@ int svf_run_noalloc(const svf_batch_desc* d, void* hip_stream, int32_t* start, i
 
     std::lock_guard<std::mutex> lock(g_na_mu);
     const HostView v{d->arrival, d->prompt, d->output, d->plan_len, d->long_bit};
-    int64_t max_plan = 1, max_profile = 0;
-    uint64_t max_key[8];
-    RETCHK(validate(d, v, off, N, g_na_stepped, &max_plan, &max_profile, max_key));
+    Facts facts;
+    RETCHK(validate(d, v, off, N, g_na_stepped, 1, &facts));
     svf_batch h;  // the launch plan; its buffers are the scratch and the caller's outputs
     h.stream = (hipStream_t)hip_stream;
     HIPCHK(hipGetDevice(&h.device));
-    RETCHK(plan_batch(&h, d, v, off, g_na_stepped, max_plan, max_profile, max_key, g_na_bw_off));
+    RETCHK(plan_batch(&h, d, off, g_na_stepped, facts, g_na_bw_off));
 
     void* base = nullptr;
     size_t cap = 0;
     HIPCHK(svfk::noalloc_scratch(&base, &cap));
-    Carve c{static_cast<char*>(base), 0};
+    Carve c{reinterpret_cast<uintptr_t>(base), 0};
     h.d_off = c.take<int64_t>(I + 1);
+    h.d_pol = c.take<int32_t>(P);
+    h.d_stepped = c.take<uint8_t>(G);
+    h.d_bw_off = c.take<int64_t>(I + 1);
     h.d_a = c.take<int32_t>(N);
     h.d_s = c.take<int32_t>(N);
     h.d_o = c.take<int32_t>(N);
     if (d->plan_len) h.d_plan = c.take<int32_t>(N);
     if (d->long_bit) h.d_bit = c.take<int8_t>(N);
-    h.d_pol = c.take<int32_t>(P);
+    const size_t inputs = c.used;
     h.d_rec = c.take<int4>(PN);
     h.d_rank = c.take<int32_t>(PN);
-    h.d_stepped = c.take<uint8_t>(G);
-    h.d_bw_off = c.take<int64_t>(I + 1);
     h.d_bitmap = c.take<uint64_t>((int64_t)P * h.bw_total);
     if (h.ring_used) h.d_ring = c.take<int32_t>(G * (h.H + 64));
     if (h.list_known || h.list_stepped) {
@@ -1056,7 +1300,7 @@ int svf_run_noalloc(const svf_batch_desc* d, void* hip_stream, int32_t* start, i
     h.d_fin = c.take<int32_t>(PN);
     if (h.any_stepped) {
         h.d_act = c.take<int4>(PN);
-        h.d_actkr = c.take<int2>(PN);
+        if (!h.step_regs) h.d_actkr = c.take<int2>(PN);
         h.d_evl = c.take<int32_t>(PN);
     }
     h.d_st = c.take<SegState>(G);
@@ -1072,21 +1316,25 @@ int svf_run_noalloc(const svf_batch_desc* d, void* hip_stream, int32_t* start, i
 
     // inputs and host tables into the scratch; everything else the call reads
     // is rebuilt by its own kernels (the scratch keeps the previous call's data)
+    // (small ones side by side in host memory first: one copy instead of nine)
     const hipMemcpyKind k = hipMemcpyHostToDevice;
     hipError_t e = hipSuccess;
-#define CPY(dst, src, bytes) \
-    if (e == hipSuccess && (bytes) > 0) e = hipMemcpyAsync((dst), (src), (bytes), k, h.stream);
-    CPY(h.d_off, off, 8 * (I + 1));
-    CPY(h.d_a, d->arrival, 4 * N);
-    CPY(h.d_s, d->prompt, 4 * N);
-    CPY(h.d_o, d->output, 4 * N);
-    if (d->plan_len) CPY(h.d_plan, d->plan_len, 4 * N);
-    if (d->long_bit) CPY(h.d_bit, d->long_bit, N);
-    CPY(h.d_pol, d->policies, 4 * P);
-    CPY(h.d_stepped, g_na_stepped, G);
-    CPY(h.d_bw_off, g_na_bw_off, 8 * (I + 1));
-#undef CPY
-    h.clear_all = true;  // finishes and preemption counts start cleared, as at svf_create
+    const bool together = inputs <= sizeof g_na_stage;
+    auto put = [&](void* dst, const void* src, size_t bytes) {
+        if (!dst || !bytes || e != hipSuccess) return;
+        if (together) memcpy(g_na_stage + (static_cast<char*>(dst) - static_cast<char*>(base)), src, bytes);
+        else e = hipMemcpyAsync(dst, src, bytes, k, h.stream);
+    };
+    put(h.d_off, off, 8 * ((size_t)I + 1));
+    put(h.d_pol, d->policies, 4 * (size_t)P);
+    put(h.d_stepped, g_na_stepped, (size_t)G);
+    put(h.d_bw_off, g_na_bw_off, 8 * ((size_t)I + 1));
+    put(h.d_a, d->arrival, 4 * (size_t)N);
+    put(h.d_s, d->prompt, 4 * (size_t)N);
+    put(h.d_o, d->output, 4 * (size_t)N);
+    if (d->plan_len) put(h.d_plan, d->plan_len, 4 * (size_t)N);
+    if (d->long_bit) put(h.d_bit, d->long_bit, (size_t)N);
+    if (together && e == hipSuccess) e = hipMemcpyAsync(base, g_na_stage, inputs, k, h.stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h.stream);
     if (e != hipSuccess)
         return fail(SVF_EHIP, "svf_run_noalloc: copying the inputs failed: %s", hipGetErrorString(e));
