@@ -1044,8 +1044,13 @@ int create(const svf_batch_desc* d, void* hip_stream, svf_batch** out) {
 }
 
 // A large read: src[k] to dst[k], ``bytes`` each (dst[k] null: skipped), in
-// slots over host threads.  The stream's earlier work is waited for.
+// slots over host threads.  The stream's earlier work is waited for here, in
+// the calling thread: hipStreamPerThread names another stream in each of the
+// others.  The caller's current device stays what it was.
 int read_large(svf_batch* h, const int32_t* const src[4], int32_t* const dst[4], size_t bytes) {
+    HIPCHK(hipStreamSynchronize(h->stream));
+    int current = h->device;
+    HIPCHK(hipGetDevice(&current));
     const int64_t per = (int64_t)((bytes + READ_SLOT - 1) / READ_SLOT);
     std::atomic<int64_t> next{0};
     std::atomic<int> err{0};
@@ -1070,6 +1075,7 @@ int read_large(svf_batch* h, const int32_t* const src[4], int32_t* const dst[4],
         if (ev) (void)hipEventDestroy(ev);
         if (e != hipSuccess) err = (int)e;
     });
+    (void)hipSetDevice(current);
     if (err) return fail(SVF_EHIP, "reading the outputs failed: %s", hipGetErrorString((hipError_t)err.load()));
     return SVF_OK;
 }
