@@ -92,6 +92,7 @@ struct svf_batch {
     bool any_stepped = false;
     int64_t n_known = 0, n_stepped = 0;
     bool was_reset = false, dirty = false;
+    bool cleared = false;     // a reset outside of stream capture cleared every output
     bool prof = false;
     std::vector<Timed> timed;
     double acc_ms[3] = {0, 0, 0};
@@ -669,9 +670,15 @@ int do_reset(svf_batch* h) {
     for (int p = 0; p < 8; ++p) A.kbits[p] = h->kbits[p];
     A.start = h->d_start; A.fin = h->d_fin; A.preempt = h->d_pre; A.admit_seq = h->d_seq;
     A.stepped = h->d_stepped;
-    // finishes and preemption counts of event-path segments are never written:
-    // cleared once
-    A.clear_all = !h->was_reset;
+    // Finishes and preemption counts of event-path segments are never written:
+    // cleared once, by the first reset that runs (one recorded into a graph
+    // may not).
+    A.clear_all = !h->cleared;
+    if (!h->cleared) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(h->stream, &cs) != hipSuccess) (void)hipGetLastError();
+        else h->cleared = cs == hipStreamCaptureStatusNone;
+    }
     A.st = h->d_st;
     A.bitmap = h->d_bitmap;
     A.bw_off = h->d_bw_off;
