@@ -47,6 +47,8 @@ struct StatsOut {
 
 // Progress counters of one launch: one per cache line.
 enum { PROG_LINES = 64, PROG_STRIDE = 16, PROG_WORDS = PROG_LINES * PROG_STRIDE };
+// Behind the scratch of the no-allocation entry point: its two launches' progress counters.
+enum { NOALLOC_PROG_BYTES = 2 * PROG_WORDS * 8 };
 
 struct SortArgs {
     const int64_t* offsets;   // [I+1]
@@ -185,7 +187,8 @@ hipError_t launch_sim(const SimArgs& P, int G, bool d_lds, bool stepped, bool li
 hipError_t sim_step_occupancy(size_t lds_bytes, int* blocks);
 hipError_t launch_finalize(const FinArgs& F, int G, hipStream_t s);
 // Device address and size of the calling thread's current device's scratch
-// array of the no-allocation entry point (svf_noalloc.hip).
+// array of the no-allocation entry point (svf_noalloc.hip); NOALLOC_PROG_BYTES
+// more follow it.
 hipError_t noalloc_scratch(void** addr, size_t* bytes);
 
 }  // namespace svfk

@@ -12,7 +12,7 @@
 #include "svf_kernels.h"
 #include "svfsim.h"
 
-static __device__ __align__(256) unsigned char scratch[SVF_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[SVF_NOALLOC_SCRATCH_BYTES + svfk::NOALLOC_PROG_BYTES];
 
 namespace svfk {
 namespace {
@@ -37,7 +37,7 @@ hipError_t noalloc_scratch(void** addr, size_t* bytes) {
         g_addr[dev] = p;
     }
     *addr = g_addr[dev];
-    *bytes = sizeof(scratch);
+    *bytes = SVF_NOALLOC_SCRATCH_BYTES;
     return hipSuccess;
 }
 

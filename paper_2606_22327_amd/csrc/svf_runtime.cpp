@@ -1317,7 +1317,9 @@ int svf_run_noalloc(const svf_batch_desc* d, void* hip_stream, int32_t* start, i
         h.d_evl = c.take<int32_t>(PN);
     }
     h.d_st = c.take<SegState>(G);
-    h.d_prog = c.take<unsigned long long>(2 * svfk::PROG_WORDS);
+    // (of the progress counters, 16 bytes count against the limit; the scratch
+    // array has room for the rest behind it)
+    h.d_prog = c.take<unsigned long long>(2);
     if (c.used > cap)
         return fail(SVF_EINVAL, "svf_run_noalloc: the batch needs %zu bytes of device scratch, "
                                 "more than the %zu this entry point has", c.used, cap);
