@@ -789,9 +789,10 @@ int do_sim(svf_batch* h, int64_t delta) {
         le = svfk::launch_sim(T, G, h->d_lds, true, h->list_stepped,
                               h->list_stepped ? h->lds_step : h->lds_bytes, st_stepped);
         if (le == hipSuccess && h->list_stepped &&
-            (h->step_cap < h->step_full || (h->step_regs && h->list_stride > 64 * svfk::STEP_E))) {
+            (h->step_cap < h->step_full || (h->step_regs && h->list_stride >= 64 * svfk::STEP_E))) {
             // segments whose list outgrew the LDS capacity (or whose running
-            // requests the registers), up to the same step
+            // requests the registers: with every place taken a segment stops
+            // at the next candidate, fit or not), up to the same step
             T.list_cap = h->step_full;
             T.list_resume = 1;
             T.prio = 0;

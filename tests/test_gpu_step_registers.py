@@ -103,3 +103,15 @@ def test_limits_of_the_register_form(limit):
     else:
         for n in (2000, 2100):  # all of them fit at once
             check(W.assemble(limit, parts(n, np.full(n, 1), rng.integers(4, 30, n)), 1 << 17, ("svf",)))
+
+
+@pytest.mark.parametrize("k", [383, 384, 385, 639, 640, 641])
+def test_bound_equal_to_the_places(k):
+    """Exactly k requests of one token fit at the next step, one more waits:
+    with every place taken the launch stops at that candidate, fit or not."""
+    n = k + 40
+    rng = np.random.default_rng(k)
+    o = rng.integers(1, 30, n)
+    part = {"arrival": np.zeros(n, dtype=np.int64), "prompt": np.ones(n, dtype=np.int64), "output": o,
+            "plan_len": np.maximum(1, o + rng.integers(-2, 3, n))}
+    check(W.assemble(f"places{k}", [part] * 3, 2 * k, ("svf+cur", "fcfs+cur", "sjf")))
