@@ -123,7 +123,8 @@ struct SimArgs {
     int32_t list_cap;         // entries per segment in this launch (in LDS and registers)
     int32_t list_nb;          // event path: bitmap pairs in registers (0: bitmap in LDS)
     int32_t step_regs;        // per-step path: its running requests in registers (k_sim_step)
-    int32_t list_resume;      // 1: only continue the segments that stopped with a full list
+    int32_t list_resume;      // not 0: only continue the segments that stopped with a full list
+                              //   (per-step path in registers: 1 with STEP_E_MID, 2 with STEP_E_FULL)
     int32_t prio;             // 1: the waves set their issue priorities
     unsigned long long* prog; // [PROG_WORDS] progress counters of this launch, zero before it (and after
                               //   it: every wave takes back what it added)
@@ -170,15 +171,16 @@ hipError_t prepare_list(int nb, size_t lds_first, size_t lds_full);
 // resident waves per compute unit of its first launch
 hipError_t list_occupancy(int nb, size_t lds_bytes, int* blocks);
 // The per-step path with its running requests in registers: places of the
-// first launch and of the continuation (64 each), and what it assumes of a
+// first launch and of its two continuations (64 each), and what it assumes of a
 // batch: the bound on running requests below its places, indexes and ranks in
 // 16 bits, the factors of a remaining volume in 24 bits, twice a volume in 32.
-enum { STEP_E = 6, STEP_E_FULL = 32 };
+enum { STEP_E = 6, STEP_E_MID = 10, STEP_E_FULL = 32 };
 inline bool step_regs_ok(int64_t bound, int64_t max_n, int64_t M, uint64_t max_volume) {
     return bound < 64 * STEP_E_FULL && max_n <= 65536 && M < (1 << 23) - 1 &&
            max_volume < (uint64_t(1) << 31);
 }
-hipError_t prepare_step(int nb, size_t lds_first, size_t lds_full);
+// step: 0 the first launch, 1 and 2 the continuations (SimArgs::list_resume)
+hipError_t prepare_step(int nb, const size_t lds[3]);
 hipError_t step_occupancy(int nb, size_t lds_bytes, int* blocks);
 // list: the event path keeps its profile as the finish-ordered list
 hipError_t launch_sim(const SimArgs& P, int G, bool d_lds, bool stepped, bool list,

@@ -1346,14 +1346,17 @@ __device__ __forceinline__ void run_step_list(const SimArgs& P, const Seg& sg, u
     asm volatile(ST_LOOP_0(E_) : ST_STATE                                                         \
                  : ST_INPUT, [bb] "s"(bb), [sb] "s"(bb + 8 * W0), [w1] "s"(W1) : ST_CLOBBER_##E_)
         if (NB == 1) {
-            if (E == 6) ST_RUN(1, 6, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0));
+            if (E == STEP_E) ST_RUN(1, 6, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0));
+            else if (E == STEP_E_MID) ST_RUN(1, 10, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0));
             else ST_RUN(1, 32, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0));
         } else if (NB == 2) {
-            if (E == 6) ST_RUN(2, 6, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0), [b1l] "+&v"(lo1), [b1h] "+&v"(hi1));
+            if (E == STEP_E) ST_RUN(2, 6, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0), [b1l] "+&v"(lo1), [b1h] "+&v"(hi1));
+            else if (E == STEP_E_MID) ST_RUN(2, 10, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0), [b1l] "+&v"(lo1), [b1h] "+&v"(hi1));
             else ST_RUN(2, 32, , [b0l] "+&v"(lo0), [b0h] "+&v"(hi0), [b1l] "+&v"(lo1), [b1h] "+&v"(hi1));
         } else {
             const uint32_t bb = (uint32_t)(uintptr_t)(lds_ptr)B;
-            if (E == 6) ST_RUN_0(6);
+            if (E == STEP_E) ST_RUN_0(6);
+            else if (E == STEP_E_MID) ST_RUN_0(10);
             else ST_RUN_0(32);
         }
 #undef ST_RUN
@@ -2467,17 +2470,22 @@ static SimKernel list_kernel(int nb, bool resume) {
 }
 
 // the per-step path's kernel with the running requests in registers
-static SimKernel step_kernel(int nb, bool resume) {
-    if (nb == 1) return resume ? &k_sim_step<1, STEP_E_FULL> : &k_sim_step<1, STEP_E>;
-    if (nb == 2) return resume ? &k_sim_step<2, STEP_E_FULL> : &k_sim_step<2, STEP_E>;
-    return resume ? &k_sim_step<0, STEP_E_FULL> : &k_sim_step<0, STEP_E>;
+template <int NB>
+static SimKernel step_form(int resume) {
+    if (resume == 0) return &k_sim_step<NB, STEP_E>;
+    return resume == 1 ? &k_sim_step<NB, STEP_E_MID> : &k_sim_step<NB, STEP_E_FULL>;
+}
+static SimKernel step_kernel(int nb, int resume) {
+    if (nb == 1) return step_form<1>(resume);
+    if (nb == 2) return step_form<2>(resume);
+    return step_form<0>(resume);
 }
 
 hipError_t launch_sim(const SimArgs& P, int G, bool d_lds, bool stepped, bool list,
                       size_t lds_bytes, hipStream_t s) {
     if (G <= 0) return hipSuccess;
     if (stepped && list && P.step_regs) {
-        hipLaunchKernelGGL(step_kernel(P.list_nb, P.list_resume != 0), dim3(G), dim3(64), lds_bytes, s, P);
+        hipLaunchKernelGGL(step_kernel(P.list_nb, P.list_resume), dim3(G), dim3(64), lds_bytes, s, P);
     } else if (stepped && list) {
         if (P.list_resume) hipLaunchKernelGGL(k_sim_steplist_resume, dim3(G), dim3(64), lds_bytes, s, P);
         else if (P.list_cap < P.list_stride) hipLaunchKernelGGL(k_sim_steplist_stop, dim3(G), dim3(64), lds_bytes, s, P);
@@ -2521,14 +2529,14 @@ hipError_t prepare_list(int nb, size_t lds_first, size_t lds_full) {
     return r;
 }
 
-hipError_t prepare_step(int nb, size_t lds_first, size_t lds_full) {
-    hipError_t r = sim_attr((const void*)step_kernel(nb, false), lds_first);
-    if (r == hipSuccess) r = sim_attr((const void*)step_kernel(nb, true), lds_full);
+hipError_t prepare_step(int nb, const size_t lds[3]) {
+    hipError_t r = hipSuccess;
+    for (int k = 0; k < 3 && r == hipSuccess; ++k) r = sim_attr((const void*)step_kernel(nb, k), lds[k]);
     return r;
 }
 
 hipError_t step_occupancy(int nb, size_t lds_bytes, int* blocks) {
-    const void* f = (const void*)step_kernel(nb, false);
+    const void* f = (const void*)step_kernel(nb, 0);
     hipError_t r = sim_attr(f, lds_bytes);
     if (r != hipSuccess) return r;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, 64, lds_bytes);

@@ -17,13 +17,16 @@
 // policies 4,096 x 1,000: 9.2 -> 3.4 ms; next-step admission 2,048 x 1,000 x 2:
 // 9.9 -> 2.4 ms; predicted lengths, 1,531 ragged queues x 2: 23.2 -> 7.7 ms.
 // E = 6: at most 231 requests run at once in those and 376 at twice their
-// budget; 24 registers still leave six waves per SIMD.
+// budget; 24 registers still leave six waves per SIMD.  E = 4 (eight
+// waves) took 2 to 6 % less on the three smaller ones and a third more on
+// predicted lengths 8,192 x 5,000 (56.9 against 42.4 ms a pass).
 //
 // The planned profile is the finish-ordered list of the event path
 // (svf_event_loop.h: EV_FIT, EV_DEEP), with removal of entries whose request
 // finishes early or is evicted.  A segment that needs more than 64 E places or
-// a longer list leaves inside the admissions of its step; a launch with E = 32
-// and room for the bound continues it there.  Registers and wait states as in
+// a longer list leaves inside the admissions of its step; a launch with E = 10
+// (five waves per SIMD) continues it there, and one with E = 32 and room for the
+// bound what outgrows that.  Registers and wait states as in
 // svf_event_loop.h.
 #pragma once
 
@@ -77,6 +80,7 @@
     ".set uR, 38\n\t"         /* E registers: a b of the group's requests */
 
 #define ST_PLACES_6           ".set uU, 44\n\t"   /* 4 E registers: the running requests */
+#define ST_PLACES_10           ".set uU, 48\n\t"   /* 4 E registers: the running requests */
 #define ST_PLACES_32          ".set uU, 70\n\t"   /* 4 E registers: the running requests */
 
 #define ST_CLOBBER_6                                                          \
@@ -89,6 +93,19 @@
     "v46", "v47", "v48", "v49", "v50", "v51", "v52", "v53", "v54", "v55",     \
     "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "v64", "v65",     \
     "v66", "v67", "vcc", "scc", "memory"
+
+#define ST_CLOBBER_10                                                         \
+    "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s68", "s69",     \
+    "s70", "s71", "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79",     \
+    "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89",     \
+    "s90", "s91", "s92", "s93", "v20", "v21", "v22", "v23", "v24", "v25",     \
+    "v26", "v27", "v28", "v29", "v30", "v31", "v32", "v33", "v34", "v35",     \
+    "v36", "v37", "v38", "v39", "v40", "v41", "v42", "v43", "v44", "v45",     \
+    "v46", "v47", "v48", "v49", "v50", "v51", "v52", "v53", "v54", "v55",     \
+    "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "v64", "v65",     \
+    "v66", "v67", "v68", "v69", "v70", "v71", "v72", "v73", "v74", "v75",     \
+    "v76", "v77", "v78", "v79", "v80", "v81", "v82", "v83", "v84", "v85",     \
+    "v86", "v87", "vcc", "scc", "memory"
 
 #define ST_CLOBBER_32                                                         \
     "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s68", "s69",     \
@@ -117,6 +134,9 @@
 
 #define ST_REP_6(M)                                                           \
     M(0) M(1) M(2) M(3) M(4) M(5)
+
+#define ST_REP_10(M)                                                          \
+    M(0) M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9)
 
 #define ST_REP_32(M)                                                          \
     M(0) M(1) M(2) M(3) M(4) M(5) M(6) M(7)                                   \
