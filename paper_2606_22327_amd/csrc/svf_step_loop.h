@@ -262,6 +262,9 @@
     "global_load_dword v[vNa], v[vAd], %[arr]\n\t"                            \
     "global_load_dword v[vNr], v[vAd], %[rank]\n\t"
 
+// what a partial sum of the list is held at or above, -2^30
+#define ST_FLOOR "0xc0000000"
+
 // ---- the loop
 
 #define ST_LOOP(REP, PLACES, SET, CLOSE, EMPTY, SCAN)                         \
@@ -564,8 +567,13 @@
     "s_setpc_b64 s[eRet:eRet+1]\n\t"                                          \
                                                                               \
     /* An entry with F = eFa and c = eCh leaves the list: the last lane q with that\
-       F (entries with one F are interchangeable: only the sum over all of them is */\
-    /* ever used).  Those before q lose F + c, those from q on move down by one. */\
+       F.  Those before q lose F + c, those from q on move down by one.  Of entries\
+       with one F the first holds the sum over all of them, and that one is exact\
+       and decides every check (a candidate with that te becomes the first).  The\
+       others lose also what was never in them, without end while requests come\
+       and go at one F: at -2^30 they stop, below any first (a sum of memory, not\
+       negative) and far from wrapping in a check or by one more loss (F + c is a\
+       request's size plus planned length, at most M). */                     \
     ".Lst_del_%=:\n"                                                          \
     "v_cmp_ge_i32 vcc, s[eFa], %[F]\n\t"                                      \
     "s_bcnt1_i32_b64 s[eP], vcc\n\t"                                          \
@@ -592,6 +600,7 @@
     "v_writelane_b32 v[vX], s[eV], 63\n\t"                                    \
     "v_writelane_b32 v[vY], s[eC1], 63\n\t"                                   \
     "v_sub_u32 v[vAd], %[G], v[vAd]\n\t"                                      \
+    "v_max_i32 v[vAd], " ST_FLOOR ", v[vAd]\n\t"                              \
     "v_cndmask_b32 %[F], %[F], v[vX], s[eMk:eMk+1]\n\t"                       \
     "v_cndmask_b32 %[G], v[vAd], v[vY], s[eMk:eMk+1]\n\t"                     \
     "s_sub_i32 %[ln1], %[ln1], 1\n\t"                                         \
@@ -625,8 +634,10 @@
     ".Lst_delg_%=:\n"                                                         \
     "v_add_u32 v[vZ], s[eCh], %[F]\n\t"                                       \
     "v_sub_u32 %[G], %[G], v[vZ]\n\t"                                         \
+    "v_max_i32 %[G], " ST_FLOOR ", %[G]\n\t"                                  \
     "v_add_u32 v[vZ], s[eCh], v[vX]\n\t"                                      \
     "v_sub_u32 v[vY], v[vY], v[vZ]\n\t"                                       \
+    "v_max_i32 v[vY], " ST_FLOOR ", v[vY]\n\t"                                \
     "v_add_u32 v[vAd], -8, v[vAd]\n\t"                                        \
     "s_add_i32 s[eP], s[eP], -1\n\t"                                          \
     "s_bfm_b64 exec, s[eP], 0\n\t"                                            \
@@ -644,6 +655,7 @@
     "s_waitcnt lgkmcnt(0)\n\t"                                                \
     "v_add_u32 v[vZ], s[eCh], v[vX]\n\t"                                      \
     "v_sub_u32 v[vY], v[vY], v[vZ]\n\t"                                       \
+    "v_max_i32 v[vY], " ST_FLOOR ", v[vY]\n\t"                                \
     "ds_write_b64 v[vAd], v[vX:vX+1]\n\t"                                     \
     "s_branch .Lst_delu_%=\n\t"                                               \
     ".Lst_dele_%=:\n"                                                         \

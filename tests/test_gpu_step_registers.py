@@ -115,3 +115,31 @@ def test_bound_equal_to_the_places(k):
     part = {"arrival": np.zeros(n, dtype=np.int64), "prompt": np.ones(n, dtype=np.int64), "output": o,
             "plan_len": np.maximum(1, o + rng.integers(-2, 3, n))}
     check(W.assemble(f"places{k}", [part] * 3, 2 * k, ("svf+cur", "fcfs+cur", "sjf")))
+
+
+def one_finish_many_removals(base, per_step, big, M):
+    """``base`` small requests run from step 0 to 300, their planned finish too.
+    Every step ``per_step`` requests of ``big`` tokens start, planned to finish
+    at 300 as well and over after one step: while one entry of the planned
+    profile waits for the ``base`` behind it to leave, over 2^31 tokens are
+    taken out at 300.  At step 284 one candidate asks for the steps up to 384."""
+    rows = [(0, 1, 300, 300)] * base
+    for t in range(290):
+        if t == 284:
+            rows.append((t, 10, 50, 100))
+        rows += [(t, big, 1, 300 - t)] * per_step
+    a, s, o, plan = (np.array(x, dtype=np.int32) for x in zip(*rows))
+    assert base * big > 1 << 31
+    return W.assemble(f"one finish {base}", [{"arrival": a, "prompt": s, "output": o, "plan_len": plan}],
+                      M, ("fcfs",))
+
+
+@pytest.mark.parametrize("base,per_step,big", [(560, 2, 4000000), (840, 3, 2600000), (1000, 3, 2600000)])
+def test_planned_finish_shared_by_more_than_2_31_tokens_removed(base, per_step, big):
+    """In each of the two continuations (in the first launch 384 entries of at most
+    M / 2 tokens cannot add up to that)."""
+    b = one_finish_many_removals(base, per_step, big, (1 << 23) - 2)
+    r = oracle.run(b, "fcfs")
+    assert r["start"][base + 284 * per_step] == 284 and int(r["preempt"].sum()) == 0
+    check(b)
+    check(b, chunks=(100, 150, 20, 10, 5))
