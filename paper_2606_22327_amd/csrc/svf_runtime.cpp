@@ -679,12 +679,13 @@ int do_reset(svf_batch* h) {
     A.stepped = h->d_stepped;
     // Finishes and preemption counts of event-path segments are never written:
     // cleared once, by the first reset that runs (one recorded into a graph
-    // may not).
+    // may not, and one whose launch fails does not).
     A.clear_all = !h->cleared;
+    bool runs = false;
     if (!h->cleared) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(h->stream, &cs) != hipSuccess) (void)hipGetLastError();
-        else h->cleared = cs == hipStreamCaptureStatusNone;
+        else runs = cs == hipStreamCaptureStatusNone;
     }
     A.st = h->d_st;
     A.bitmap = h->d_bitmap;
@@ -696,6 +697,7 @@ int do_reset(svf_batch* h) {
     if (h->fused_sort) {
         // keys, sort, records, ranks, cleared outputs and the first state in one kernel
         HIPCHK(svfk::launch_sort_rec(A, G, h->max_n, h->stream));
+        h->cleared |= runs;
         record_end(h, 0, e0);
         h->was_reset = true;
         h->dirty = true;

@@ -1,0 +1,321 @@
+// Test driver for the host runtime (svf_runtime.cpp) on a machine without a
+// GPU: HIP's calls and the kernel launchers are replaced by the small host
+// functions below ("device" memory is malloc'd and filled with 0xAB, copies
+// are memcpy), so that the paths past the first device allocation run under
+// the sanitizers.  No simulation result is looked at here.
+// tests/test_host_runtime.py builds and runs it.
+//
+//   reset       a reset whose launch fails leaves the outputs to the next one
+//   validate    validation on several threads against one thread
+#include <hip/hip_runtime_api.h>
+
+#include <algorithm>
+#include <atomic>
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <mutex>
+#include <random>
+#include <string>
+#include <vector>
+
+#include "svf_kernels.h"
+#include "svfsim.h"
+
+// ---------------------------------------------------------------- stand-ins
+
+namespace {
+
+std::mutex g_mu;
+std::map<uintptr_t, std::pair<size_t, hipMemoryType>> g_mem;  // known ranges
+std::atomic<int> g_host_mallocs{0}, g_copies{0}, g_into_pinned{0}, g_copy_kernels{0}, g_ring_launches{0};
+int g_fail_sort = 0;           // launch_sort_rec calls that fail from here on
+bool g_pattern = false;        // launch_finalize writes outputs 4 i + {0, 1, 2, 3}
+svfk::SortArgs g_sort;         // arguments of the last reset
+svfk::SimArgs g_sim;           // and of the last simulation launch
+
+void know(void* p, size_t n, hipMemoryType t) {
+    std::lock_guard<std::mutex> lock(g_mu);
+    g_mem[(uintptr_t)p] = {n, t};
+}
+void forget(void* p) {
+    std::lock_guard<std::mutex> lock(g_mu);
+    g_mem.erase((uintptr_t)p);
+}
+hipMemoryType kind_of(const void* p) {
+    std::lock_guard<std::mutex> lock(g_mu);
+    auto it = g_mem.upper_bound((uintptr_t)p);
+    if (it == g_mem.begin()) return hipMemoryTypeUnregistered;
+    --it;
+    return (uintptr_t)p < it->first + it->second.first ? it->second.second : hipMemoryTypeUnregistered;
+}
+
+}  // namespace
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+    *p = malloc(n);
+    if (!*p) return hipErrorOutOfMemory;
+    memset(*p, 0xAB, n);
+    know(*p, n, hipMemoryTypeDevice);
+    return hipSuccess;
+}
+hipError_t hipFree(void* p) { forget(p); free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+    ++g_host_mallocs;
+    *p = malloc(n);
+    know(*p, n, hipMemoryTypeHost);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void* p) { forget(p); free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+    ++g_copies;
+    if (kind_of(d) == hipMemoryTypeHost) ++g_into_pinned;
+    memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+    memset(a, 0, sizeof *a);
+    a->type = kind_of(p);
+    return a->type == hipMemoryTypeUnregistered ? hipErrorInvalidValue : hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "stand-in"; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
+    *c = hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+}
+
+namespace svfk {
+hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t) { std::fill(p, p + n, v); return hipSuccess; }
+hipError_t launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t) { std::fill(p, p + n, v); return hipSuccess; }
+hipError_t launch_init_ring(int32_t* p, int64_t n, int32_t, hipStream_t) {
+    ++g_ring_launches;
+    std::fill(p, p + n, 0);
+    return hipSuccess;
+}
+hipError_t launch_copy4(const CopyArgs& C, int arrays, hipStream_t) {
+    ++g_copy_kernels;
+    for (int x = 0; x < arrays; ++x) memcpy(C.dst[x], C.src[x], 4 * (size_t)C.n);
+    return hipSuccess;
+}
+hipError_t launch_init_state(SegState*, int32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_chunk_sort(const SortArgs&, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_merge_pass(const SortArgs&, int, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_build_rec(const SortArgs&, int, hipStream_t) { return hipSuccess; }
+hipError_t prepare_sort_rec(int) { return hipSuccess; }
+hipError_t launch_sort_rec(const SortArgs& A, int, int, hipStream_t) {
+    g_sort = A;
+    if (g_fail_sort > 0) {
+        --g_fail_sort;
+        return hipErrorLaunchFailure;
+    }
+    for (int64_t x = 0; x < A.P * A.N; ++x) {
+        A.start[x] = A.admit_seq[x] = -1;
+        if (A.clear_all) {
+            A.fin[x] = -1;
+            A.preempt[x] = 0;
+        }
+    }
+    return hipSuccess;
+}
+hipError_t prepare_sim(bool, size_t, bool, size_t) { return hipSuccess; }
+hipError_t prepare_list(int, size_t, size_t) { return hipSuccess; }
+hipError_t prepare_step(int, const size_t[3]) { return hipSuccess; }
+static hipError_t occupancy(size_t lds, int* b) {
+    *b = (int)std::min<size_t>(32, 160 * 1024 / std::max<size_t>(lds, 1));
+    return hipSuccess;
+}
+hipError_t list_occupancy(int, size_t lds, int* b) { return occupancy(lds, b); }
+hipError_t step_occupancy(int, size_t lds, int* b) { return occupancy(lds, b); }
+hipError_t sim_step_occupancy(size_t lds, int* b) { return occupancy(lds, b); }
+hipError_t launch_sim(const SimArgs& P, int, bool, bool, bool, size_t, hipStream_t) {
+    g_sim = P;
+    return hipSuccess;
+}
+hipError_t launch_finalize(const FinArgs& F, int, hipStream_t) {
+    const int64_t PN = F.P * F.N;
+    for (int64_t x = 0; x < PN; ++x) {
+        F.fin_out[x] = g_pattern ? (int32_t)(4 * x + 1) : F.fin[x];
+        if (!g_pattern) continue;
+        g_sort.start[x] = (int32_t)(4 * x);
+        g_sort.preempt[x] = (int32_t)(4 * x + 2);
+        g_sort.admit_seq[x] = (int32_t)(4 * x + 3);
+    }
+    return hipSuccess;
+}
+hipError_t noalloc_scratch(void** p, size_t* n) {
+    static std::vector<char> scratch(size_t(256) << 20);
+    *p = scratch.data();
+    *n = scratch.size() - NOALLOC_PROG_BYTES;
+    return hipSuccess;
+}
+}  // namespace svfk
+
+// ---------------------------------------------------------------- the tests
+
+namespace {
+
+int failures = 0;
+
+void expect(bool ok, const char* what, long long a = 0, long long b = 0) {
+    if (ok) return;
+    fprintf(stderr, "FAILED: %s (%lld, %lld; last error: %s)\n", what, a, b, svf_last_error());
+    ++failures;
+}
+
+struct Batch {
+    std::vector<int64_t> off;
+    std::vector<int32_t> a, s, o, plan, pol;
+    std::vector<int8_t> bit;
+    int64_t M = 0;
+    svf_batch_desc desc() const {
+        svf_batch_desc d{};
+        d.num_instances = (int32_t)off.size() - 1;
+        d.req_offsets = off.data();
+        d.arrival = a.data();
+        d.prompt = s.data();
+        d.output = o.data();
+        d.plan_len = plan.empty() ? nullptr : plan.data();
+        d.long_bit = bit.empty() ? nullptr : bit.data();
+        d.M = M;
+        d.num_policies = (int32_t)pol.size();
+        d.policies = pol.data();
+        d.O0 = 16;
+        d.O1 = 700;
+        d.max_steps = 1 << 20;
+        return d;
+    }
+};
+
+// n requests in equal instances of ``each``
+Batch plain(int64_t n, int64_t each) {
+    Batch b;
+    for (int64_t x = 0; x <= n; x += each) b.off.push_back(x);
+    if (b.off.back() < n) b.off.push_back(n);
+    b.a.assign((size_t)n, 0);
+    b.s.assign((size_t)n, 3);
+    b.o.assign((size_t)n, 5);
+    b.M = 1000;
+    b.pol = {SVF_POLICY_SVF};
+    return b;
+}
+
+void reset_mode() {
+    Batch b = plain(1000, 50);
+    const svf_batch_desc d = b.desc();
+    svf_batch* h = nullptr;
+    expect(svf_create(&d, nullptr, &h) == SVF_OK, "create");
+    g_fail_sort = 2;
+    expect(svf_reset(h) == SVF_EHIP, "the failing reset says so");
+    expect(svf_run(h) == SVF_EHIP, "and the one a run starts with");
+    expect(svf_reset(h) == SVF_OK && svf_run(h) == SVF_OK, "the next one");
+    std::vector<int32_t> fin(1000), pre(1000);
+    expect(svf_read(h, 0, nullptr, fin.data(), pre.data(), nullptr, 0) == SVF_OK, "read");
+    for (int x = 0; x < 1000 && !failures; ++x)
+        expect(fin[x] == -1 && pre[x] == 0, "outputs cleared by the first reset that ran", fin[x], pre[x]);
+    expect(svf_reset(h) == SVF_OK && g_sort.clear_all == 0, "cleared once");
+    svf_destroy(h);
+}
+
+void validate_mode() {
+    std::mt19937_64 rng(7);
+    auto draw = [&](int lo, int hi) { return lo + (int32_t)(rng() % (uint64_t)(hi - lo + 1)); };
+    Batch b;
+    b.M = 30000;
+    b.off.push_back(0);
+    while (b.off.back() < (1 << 20) + 50000) {
+        const int n = draw(0, 9) == 0 ? 0 : draw(1, 3000);
+        int32_t t = 0;
+        for (int j = 0; j < n; ++j) {
+            t += draw(0, 2);
+            b.a.push_back(t);
+            b.s.push_back(draw(1, 900));
+            b.o.push_back(draw(1, 700));
+            b.plan.push_back(draw(0, 3) ? b.o.back() : draw(1, 700));
+            b.bit.push_back((int8_t)draw(0, 1));
+        }
+        b.off.push_back(b.off.back() + n);
+    }
+    const int64_t N = b.off.back(), I = (int64_t)b.off.size() - 1;
+    b.pol = {SVF_POLICY_SVF, SVF_POLICY_FCFS | SVF_ADMIT_CURRENT, SVF_POLICY_SVF1BIT, SVF_POLICY_SJF};
+    const size_t P = b.pol.size();
+    std::vector<int32_t> out((size_t)N * P);
+    std::vector<svf_instance_stats> st((size_t)I * P);
+    auto noalloc = [&](const svf_batch_desc& d) {
+        return svf_run_noalloc(&d, nullptr, out.data(), out.data(), out.data(), out.data(), st.data());
+    };
+    const svf_batch_desc d = b.desc();
+    expect(I <= SVF_NOALLOC_MAX_INSTANCES, "instances");
+    expect(noalloc(d) == SVF_OK, "one thread");
+    const svfk::SortArgs s1 = g_sort;
+    const svfk::SimArgs q1 = g_sim;
+    const std::vector<uint8_t> step1(s1.stepped, s1.stepped + P * I);
+    const std::vector<int64_t> bw1(s1.bw_off, s1.bw_off + I + 1);
+    for (int round = 0; round < 3; ++round) {
+        svf_batch* h = nullptr;
+        expect(svf_create(&d, nullptr, &h) == SVF_OK && svf_run(h) == SVF_OK, "several threads");
+        if (!h) return;
+        const svfk::SortArgs& s = g_sort;
+        const svfk::SimArgs& q = g_sim;
+        expect(!memcmp(s.kbits, s1.kbits, sizeof s.kbits), "bits of the keys");
+        expect(s.H == s1.H && s.bw_total == s1.bw_total && s.CH == s1.CH, "sizes");
+        expect(!memcmp(s.stepped, step1.data(), step1.size()), "paths");
+        expect(!memcmp(s.bw_off, bw1.data(), 8 * bw1.size()), "bitmap offsets");
+        expect(q.list_stride == q1.list_stride && q.list_cap == q1.list_cap && q.list_nb == q1.list_nb &&
+                   q.step_regs == q1.step_regs && q.prio == q1.prio && q.bw_max == q1.bw_max && q.M == q1.M,
+               "launch plan");
+        svf_destroy(h);
+    }
+    // malformed requests, several at once: the first in instance order is named
+    for (int round = 0; round < 40; ++round) {
+        Batch w = b;
+        for (int k = 0; k < 3; ++k) {
+            const int64_t x = (int64_t)(rng() % (uint64_t)N);
+            switch (draw(0, 6)) {
+            case 0: w.a[x] = -1; break;
+            case 1: w.a[x] = 1 << 29; break;
+            case 2: w.s[x] = 0; break;
+            case 3: w.o[x] = INT32_MIN; break;
+            case 4: w.plan[x] = 0; break;
+            case 5: w.bit[x] = 2; break;
+            default: w.s[x] = INT32_MAX; break;
+            }
+        }
+        const svf_batch_desc e = w.desc();
+        const int rc = noalloc(e);
+        const std::string text = svf_last_error();
+        svf_batch* h = nullptr;
+        expect(svf_create(&e, nullptr, &h) == rc && rc != SVF_OK && text == svf_last_error(),
+               "the error of one thread", rc);
+        if (h) svf_destroy(h);
+    }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+    const std::string mode = argc > 1 ? argv[1] : "";
+    if (mode == "reset") reset_mode();
+    else if (mode == "validate") validate_mode();
+    else return 2;
+    printf("%s: %s\n", mode.c_str(), failures ? "FAILED" : "ok");
+    return failures ? 1 : 0;
+}
