@@ -660,6 +660,8 @@ void record_end(svf_batch* h, int kind, hipEvent_t a) {
     h->timed.push_back({kind, a, b});
 }
 
+constexpr int32_t RING_BY_SORT = 1 << 14;
+
 int do_reset(svf_batch* h) {
     const int32_t G = h->P * h->I;
     const int64_t PN = (int64_t)h->P * h->N;
@@ -691,10 +693,17 @@ int do_reset(svf_batch* h) {
     A.bitmap = h->d_bitmap;
     A.bw_off = h->d_bw_off;
     A.bw_total = h->bw_total;
-    A.ring = h->ring_used ? h->d_ring : nullptr;
+    // Short rings are written by the sort's workgroup of their segment, long
+    // ones (per-step batches with the ring in global memory) by a launch of
+    // their own over the whole GPU: one workgroup took 70 us for 2^17 slots
+    // and 744 for 2^22 where the launch takes 54 and 59, the sort included.
+    const bool long_ring = h->ring_used && h->H > RING_BY_SORT;
+    A.ring = h->ring_used && !long_ring ? h->d_ring : nullptr;
     A.H = h->H;
     A.prog = h->d_prog;
     if (h->fused_sort) {
+        if (long_ring)
+            HIPCHK(svfk::launch_init_ring(h->d_ring, (int64_t)G * (h->H + 64), h->H, h->stream));
         // keys, sort, records, ranks, cleared outputs and the first state in one kernel
         HIPCHK(svfk::launch_sort_rec(A, G, h->max_n, h->stream));
         h->cleared |= runs;

@@ -6,6 +6,7 @@
 // tests/test_host_runtime.py builds and runs it.
 //
 //   reset       a reset whose launch fails leaves the outputs to the next one
+//   rings       who writes the first ring, by its length
 //   validate    validation on several threads against one thread
 #include <hip/hip_runtime_api.h>
 
@@ -235,6 +236,25 @@ void reset_mode() {
     svf_destroy(h);
 }
 
+void rings_mode() {
+    // per-step path, too many running for the list: a ring of the longest plan
+    for (int lg : {10, 14, 15, 20}) {
+        Batch b = plain(8192, 8192);
+        b.M = 1 << 25;
+        b.plan = b.o;
+        b.plan[7] = 1 << lg;
+        b.pol = {SVF_POLICY_FCFS};
+        const svf_batch_desc d = b.desc();
+        svf_batch* h = nullptr;
+        expect(svf_create(&d, nullptr, &h) == SVF_OK, "create");
+        g_ring_launches = 0;
+        expect(svf_reset(h) == SVF_OK, "reset");
+        expect((g_sort.ring != nullptr) == (lg <= 14), "the sort writes short rings", lg);
+        expect(g_ring_launches == (lg <= 14 ? 0 : 1), "a launch of their own for long ones", lg);
+        svf_destroy(h);
+    }
+}
+
 void validate_mode() {
     std::mt19937_64 rng(7);
     auto draw = [&](int lo, int hi) { return lo + (int32_t)(rng() % (uint64_t)(hi - lo + 1)); };
@@ -314,6 +334,7 @@ void validate_mode() {
 int main(int argc, char** argv) {
     const std::string mode = argc > 1 ? argv[1] : "";
     if (mode == "reset") reset_mode();
+    else if (mode == "rings") rings_mode();
     else if (mode == "validate") validate_mode();
     else return 2;
     printf("%s: %s\n", mode.c_str(), failures ? "FAILED" : "ok");
