@@ -887,6 +887,16 @@ bool kernel_writable(const void* p, int device) {
            (reinterpret_cast<uintptr_t>(p) & 3) == 0;
 }
 
+// p is memory of the runtime's (page-locked, managed): it copies there directly.
+bool known_to_runtime(const void* p) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type != hipMemoryTypeUnregistered;
+}
+
 // Sequential placement of buffers in a fixed device region (256-byte
 // aligned); ``used`` may exceed the region, and is checked before any use.
 struct Carve {
@@ -921,11 +931,16 @@ struct Destroy {
     }
 };
 
-// Reads of at least READ_LARGE bytes go through pinned staging, READ_SLOTS
-// slots of READ_SLOT bytes, a host thread per slot: the copies out of the GPU
-// run at the link's rate beside the stores into the caller's pages (which are
-// often touched there for the first time).  Measured, 82 MB into fresh pages:
-// 8.7 ms by four pageable copies.
+// Reads of at least READ_LARGE bytes into ordinary memory go through pinned
+// staging, READ_SLOTS slots of READ_SLOT bytes, a host thread per slot: the
+// copies out of the GPU run at the link's rate beside the stores into the
+// caller's pages (which are often touched there for the first time).  Measured,
+// four arrays into fresh pages, one pageable copy each against this, the first
+// read of a handle (it pins the slots) and later ones: 8.5 MB 510 against 420
+// and 380 us, 80 MB 6.1 against 2.5 and 2.1 ms; 2 to 4 MB of one array, 160 to
+// 260 against 270 to 300 and 180 to 230 us: below 8 MB the copies stay.
+// Page-locked destinations take no part: their one copy each runs at the
+// link's rate (9.6 MB 0.21 ms, through the slots 0.42).
 constexpr int READ_SLOTS = 8;
 constexpr size_t READ_SLOT = size_t(2) << 20, READ_LARGE = size_t(8) << 20;
 // Batches whose outputs of one slot take at most this are read in one copy.
@@ -1190,8 +1205,10 @@ int svf_read(svf_batch* h, int32_t slot, int32_t* start, int32_t* finish, int32_
         return ok();
     }
     const int32_t* const src[4] = {h->d_start + base, h->d_fin_out + base, h->d_pre + base, h->d_seq + base};
-    int32_t* const dst[4] = {start, finish, preempt, admit_seq};
-    if (bytes && h->d_pack) {
+    int32_t* dst[4] = {start, finish, preempt, admit_seq};
+    int wanted = 0;
+    for (int32_t* p : dst) wanted += p != nullptr;
+    if (bytes && wanted > 1 && h->d_pack) {
         // side by side on the device, then one copy
         svfk::CopyArgs C{};
         C.n = h->N;
@@ -1204,22 +1221,29 @@ int svf_read(svf_batch* h, int32_t slot, int32_t* start, int32_t* finish, int32_
             }
         std::unique_ptr<char[]> host(new (std::nothrow) char[bytes * 4]);
         if (!host) return fail(SVF_ENOMEM, "host allocation failed");
-        if (arrays > 0) {
-            HIPCHK(svfk::launch_copy4(C, arrays, h->stream));
-            HIPCHK(hipMemcpyAsync(host.get(), h->d_pack, bytes * arrays, k, h->stream));
-            HIPCHK(hipStreamSynchronize(h->stream));
-        }
+        HIPCHK(svfk::launch_copy4(C, arrays, h->stream));
+        HIPCHK(hipMemcpyAsync(host.get(), h->d_pack, bytes * arrays, k, h->stream));
+        HIPCHK(hipStreamSynchronize(h->stream));
         arrays = 0;
         for (int x = 0; x < 4; ++x)
             if (dst[x]) memcpy(dst[x], host.get() + bytes * arrays++, bytes);
         return ok();
     }
-    if (4 * bytes >= READ_LARGE && !h->pinned &&
+    if (bytes * wanted >= READ_LARGE) {
+        // page-locked destinations need no staging: one copy each at the link's rate
+        for (int x = 0; x < 4; ++x)
+            if (dst[x] && known_to_runtime(dst[x])) {
+                HIPCHK(hipMemcpyAsync(dst[x], src[x], bytes, k, h->stream));
+                dst[x] = nullptr;
+                --wanted;
+            }
+    }
+    if (bytes * wanted >= READ_LARGE && !h->pinned &&
         hipHostMalloc((void**)&h->pinned, READ_SLOTS * READ_SLOT, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         h->pinned = nullptr;
     }
-    if (4 * bytes >= READ_LARGE && h->pinned) {
+    if (bytes * wanted >= READ_LARGE && h->pinned) {
         try {
             return read_large(h, src, dst, bytes);
         } catch (const std::exception&) {

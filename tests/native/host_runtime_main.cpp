@@ -7,6 +7,7 @@
 //
 //   reset       a reset whose launch fails leaves the outputs to the next one
 //   rings       who writes the first ring, by its length
+//   reads       svf_read into host memory of every kind and size
 //   validate    validation on several threads against one thread
 #include <hip/hip_runtime_api.h>
 
@@ -255,6 +256,60 @@ void rings_mode() {
     }
 }
 
+void reads_mode() {
+    g_pattern = true;
+    constexpr int64_t SLOT = 1 << 19;  // words of a slot
+    for (int64_t n : {int64_t(1), int64_t(100), int64_t(16384), int64_t(16385), int64_t(100000),
+                      SLOT + 1, 2 * SLOT, 5 * SLOT + 77}) {
+        Batch b = plain(n, 1000);
+        b.pol = {SVF_POLICY_SVF, SVF_POLICY_FCFS};
+        const svf_batch_desc d = b.desc();
+        svf_batch* h = nullptr;
+        expect(svf_create(&d, nullptr, &h) == SVF_OK && svf_run(h) == SVF_OK, "create and run");
+        g_host_mallocs = 0;
+        // which arrays are wanted, and which of them are page-locked
+        for (int wanted = 0; wanted < 16; wanted += n > SLOT ? 5 : 1)
+            for (int locked : {0, 15, 5}) {
+                int32_t* buf[4];
+                for (int x = 0; x < 4; ++x) {
+                    buf[x] = (int32_t*)malloc(4 * (size_t)n);
+                    std::fill(buf[x], buf[x] + n, -7);
+                    if (locked >> x & 1) know(buf[x], 4 * (size_t)n, hipMemoryTypeHost);
+                }
+                auto arg = [&](int x) { return wanted >> x & 1 ? buf[x] : nullptr; };
+                const int slot = wanted & 1;
+                g_copies = g_into_pinned = g_copy_kernels = 0;
+                const int before = g_host_mallocs;
+                expect(svf_read(h, slot, arg(0), arg(1), arg(2), arg(3), 0) == SVF_OK, "read");
+                const int want = __builtin_popcount(wanted), lock = __builtin_popcount(wanted & locked);
+                const int64_t pageable = 4 * n * (want - lock);
+                for (int x = 0; x < 4; ++x) {
+                    bool right = true;
+                    for (int64_t y = 0; y < n && right; ++y)
+                        right = buf[x][y] == (wanted >> x & 1 ? (int32_t)(4 * (slot * n + y) + x) : -7);
+                    expect(right, "the outputs", n, wanted);
+                    if (locked >> x & 1) forget(buf[x]);
+                    free(buf[x]);
+                }
+                if (16 * n > (256 << 10)) {
+                    // page-locked memory is written directly, one copy per array
+                    const bool slots = pageable >= (8 << 20);
+                    expect(slots || (g_copies == want && g_into_pinned == lock), "one copy per array", n, wanted);
+                    expect(slots || g_host_mallocs == before, "no slots for less than 8 MB", n, wanted);
+                    const int64_t per = (4 * n + 4 * SLOT - 1) / (4 * SLOT);
+                    expect(!slots || g_copies == lock + per * (want - lock), "copies of a large read", g_copies, wanted);
+                } else if (want == 1) {
+                    expect(g_copy_kernels == 0 && g_copies == 1, "one small array in one copy", n, wanted);
+                } else if (want > 1) {
+                    expect(g_copy_kernels == 1 && g_copies == 1, "small arrays side by side", n, wanted);
+                }
+            }
+        expect(g_host_mallocs <= 1, "slots are pinned once per handle", g_host_mallocs);
+        svf_destroy(h);
+    }
+    expect(g_mem.empty(), "everything released", (long long)g_mem.size());
+}
+
 void validate_mode() {
     std::mt19937_64 rng(7);
     auto draw = [&](int lo, int hi) { return lo + (int32_t)(rng() % (uint64_t)(hi - lo + 1)); };
@@ -335,6 +390,7 @@ int main(int argc, char** argv) {
     const std::string mode = argc > 1 ? argv[1] : "";
     if (mode == "reset") reset_mode();
     else if (mode == "rings") rings_mode();
+    else if (mode == "reads") reads_mode();
     else if (mode == "validate") validate_mode();
     else return 2;
     printf("%s: %s\n", mode.c_str(), failures ? "FAILED" : "ok");

@@ -45,11 +45,11 @@ def run(exe, mode):
     assert f"{mode}: ok" in r.stdout
 
 
-@pytest.mark.parametrize("mode", ["reset", "rings", "validate"])
+@pytest.mark.parametrize("mode", ["reset", "rings", "reads", "validate"])
 def test_under_address_and_undefined_sanitizers(address, mode):
     run(address, mode)
 
 
-@pytest.mark.parametrize("mode", ["validate"])
+@pytest.mark.parametrize("mode", ["reads", "validate"])
 def test_under_thread_sanitizer(threads, mode):
     run(threads, mode)
