@@ -1,6 +1,6 @@
 // svf_event_loop.h -- the event loop of the known-length path in gfx950
 // assembly: one wave simulates one instance under one policy, with the
-// finish-ordered list (ListProf) and the rank bitmap (RankBits).
+// finish-ordered list (ListProf) and the rank bitmap (bits_in, bits_out).
 //
 // What bounds it.  The loop is almost all uniform control flow with a few
 // wave-wide operations on 64 list entries, so its time is the number of
@@ -20,7 +20,9 @@
 // Wait states kept by hand (gfx940 and later): 2 between a VALU write of a
 // scalar register or VCC and a VALU read of it, 1 between a VALU write of a
 // vector register and a lane read, 2 before a DPP read, 4 between a VALU
-// write of a scalar register and its use as a lane number.
+// write of a scalar register and its use as a lane number, 5 to its use as an
+// address.  The s_nop at the start covers what the compiler, which does not
+// look into the block, may have written right before it.
 //
 // The steps (t: current step, rank: priority position, lower first):
 //   visit    every request admitted and finished: done; t at the limit: leave
@@ -267,7 +269,7 @@
 
 // The check of a candidate (size eQ+1, planned length eQ+2) started at t and,
 // when it fits, its place in the list: entries with t < F < te, their largest
-// G (vM) and number (eP); then, past EV_ADMITTED, the insertion.  A full
+// G (vM) and number (eP); then, past the limit and the room, the insertion.  A full
 // register group first pushes lane 63's entry.
 #define EV_FIT                                                                \
     "v_subrev_u32 v[vX], s[eT1], %[F]\n\t"                                    \
@@ -490,6 +492,7 @@
 
 #define EV_LOOP(SET, OPEN, CLOSE, EMPTY, SCAN)                                \
     EV_NAMES                                                                  \
+    "s_nop 4\n\t"                                                             \
     "v_mov_b32 v[vM0], m0\n\t"                                                \
     /* the first window's arrivals and ranks; the progress counter */         \
     "v_add_u32 v[vAd], %[wb], %[lane]\n\t"                                    \

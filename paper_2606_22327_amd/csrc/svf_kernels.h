@@ -27,8 +27,8 @@ struct SegState {
                         //   running ones, modulo 2^32)
     int64_t peak;       // largest memory total over the steps folded so far
     int64_t req_steps;  // per-step path: sum over steps of running requests
-    int32_t ln;         // event path with the list profile: running requests
-    uint32_t lq;        //   and the prefix sum of (s - k) of the last entry
+    int32_t ln;         // with the list profile: its entries
+    uint32_t lq;        //   and (k_sim_steplist) the prefix sum of (s - k) of the last entry
     int32_t resume_lim; // list full before step resume_lim: continue up to there (0: no)
     int32_t resume_nev; // per-step path: -1, or stopped in the admission phase of step t
                         //   with this many evictions of that step (ranks in evl)

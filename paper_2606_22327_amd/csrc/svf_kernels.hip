@@ -424,7 +424,7 @@ __global__ __launch_bounds__(NT) void k_sort_rec(SortArgs A) {
             if (r < n) {
                 A.start[base + r] = -1;
                 A.admit_seq[base + r] = -1;
-                if (stepped || A.clear_all) {  // the event path never writes these (cleared at creation)
+                if (stepped || A.clear_all) {  // the event path never writes these (cleared by the first reset)
                     A.fin[base + r] = -1;
                     A.preempt[base + r] = 0;
                 }
@@ -894,13 +894,12 @@ __device__ __forceinline__ void fold_range(const Ring<LDS>& R, int lo, int hi, i
 // ---- known lengths: event-driven
 
 // The event path keeps the future memory profile of the running requests in
-// one of two forms (chosen per batch by the host from the LDS each needs):
-// the ring of G = D + tau values (RingProf) or a list of the running requests
-// ordered by planned finish (ListProf).  Both offer begin (at each visited
-// step, before admissions), fit (the forward-looking check of a candidate
+// one of two forms (chosen per batch by the host): the ring of G = D + tau
+// values (RingProf, run_known) or a list of the running requests ordered by
+// planned finish (ListProf, whose check and insertion are in the assembly
+// loops).  RingProf offers fit (the forward-looking check of a candidate
 // started at t, and its admission when it fits; *t_free as in fit_and_admit
-// otherwise, or -1: the segment has to leave the launch at the current step)
-// and end (the peak of the steps up to t).
+// otherwise) and end (the peak of the steps up to t).
 
 template <bool LDS>
 struct RingProf {
@@ -908,7 +907,6 @@ struct RingProf {
     int folded;     // slots of steps <= folded are labelled for the current window
     int peak_lane;  // per-lane largest memory total of the folded steps
     __device__ __forceinline__ RingProf(const Ring<LDS>& d, int t) : D(d), folded(t), peak_lane(0) {}
-    __device__ __forceinline__ void begin(int) {}
     __device__ __forceinline__ bool fit(int t, int s_h, int oh, int M, int maxF, int* t_free) {
         // slots up to t + oh must be labelled for the current window
         if (t + oh - D.H > folded) {
@@ -924,11 +922,6 @@ struct RingProf {
         return wmax(peak_lane);
     }
 };
-
-// One step down the lanes: lane i gets lane i-1's value (lane 0: undefined).
-__device__ __forceinline__ int lane_up(int v) {
-    return __builtin_amdgcn_update_dpp(v, v, 0x138, 0xf, 0xf, false);  // wave_shr:1
-}
 
 // v with lane l (uniform) replaced by the uniform x.
 __device__ int amdgcn_writelane(int x, int l, int v) __asm("llvm.amdgcn.writelane.i32");
@@ -952,18 +945,18 @@ __device__ __forceinline__ int setlane(int v, int x, int l) { return amdgcn_writ
 // (every quantity formed from it fits in int32).
 //
 // The 64 entries that finish first are in registers, lane i holding the one
-// with i entries before it in order of finish; the others are a stack in LDS.  Most candidates finish among the first 64, so
-// a check reads no memory, and an admission moves the lanes from its place up
-// by one (a DPP move) and pushes the last lane's entry.
-// Finished entries are the first lanes: they stay there, out of every range,
-// until 32 have gathered and the list moves down.  Places past the
-// list hold (INT32_MAX, INT32_MAX), the entry for which the formula above
+// with i entries before it in order of finish; the others are a stack in LDS.
+// Most candidates finish among the first 64, so a check reads no memory, and
+// an admission moves the lanes from its place up by one (a DPP move) and
+// pushes the last lane's entry.  Finished entries are the first lanes: they
+// stay there, out of every range, until 32 have gathered and the list moves
+// down.  Places past the list hold (INT32_MAX, INT32_MAX), the entry for which the formula above
 // gives D(te) + te = te.
 //
 // The host bounds the requests that can run at once; the LDS may hold fewer
-// (more waves then fit on a compute unit).  A candidate that fits into a full
-// list gets *t_free = -1 (a real failure always gives a step after t): the
-// segment stops at that step with the candidate as the head, and a later
+// (more waves then fit on a compute unit).  When a candidate fits into a full
+// list the loop leaves with t_f = -1 (a real failure gives a step after t):
+// the segment stops at that step with the candidate as the head, and a later
 // launch with room for the bound continues it.
 struct ListProf {
     int F, G;
@@ -1071,9 +1064,9 @@ struct LdsBits {
     }
 };
 
-template <class PROF, class BITS>
-__device__ __forceinline__ void run_known(const SimArgs& P, const Seg& sg, BITS& bits, PROF& prof,
-                                          SegState& st, int t_lim) {
+template <bool LDS>
+__device__ __forceinline__ void run_known(const SimArgs& P, const Seg& sg, LdsBits& bits,
+                                          RingProf<LDS>& prof, SegState& st, int t_lim) {
     const int lane = lane_id();
     const int M = P.M;
     const int n = sg.n;
@@ -1153,7 +1146,6 @@ __device__ __forceinline__ void run_known(const SimArgs& P, const Seg& sg, BITS&
 
         // 4. admissions (known lengths: completions change nothing ahead)
         if (r < old_head || (head >= 0 && t >= t_f)) {
-            prof.begin(t);
             bits.open(r);
             for (;;) {
                 int tf = 0;
@@ -1179,9 +1171,6 @@ __device__ __forceinline__ void run_known(const SimArgs& P, const Seg& sg, BITS&
                 q = rec_of(r);
             }
             bits.close();
-            // a full list: the candidate is the head, checked again at t when
-            // the segment resumes
-            if (t_f < 0) break;
         }
 
         // 5. advance to the next step where anything can happen: with a

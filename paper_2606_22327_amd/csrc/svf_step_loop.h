@@ -270,6 +270,7 @@
 #define ST_LOOP(REP, PLACES, SET, CLOSE, EMPTY, SCAN)                         \
     ST_NAMES                                                                  \
     PLACES                                                                    \
+    "s_nop 4\n\t"                                                             \
     "v_mov_b32 v[vM0], m0\n\t"                                                \
     /* the running requests of the launch before */                           \
     REP(ST_LOADU)                                                             \
