@@ -8,6 +8,7 @@
 //   reset       a reset whose launch fails leaves the outputs to the next one
 //   rings       who writes the first ring, by its length
 //   reads       svf_read into host memory of every kind and size
+//   whole       every call on batches of both paths side by side
 //   validate    validation on several threads against one thread
 #include <hip/hip_runtime_api.h>
 
@@ -37,6 +38,7 @@ int g_fail_sort = 0;           // launch_sort_rec calls that fail from here on
 bool g_pattern = false;        // launch_finalize writes outputs 4 i + {0, 1, 2, 3}
 svfk::SortArgs g_sort;         // arguments of the last reset
 svfk::SimArgs g_sim;           // and of the last simulation launch
+int g_sims = 0, g_continued = 0;  // simulation launches, and continuations among them
 
 void know(void* p, size_t n, hipMemoryType t) {
     std::lock_guard<std::mutex> lock(g_mu);
@@ -150,6 +152,8 @@ hipError_t step_occupancy(int, size_t lds, int* b) { return occupancy(lds, b); }
 hipError_t sim_step_occupancy(size_t lds, int* b) { return occupancy(lds, b); }
 hipError_t launch_sim(const SimArgs& P, int, bool, bool, bool, size_t, hipStream_t) {
     g_sim = P;
+    ++g_sims;
+    g_continued += P.list_resume != 0;
     return hipSuccess;
 }
 hipError_t launch_finalize(const FinArgs& F, int, hipStream_t) {
@@ -310,14 +314,15 @@ void reads_mode() {
     expect(g_mem.empty(), "everything released", (long long)g_mem.size());
 }
 
-void validate_mode() {
-    std::mt19937_64 rng(7);
+// Ragged instances, some empty, of at least ``least`` requests together, plans
+// that differ from the truth in a quarter of them, bits.
+Batch ragged(std::mt19937_64& rng, int64_t least, int longest) {
     auto draw = [&](int lo, int hi) { return lo + (int32_t)(rng() % (uint64_t)(hi - lo + 1)); };
     Batch b;
     b.M = 30000;
     b.off.push_back(0);
-    while (b.off.back() < (1 << 20) + 50000) {
-        const int n = draw(0, 9) == 0 ? 0 : draw(1, 3000);
+    while (b.off.back() < least) {
+        const int n = draw(0, 9) == 0 ? 0 : draw(1, longest);
         int32_t t = 0;
         for (int j = 0; j < n; ++j) {
             t += draw(0, 2);
@@ -329,6 +334,54 @@ void validate_mode() {
         }
         b.off.push_back(b.off.back() + n);
     }
+    return b;
+}
+
+void whole_mode() {
+    std::mt19937_64 rng(11);
+    const std::vector<std::vector<int32_t>> mixes = {
+        {SVF_POLICY_SVF}, {SVF_POLICY_SVF, SVF_POLICY_SVF | SVF_ADMIT_CURRENT},
+        {SVF_POLICY_SVF, SVF_POLICY_SJF | SVF_ADMIT_CURRENT, SVF_POLICY_FCFS, SVF_POLICY_SVF1BIT}};
+    // up to 2,700 running: the register form with a continuation, and past it
+    for (int64_t M : {3000, 30000, 400000, 4000000})
+        for (int longest : {120, 5000, 9000})
+            for (const auto& mix : mixes)
+                for (bool predicted : {false, true}) {
+                    Batch b = ragged(rng, 20000, longest);
+                    b.M = M;
+                    b.pol = mix;
+                    if (!predicted) b.plan.clear();
+                    const svf_batch_desc d = b.desc();
+                    const size_t N = (size_t)b.off.back(), I = b.off.size() - 1, P = mix.size();
+                    std::vector<int32_t> out(4 * N * P);
+                    std::vector<svf_instance_stats> st(I * P);
+                    svf_batch* h = nullptr;
+                    expect(svf_create(&d, nullptr, &h) == SVF_OK, "create", M, longest);
+                    if (!h) continue;
+                    expect(svf_set_profiling(h, 1) == SVF_OK, "profiling");
+                    expect(svf_run(h) == SVF_OK && svf_reset(h) == SVF_OK, "run");
+                    for (int64_t k : {0, 7, 1, 100}) expect(svf_step(h, k) == SVF_OK, "step");
+                    svf_timing t;
+                    expect(svf_timings(h, &t) == SVF_OK && t.sim_launches == 5, "timings", t.sim_launches);
+                    for (size_t p = 0; p < P; ++p) {
+                        int32_t* o = out.data() + 4 * N * p;
+                        expect(svf_read(h, (int)p, o, o + N, o + 2 * N, o + 3 * N, 0) == SVF_OK, "read");
+                        expect(svf_read(h, (int)p, o, o + N, o + 2 * N, o + 3 * N, 1) == SVF_OK, "read");
+                        expect(svf_stats(h, (int)p, st.data() + I * p) == SVF_OK, "stats");
+                    }
+                    expect(svf_destroy(h) == SVF_OK, "destroy");
+                    const int rc = svf_run_noalloc(&d, nullptr, out.data(), out.data() + N * P,
+                                                   out.data() + 2 * N * P, out.data() + 3 * N * P, st.data());
+                    expect(rc == (longest > 8192 && rc ? SVF_EINVAL : SVF_OK), "run_noalloc", rc);
+                }
+    expect(g_continued > 0 && g_sims > g_continued, "continuations launched", g_sims, g_continued);
+    expect(g_mem.empty(), "everything released", (long long)g_mem.size());
+}
+
+void validate_mode() {
+    std::mt19937_64 rng(7);
+    auto draw = [&](int lo, int hi) { return lo + (int32_t)(rng() % (uint64_t)(hi - lo + 1)); };
+    Batch b = ragged(rng, (1 << 20) + 50000, 3000);
     const int64_t N = b.off.back(), I = (int64_t)b.off.size() - 1;
     b.pol = {SVF_POLICY_SVF, SVF_POLICY_FCFS | SVF_ADMIT_CURRENT, SVF_POLICY_SVF1BIT, SVF_POLICY_SJF};
     const size_t P = b.pol.size();
@@ -391,6 +444,7 @@ int main(int argc, char** argv) {
     if (mode == "reset") reset_mode();
     else if (mode == "rings") rings_mode();
     else if (mode == "reads") reads_mode();
+    else if (mode == "whole") whole_mode();
     else if (mode == "validate") validate_mode();
     else return 2;
     printf("%s: %s\n", mode.c_str(), failures ? "FAILED" : "ok");

@@ -97,9 +97,19 @@ def test_limits_of_the_register_form(limit):
             check(W.assemble(limit, parts(200, rng.integers(1 << 18, 1 << 20, 200),
                                           rng.integers(4, 60, 200)), M, ("svf", "svf+cur")))
     elif limit == "volume":
-        for s in (20000, 40000):  # s * 60000: below and above 2^31
-            o = rng.integers(20000, 59000, 60)
-            check(W.assemble(limit, parts(60, np.full(60, s), o), 1 << 18, ("sjf", "fcfs")))
+        # size and longest plan whose volume is just below 2^31, and just above;
+        # the victim is chosen among doubled volumes up to twice that
+        s = 20000
+        for longest, below in ((48500, True), (48600, False)):
+            volume = s * longest + (longest * longest + longest) // 2
+            assert (volume < 1 << 31) == below and abs(volume - (1 << 31)) < 1 << 23
+            n = 120
+            plan = np.where(rng.random(n) < 0.5, longest - rng.integers(0, 3, n),
+                            rng.integers(1000, longest, n))
+            plan[0] = longest
+            part = {"arrival": np.cumsum(rng.integers(0, 2000, n)), "prompt": np.full(n, s),
+                    "output": rng.integers(20000, 48000, n), "plan_len": plan}
+            assert check(W.assemble(limit, [part] * 2, 1 << 18, ("svf", "fcfs+cur", "svf+cur"))) > 20
     else:
         for n in (2000, 2100):  # all of them fit at once
             check(W.assemble(limit, parts(n, np.full(n, 1), rng.integers(4, 30, n)), 1 << 17, ("svf",)))

@@ -163,7 +163,10 @@ RUN_CASES = [
 # "config 4 predicted" wrote outputs equal to the oracle's and then did not end: its main thread
 # waited in the leak checker's stop-the-world at exit, all threads stopped, the GPU idle. Why the
 # checker does not return is not shown; "random ragged" ends through the same exit and has not
-# been run with that program since.
+# been run with that program since: both count as not run. The host code behind such batches
+# (predicted, ragged, both paths, continuations) runs under the sanitizers, leak check included,
+# in test_host_runtime.py without a GPU; their results are compared with the oracle, without
+# sanitizers, in test_gpu_parity.py.
 EXIT_NOT_SHOWN = {"config 4 predicted", "random ragged"}
 RUN_PARAMS = [pytest.param(*c, id=c[0], marks=[pytest.mark.skip(
     reason="the leak check at the program's exit did not return; cause not shown")]

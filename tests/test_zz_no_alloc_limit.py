@@ -30,7 +30,7 @@ def test_largest_batch_of_the_scratch():
     while need(sizes + [n], H) <= LIMIT:
         sizes.append(n)
     last = next(k for k in range(n, -1, -1) if need(sizes + [k], H) <= LIMIT)
-    fits, over = sizes + [last], sizes + [last + 64]
+    fits, over = sizes + [last], sizes + [last + 1]
     assert LIMIT - need(fits, H) < 4096 and need(over, H) > LIMIT
     rng = np.random.default_rng(5)
     N = sum(over)
