@@ -875,16 +875,22 @@ int do_finalize(svf_batch* h) {
     return SVF_OK;
 }
 
-// A kernel on ``device`` may store words at p: memory of that device (another
-// device's, or host memory, is left to the runtime's copy), word-aligned.
-bool kernel_writable(const void* p, int device) {
+// A kernel on ``device`` may store ``bytes`` of words at p: memory of that
+// device (another device's, or host memory, is left to the runtime's copy),
+// word-aligned, all of it in p's allocation (one that is too short is left to
+// the runtime, whose copy refuses it).
+bool kernel_writable(const void* p, size_t bytes, int device) {
     hipPointerAttribute_t at;
-    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == device &&
-           (reinterpret_cast<uintptr_t>(p) & 3) == 0;
+    const uintptr_t at_p = reinterpret_cast<uintptr_t>(p);
+    return at.type == hipMemoryTypeDevice && at.device == device && (at_p & 3) == 0 &&
+           at_p + bytes <= reinterpret_cast<uintptr_t>(base) + size;
 }
 
 // p is memory of the runtime's (page-locked, managed): it copies there directly.
@@ -1194,7 +1200,7 @@ int svf_read(svf_batch* h, int32_t slot, int32_t* start, int32_t* finish, int32_
         int32_t* const dst[4] = {start, finish, preempt, admit_seq};
         for (int x = 0; x < 4; ++x) {
             if (!dst[x]) continue;
-            if (kernel_writable(dst[x], h->device)) {
+            if (kernel_writable(dst[x], bytes, h->device)) {
                 C.src[arrays] = src[x] + base;
                 C.dst[arrays++] = dst[x];
             } else if (bytes) {

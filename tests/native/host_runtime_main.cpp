@@ -8,6 +8,7 @@
 //   reset       a reset whose launch fails leaves the outputs to the next one
 //   rings       who writes the first ring, by its length
 //   reads       svf_read into host memory of every kind and size
+//   device      svf_read into device memory, long enough and too short
 //   whole       every call on batches of both paths side by side
 //   validate    validation on several threads against one thread
 #include <hip/hip_runtime_api.h>
@@ -48,12 +49,22 @@ void forget(void* p) {
     std::lock_guard<std::mutex> lock(g_mu);
     g_mem.erase((uintptr_t)p);
 }
-hipMemoryType kind_of(const void* p) {
+// the known range that p is in
+hipMemoryType kind_of(const void* p, uintptr_t* base = nullptr, size_t* size = nullptr) {
     std::lock_guard<std::mutex> lock(g_mu);
     auto it = g_mem.upper_bound((uintptr_t)p);
     if (it == g_mem.begin()) return hipMemoryTypeUnregistered;
     --it;
-    return (uintptr_t)p < it->first + it->second.first ? it->second.second : hipMemoryTypeUnregistered;
+    if ((uintptr_t)p >= it->first + it->second.first) return hipMemoryTypeUnregistered;
+    if (base) *base = it->first;
+    if (size) *size = it->second.first;
+    return it->second.second;
+}
+// n bytes at p lie in one range, or in none that is known
+bool inside(const void* p, size_t n) {
+    uintptr_t base = 0;
+    size_t size = 0;
+    return kind_of(p, &base, &size) == hipMemoryTypeUnregistered || (uintptr_t)p + n <= base + size;
 }
 
 }  // namespace
@@ -76,6 +87,7 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
 hipError_t hipHostFree(void* p) { forget(p); free(p); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+    if (!inside(d, n) || !inside(s, n)) return hipErrorInvalidValue;  // as the runtime does
     ++g_copies;
     if (kind_of(d) == hipMemoryTypeHost) ++g_into_pinned;
     memcpy(d, s, n);
@@ -85,6 +97,12 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
     memset(a, 0, sizeof *a);
     a->type = kind_of(p);
     return a->type == hipMemoryTypeUnregistered ? hipErrorInvalidValue : hipSuccess;
+}
+hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDeviceptr_t p) {
+    uintptr_t b = 0;
+    if (kind_of(p, &b, size) == hipMemoryTypeUnregistered) return hipErrorNotFound;
+    *base = (hipDeviceptr_t)b;
+    return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
@@ -117,6 +135,8 @@ hipError_t launch_init_ring(int32_t* p, int64_t n, int32_t, hipStream_t) {
 }
 hipError_t launch_copy4(const CopyArgs& C, int arrays, hipStream_t) {
     ++g_copy_kernels;
+    for (int x = 0; x < arrays; ++x)
+        if (!inside(C.dst[x], 4 * (size_t)C.n)) abort();  // a write out of range
     for (int x = 0; x < arrays; ++x) memcpy(C.dst[x], C.src[x], 4 * (size_t)C.n);
     return hipSuccess;
 }
@@ -314,6 +334,36 @@ void reads_mode() {
     expect(g_mem.empty(), "everything released", (long long)g_mem.size());
 }
 
+void device_mode() {
+    g_pattern = true;
+    for (int64_t n : {int64_t(1000), int64_t(3000000)}) {
+        Batch b = plain(n, 1000);
+        const svf_batch_desc d = b.desc();
+        svf_batch* h = nullptr;
+        expect(svf_create(&d, nullptr, &h) == SVF_OK && svf_run(h) == SVF_OK, "create and run");
+        int32_t* buf[4];
+        for (int32_t*& p : buf) (void)hipMalloc((void**)&p, 4 * (size_t)n);
+        g_copies = g_copy_kernels = 0;
+        expect(svf_read(h, 0, buf[0], buf[1], buf[2], buf[3], 1) == SVF_OK, "read");
+        expect(g_copy_kernels == 1 && g_copies == 0, "one launch", g_copy_kernels, g_copies);
+        for (int x = 0; x < 4; ++x)
+            expect(buf[x][0] == x && buf[x][n - 1] == (int32_t)(4 * (n - 1) + x), "the outputs", n, x);
+        // a destination that is too short is the runtime's to refuse
+        for (int x = 0; x < 4; ++x) {
+            int32_t* dst[4] = {buf[0], buf[1], buf[2], buf[3]};
+            int32_t* small = nullptr;
+            (void)hipMalloc((void**)&small, 4 * (size_t)n - 4);
+            dst[x] = small;
+            expect(svf_read(h, 0, dst[0], dst[1], dst[2], dst[3], 1) == SVF_EHIP, "too short", n, x);
+            dst[x] = buf[x] + 1;
+            expect(svf_read(h, 0, dst[0], dst[1], dst[2], dst[3], 1) == SVF_EHIP, "too short at its end", n, x);
+            (void)hipFree(small);
+        }
+        for (int32_t* p : buf) (void)hipFree(p);
+        svf_destroy(h);
+    }
+}
+
 // Ragged instances, some empty, of at least ``least`` requests together, plans
 // that differ from the truth in a quarter of them, bits.
 Batch ragged(std::mt19937_64& rng, int64_t least, int longest) {
@@ -444,6 +494,7 @@ int main(int argc, char** argv) {
     if (mode == "reset") reset_mode();
     else if (mode == "rings") rings_mode();
     else if (mode == "reads") reads_mode();
+    else if (mode == "device") device_mode();
     else if (mode == "whole") whole_mode();
     else if (mode == "validate") validate_mode();
     else return 2;

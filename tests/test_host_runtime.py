@@ -45,7 +45,7 @@ def run(exe, mode):
     assert f"{mode}: ok" in r.stdout
 
 
-@pytest.mark.parametrize("mode", ["reset", "rings", "reads", "whole", "validate"])
+@pytest.mark.parametrize("mode", ["reset", "rings", "reads", "device", "whole", "validate"])
 def test_under_address_and_undefined_sanitizers(address, mode):
     run(address, mode)
 
