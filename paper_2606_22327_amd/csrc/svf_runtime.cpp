@@ -1212,8 +1212,17 @@ int svf_read(svf_batch* h, int32_t slot, int32_t* start, int32_t* finish, int32_
     }
     const int32_t* const src[4] = {h->d_start + base, h->d_fin_out + base, h->d_pre + base, h->d_seq + base};
     int32_t* dst[4] = {start, finish, preempt, admit_seq};
+    // Page-locked destinations need no staging: one copy each.
     int wanted = 0;
-    for (int32_t* p : dst) wanted += p != nullptr;
+    for (int x = 0; x < 4; ++x) {
+        if (!dst[x]) continue;
+        if (bytes && known_to_runtime(dst[x])) {
+            HIPCHK(hipMemcpyAsync(dst[x], src[x], bytes, k, h->stream));
+            dst[x] = nullptr;
+        } else {
+            ++wanted;
+        }
+    }
     if (bytes && wanted > 1 && h->d_pack) {
         // side by side on the device, then one copy
         svfk::CopyArgs C{};
@@ -1234,15 +1243,6 @@ int svf_read(svf_batch* h, int32_t slot, int32_t* start, int32_t* finish, int32_
         for (int x = 0; x < 4; ++x)
             if (dst[x]) memcpy(dst[x], host.get() + bytes * arrays++, bytes);
         return ok();
-    }
-    if (bytes * wanted >= READ_LARGE) {
-        // page-locked destinations need no staging: one copy each at the link's rate
-        for (int x = 0; x < 4; ++x)
-            if (dst[x] && known_to_runtime(dst[x])) {
-                HIPCHK(hipMemcpyAsync(dst[x], src[x], bytes, k, h->stream));
-                dst[x] = nullptr;
-                --wanted;
-            }
     }
     if (bytes * wanted >= READ_LARGE && !h->pinned &&
         hipHostMalloc((void**)&h->pinned, READ_SLOTS * READ_SLOT, hipHostMallocDefault) != hipSuccess) {

@@ -315,19 +315,28 @@ void reads_mode() {
                     if (locked >> x & 1) forget(buf[x]);
                     free(buf[x]);
                 }
-                if (16 * n > (256 << 10)) {
-                    // page-locked memory is written directly, one copy per array
-                    const bool slots = pageable >= (8 << 20);
-                    expect(slots || (g_copies == want && g_into_pinned == lock), "one copy per array", n, wanted);
-                    expect(slots || g_host_mallocs == before, "no slots for less than 8 MB", n, wanted);
+                // page-locked memory is written directly, one copy per array
+                expect(g_into_pinned == lock || pageable >= (8 << 20), "a copy per page-locked array", n, wanted);
+                if (pageable >= (8 << 20)) {
                     const int64_t per = (4 * n + 4 * SLOT - 1) / (4 * SLOT);
-                    expect(!slots || g_copies == lock + per * (want - lock), "copies of a large read", g_copies, wanted);
-                } else if (want == 1) {
-                    expect(g_copy_kernels == 0 && g_copies == 1, "one small array in one copy", n, wanted);
-                } else if (want > 1) {
-                    expect(g_copy_kernels == 1 && g_copies == 1, "small arrays side by side", n, wanted);
+                    expect(g_copies == lock + per * (want - lock), "copies of a large read", g_copies, wanted);
+                    continue;
                 }
+                expect(g_host_mallocs == before, "no slots for less than 8 MB", n, wanted);
+                // small ordinary ones side by side in one copy
+                const bool packed = 16 * n <= (256 << 10) && want - lock > 1;
+                expect(g_copy_kernels == packed, "packed", n, wanted);
+                expect(g_copies == lock + (packed ? 1 : want - lock), "copies", g_copies, wanted);
             }
+        // a page-locked destination that is too short is the runtime's to refuse
+        if (n > 1) {
+            int32_t* small = (int32_t*)malloc(4 * (size_t)n - 4);
+            std::vector<int32_t> other((size_t)n);
+            know(small, 4 * (size_t)n - 4, hipMemoryTypeHost);
+            expect(svf_read(h, 0, other.data(), small, nullptr, nullptr, 0) == SVF_EHIP, "too short", n);
+            forget(small);
+            free(small);
+        }
         expect(g_host_mallocs <= 1, "slots are pinned once per handle", g_host_mallocs);
         svf_destroy(h);
     }
