@@ -540,11 +540,16 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const int64_t* off,
     // per running request past the 64 in registers) when the ring does not fit
     // in LDS, or when few requests run at once: the list's checks and
     // insertions touch the running requests that finish before the candidate,
-    // the ring's the candidate's whole planned length.  Measured, list against
-    // ring: 1.7 against 4.2 ms at about 140 concurrent requests (3 x 4096 x
-    // 1000), 11.1 against 59 ms at about 170 (16384 x 5000), 412 against 162
-    // ms at about 930 (64 x 200,000); the estimate is M / (mean s + mean o /
-    // 2) and the crossover is taken at 512.  The list gets the largest
+    // the ring's the candidate's whole planned length.  The estimate e = M /
+    // (mean s + mean o / 2) is compared with 512.  Measured, simulation in ms,
+    // list against ring: lengths to 2,048, 3 x 4096 x 1000 (e 140) 1.7 against
+    // 4.2; lengths to 4,096, 16384 x 5000 (e 280) 11.1 against 59, 8,192
+    // instances e 500 1.0 against 6.0, e 1000 2.2 against 11.5; lengths of 50
+    // to 300, 8,192 instances e 350 1.35 against 1.75, e 550 2.5 against 1.9,
+    // 64 instances e 150 0.61 against 0.63, e 450 0.74 against 0.57; lengths to
+    // 8,192, mean 400, 64 x 200,000 (e 930) 412 against 162.  So 512 is right
+    // for many instances of short requests, high for few of them and low for
+    // long requests: the lengths are not in the rule.  The list gets the largest
     // capacity that still lets as many waves reside as the list kernel's
     // registers allow; segments that outgrow it stop, and a second launch with
     // room for the bound on concurrent requests (and for finished entries not
@@ -630,7 +635,13 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const int64_t* off,
     h->ring_used = (h->n_known > 0 && !h->list_known) || (h->any_stepped && !h->list_stepped);
     // The waves of the first simulation launch of each path set their issue
     // priorities (timing only).
-    // With at most one segment per SIMD (four per CU) there is nothing to arbitrate.
+    // With at most one segment per SIMD (four per CU) there is nothing to
+    // arbitrate.  Measured, on against off, simulation in ms: heavy traffic 300
+    // to 768 instances equal, 1,024 (if they were on there) 3.41 against 3.51,
+    // 2,048 3.76 against 4.01, 16,384 11.1 against 12.6; planned with
+    // predicted lengths 63.2 against 64.6, under next-step admission 141
+    // against 149; Poisson 3 x 4,096 x 1,000 1.65 against 1.70, with 1-bit SVF
+    // 3.47 against 3.52.
     {
         int ncu = 0;
         const char* pp = getenv("SVFSIM_ISSUE_PRIO");  // "0": all waves at one priority
