@@ -508,7 +508,9 @@
     "s_sub_i32 %[wb], %[wb], 64\n\t"                                          \
     EV_RELOAD                                                                 \
                                                                               \
-    /* visit */                                                               \
+    /* visit (at the start of a cache line: 4 bytes further on the loop took  \
+       1.66 in place of 1.62 ms on 3 x 4096 x 1000, 0.59 for 0.57 on 512) */  \
+    ".p2align 6\n"                                                            \
     ".Lev_visit_%=:\n\t"                                                      \
     "s_add_i32 s[eU], %[seq], %[nstg]\n\t"                                    \
     "s_cmp_gt_i32 s[eU], %[n1]\n\t"                                           \
