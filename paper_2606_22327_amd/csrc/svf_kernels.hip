@@ -1457,8 +1457,11 @@ struct StepList {
             const int top = ln, base = max(top - 64, 0);
             const int jr = min(base + lane, top - 1);
             const uint64_t dm = ballot(F[jr] <= t);
-            if (dm == 0ull) break;
             const uint32_t q = Q[jr];
+            if (dm == 0ull) {  // whole groups ended: entry top - 1 is now the last
+                tot = (uint32_t)__builtin_amdgcn_readlane((int)q, 63);
+                break;
+            }
             ln = top - ((int)__popcll(dm) - (64 - (top - base)));
             if (ln > base) {
                 tot = (uint32_t)__builtin_amdgcn_readlane((int)q, ln - 1 - base);

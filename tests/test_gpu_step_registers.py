@@ -153,3 +153,23 @@ def test_planned_finish_shared_by_more_than_2_31_tokens_removed(base, per_step, 
     assert r["start"][base + 284 * per_step] == 284 and int(r["preempt"].sum()) == 0
     check(b)
     check(b, chunks=(100, 150, 20, 10, 5))
+
+
+@pytest.mark.parametrize("k", [63, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("policy", ["fcfs", "svf+cur"])
+def test_planned_entries_that_end_in_whole_groups(k, policy):
+    """Past the register form's budget the planned profile is read in groups of
+    64 from its end: k entries end at step 3, 30 stay, and what they held goes
+    to the requests that wait."""
+    M, n = (1 << 23) - 1, k + 30
+    s = M // (n + 3)
+    late = 40
+    a = np.concatenate([np.zeros(n), np.ones(late)])
+    plan = np.concatenate([np.full(k, 3), np.full(30, 50), np.full(late, 20)])
+    o = np.concatenate([np.full(k, 3), np.full(30, 40), np.full(late, 25)])
+    part = {"arrival": a, "prompt": np.full(n + late, s), "output": o, "plan_len": plan}
+    b = W.assemble(f"groups{k}", [part], M, (policy,))
+    r = oracle.run(b, policy)
+    assert (r["start"][:n] == 0).all() and (r["start"][n:] == 3).sum() >= 30
+    check(b)
+    check(b, chunks=(2, 1, 1, 5))
