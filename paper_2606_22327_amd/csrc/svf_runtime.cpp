@@ -547,7 +547,7 @@ int plan_batch(svf_batch* h, const svf_batch_desc* d, const int64_t* off,
     // instances e 500 1.0 against 6.0, e 1000 2.2 against 11.5; lengths of 50
     // to 300, 8,192 instances e 350 1.35 against 1.75, e 550 2.5 against 1.9,
     // 64 instances e 150 0.61 against 0.63, e 450 0.74 against 0.57; lengths to
-    // 8,192, mean 400, 64 x 200,000 (e 930) 412 against 162.  So 512 is right
+    // 8,192, mean 400, 64 x 200,000 (e 930) 412 against 159.  So 512 is right
     // for many instances of short requests, high for few of them and low for
     // long requests: the lengths are not in the rule.  The list gets the largest
     // capacity that still lets as many waves reside as the list kernel's
